@@ -57,7 +57,7 @@ struct HopPlan {
   int64_t tiles_word, ticket_word, tile_stride;
   int items;
   bool table;                      // dedup through the state's per-vertex table (small hops)
-  int32_t span, routers, owners;   // else by owners: destinations per router, routers, owners
+  int32_t routers, owners, lane_log;   // else by owners: routers, owners, lanes (log 2) per routed group
 };
 
 struct SamplePlan {
@@ -119,13 +119,18 @@ int plan_sampling(int32_t num_seeds, const int32_t* fanouts, int32_t num_layers,
     if (hp.table) {
       hp.tile_stride = gmb::scan_tiles(hp.cap_nnz, hp.items);
     } else {
-      // a relabel tile is one router: `span` destinations whose edges fit it
+      // a relabel tile is one router: at most `span` destinations, whose
+      // edges fit it
       while (gmb::kScanBlock * hp.items < hp.fanout) hp.items *= 2;
-      hp.span = std::min(gmb::kMaxSpan, std::max(1, gmb::kScanBlock * hp.items / hp.fanout));
-      const int64_t routers = std::max<int64_t>(1, (hp.cap_dst + hp.span - 1) / hp.span);
+      const int span = std::min(gmb::kMaxSpan, std::max(1, gmb::kScanBlock * hp.items / hp.fanout));
+      int64_t routers = std::max<int64_t>(1, (hp.cap_dst + span - 1) / span);
       if (routers > gmb::kMaxRouters)
         return fail(GMB_EINVAL, "hop %d: %lld destinations need %lld routers, above %d", h,
                     static_cast<long long>(hp.cap_dst), static_cast<long long>(routers), gmb::kMaxRouters);
+      // the destinations are split evenly over the routers: from half a
+      // chip on, a whole number of routers per CU
+      if (routers > gmb::kComputeUnits / 2)
+        routers = (routers + gmb::kComputeUnits - 1) / gmb::kComputeUnits * gmb::kComputeUnits;
       hp.routers = static_cast<int32_t>(routers);
       const int64_t pairs = hp.cap_nnz + hp.cap_dst;
       int64_t owners = std::max<int64_t>(1, (pairs + gmb::kOwnerPairs - 1) / gmb::kOwnerPairs);
@@ -138,6 +143,10 @@ int plan_sampling(int32_t num_seeds, const int32_t* fanouts, int32_t num_layers,
         if ((pairs + lower - 1) / lower <= gmb::kOwnerSlots * 3 / 4) owners = lower;
       }
       hp.owners = static_cast<int32_t>(std::min<int64_t>(gmb::kMaxOwners, owners));
+      // lanes per group of pairs in the owner kernel: the group's size at
+      // full capacity, rounded down to a power of two, 4 .. 64
+      hp.lane_log = 2;
+      while (hp.lane_log < 6 && (int64_t{2} << hp.lane_log) * hp.routers * hp.owners <= pairs) ++hp.lane_log;
       hp.tile_stride = hp.routers;
     }
     hp.tiles_word = zero_words;
@@ -180,7 +189,7 @@ int plan_sampling(int32_t num_seeds, const int32_t* fanouts, int32_t num_layers,
   p.off_res = off;
   off = align_up(off + 4 * static_cast<size_t>(pairs));
   p.off_owner = off;
-  off = align_up(off + 4 * static_cast<size_t>(owner_words));
+  off = align_up(off + sizeof(uint16_t) * static_cast<size_t>(owner_words));
   p.off_rs = off;
   off = align_up(off + 4 * static_cast<size_t>(routers));
   p.scratch_total = off;
@@ -289,7 +298,7 @@ int run_sampling(const gmb_csr* csr, const int32_t* seeds, int32_t num_seeds, in
   if (e != hipSuccess) return hip_fail(e, "seed launch");
   uint2* pairs = reinterpret_cast<uint2*>(scr + p.off_pairs);
   int32_t* answers = reinterpret_cast<int32_t*>(scr + p.off_res);
-  int32_t* owner_off = reinterpret_cast<int32_t*>(scr + p.off_owner);
+  uint16_t* owner_off = reinterpret_cast<uint16_t*>(scr + p.off_owner);
   int32_t* region = reinterpret_cast<int32_t*>(scr + p.off_rs);
   for (int h = 0; h < num_layers; ++h) {
     const HopPlan& hp = p.hop[h];
@@ -318,7 +327,7 @@ int run_sampling(const gmb_csr* csr, const int32_t* seeds, int32_t num_seeds, in
       continue;
     }
     gmb::RouteArgs ra{hops[h].sizes, hops[h].indptr, ids, hops[h].nbr, pairs, owner_off, region,
-                      csr->num_nodes, hp.span, hp.routers, hp.owners};
+                      csr->num_nodes, hp.routers, hp.owners};
     if (hp.fanout <= 64) {
       gmb::SampleArgs sa{ids, hops[h].sizes, hops[h].indptr, hops[h].nbr, status, hp.fanout, hp.layer, k0, k1,
                          h == 0 ? 1 : 0, fix};
@@ -330,7 +339,8 @@ int run_sampling(const gmb_csr* csr, const int32_t* seeds, int32_t num_seeds, in
       e = gmb::launch_route(ra, s);
       if (e != hipSuccess) return hip_fail(e, "route launch");
     }
-    gmb::OwnerArgs oa{pairs, owner_off, region, answers, table, status, hp.routers, hp.owners, owner_slots()};
+    gmb::OwnerArgs oa{pairs, owner_off, region, answers, table, status, hp.routers, hp.owners, hp.lane_log,
+                      owner_slots()};
     e = gmb::launch_owner(oa, s);
     if (e != hipSuccess) return hip_fail(e, "owner launch");
     gmb::RankArgs rk{};
@@ -345,7 +355,6 @@ int run_sampling(const gmb_csr* csr, const int32_t* seeds, int32_t num_seeds, in
     rk.ticket = hops[h].ticket;
     rk.totals = totals;
     rk.hop = h;
-    rk.span = hp.span;
     for (int v = 1; h + v < num_layers; ++v) {
       rk.indptr[v] = hops[h + v].indptr;
       rk.fanout[v] = hops[h + v].fanout;

@@ -74,10 +74,11 @@ struct AssignArgs {
   int32_t fanout[GMB_MAX_LAYERS];
 };
 
-// Dedup by owners (sample.hip): a router takes `span` destinations, whose
-// edges fit one relabel tile (span * fanout <= kScanBlock * items), and
-// routes them with the destinations themselves (at most kMaxRouteEntries
-// pairs); an owner's LDS hash table has kOwnerSlots slots.
+// Dedup by owners (sample.hip): a router takes an even share of the hop's
+// destinations, at most kMaxSpan, whose edges fit one relabel tile (share *
+// fanout <= kScanBlock * items), and routes them with the destinations
+// themselves (at most kMaxRouteEntries pairs); an owner's LDS hash table has
+// kOwnerSlots slots.
 constexpr int kMaxRouters = 2048;
 constexpr int kMaxOwners = 4096;
 constexpr int kMaxRouteEntries = 8192;
@@ -111,22 +112,23 @@ struct RouteArgs {
   const int32_t* ids;      // the destinations: ids[0 .. n_dst)
   const int32_t* nbr;      // the hop's sampled vertices [nnz]
   uint2* pairs;            // [cap_dst + cap_nnz] (key, value)
-  int32_t* off;            // [(owners + 1) * routers], owner-major
+  uint16_t* off;           // [(owners + 1) * routers], owner-major (a region holds at most kMaxRouteEntries)
   int32_t* rs;             // [routers] region start of each router
   int64_t num_nodes;
-  int32_t span, routers, owners;
+  int32_t routers, owners;
 };
 
 // Owner arguments of one hop (k_owner).
 struct OwnerArgs {
   const uint2* pairs;
-  const int32_t* off;
+  const uint16_t* off;
   const int32_t* rs;
   int32_t* res;            // [cap_dst + cap_nnz] answers, at the pairs' positions
   uint32_t* table;         // the state's per-vertex table (overflow only)
   uint32_t* status;
   int32_t routers, owners;
-  int32_t max_slots;       // LDS table size limit, a power of two in 64 .. kOwnerSlots
+  int32_t lane_log;        // 2^lane_log lanes take a router's group, 2 .. 6
+  int32_t max_slots;       // LDS table size, a power of two in 64 .. kOwnerSlots
 };
 
 // Relabel arguments of hop `hop` (k_rank).  Value v >= 1 of its scan
@@ -143,7 +145,6 @@ struct RankArgs {
   uint32_t* ticket;
   int32_t* totals;
   int hop;
-  int32_t span;
   int32_t* indptr[GMB_MAX_LAYERS];
   int32_t fanout[GMB_MAX_LAYERS];
 };

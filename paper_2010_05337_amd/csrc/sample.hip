@@ -259,20 +259,65 @@ __device__ __forceinline__ void emit_edge(int32_t pos, int32_t u, int32_t* nbr, 
   if (!valid_vertex(u, num_nodes)) raise_status(status, GMB_STATUS_ERANGE);
 }
 
+// Floyd's rule for one group of G lanes whose lane i < f holds its draw
+// t_i in [0, j_i], j_i = base + i (lanes at or past f hold ~0u): in draw
+// order, x_s = t_s unless an earlier x already equals t_s, then x_s = j_s.
+// On return x is lane i's slot x_i and rank the number of slots below it
+// (its position in the sorted row).  `s_x` is the group's G words of LDS,
+// 16-byte aligned; the group lies within one wave, whose LDS accesses
+// execute in order, so no barrier is needed.
+//
+// The rule is triangular (x_s depends on earlier x only), so starting from
+// x = t and applying it to all lanes at once until nothing changes ends in
+// its one solution; after pass n the first n entries are final, and most
+// groups are done after one to three passes.  A pass costs one LDS write,
+// G / 4 broadcast reads of 16 bytes and G compares; resolving the rule
+// entry by entry in every lane's registers took G (G - 1) / 2 compares
+// (G <= 16), and one cross-lane vote per entry a chain of f LDS round trips
+// (G > 16).
+typedef uint32_t Words4 __attribute__((ext_vector_type(4), may_alias));
+template <int G>
+__device__ __forceinline__ void floyd_resolve(uint32_t& x, uint32_t& rank, uint32_t base, uint32_t f, int lane,
+                                              uint32_t* s_x) {
+  const uint32_t t = x, j = base + lane;
+  const bool live = static_cast<uint32_t>(lane) < f;
+  uint32_t v[G];
+  for (;;) {
+    s_x[lane] = x;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+    for (int q = 0; q < G / 4; ++q) {
+      const Words4 w = reinterpret_cast<const Words4*>(s_x)[q];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) v[4 * q + i] = w[i];
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    bool hit = false;
+#pragma unroll
+    for (int r = 0; r < G - 1; ++r) hit |= (v[r] == t) & (lane > r);
+    const uint32_t y = (hit & live) ? j : t;
+    const bool changed = y != x;
+    x = y;
+    if (!__any(changed)) break;   // v holds the final slots
+  }
+  rank = 0;
+#pragma unroll
+  for (int r = 0; r < G; ++r) rank += v[r] < x ? 1u : 0u;
+}
+
 // Sampling of a hop whose dedup runs through the state's per-vertex table
 // (the small hops before the last: few edges, so few table lines).
 // G lanes per destination (G >= fanout, G a power of two <= 64): lane i
-// draws t_i uniform in [0, j_i], j_i = d - f + i; Floyd's rule is then
-// resolved in draw order with one group-wide vote per step (x_s = t_s
-// unless an earlier lane already holds t_s, then x_s = j_s), and every lane
-// finds the rank of its slot among the group's.  The grid also covers the
-// previous hop's edges for the deferred local ids.
+// draws t_i uniform in [0, j_i], j_i = d - f + i; floyd_resolve then gives
+// every lane its slot and the slot's rank among the group's.  The grid also
+// covers the previous hop's edges for the deferred local ids.
 template <int G, bool WIDE>
 __global__ __launch_bounds__(256) void k_sample_table(CsrArgs ga, const int32_t* ids, const int32_t* sizes,
                                                 const int32_t* blk_indptr, int64_t cap_dst,
                                                 int32_t* nbr, uint32_t* table, uint32_t* status,
                                                 int fanout, int layer, uint32_t k0, uint32_t k1,
                                                 int check_seeds, DeferredArgs fix) {
+  __shared__ __attribute__((aligned(16))) uint32_t s_x[256];
   const CsrView g = view(ga);
   const int64_t tid = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
   const int64_t p = tid / G;
@@ -314,22 +359,11 @@ __global__ __launch_bounds__(256) void k_sample_table(CsrArgs ga, const int32_t*
     }
   } else {
     const uint32_t f = static_cast<uint32_t>(fanout);
-    uint32_t j = 0, t = 0;
-    if (static_cast<uint32_t>(lane) < f) {
-      j = static_cast<uint32_t>(d - fanout) + lane;
-      t = draw_below(k0, k1, static_cast<uint32_t>(v), static_cast<uint32_t>(layer), lane, j + 1);
-    }
-    uint32_t x = t;
-    const int group_base = (threadIdx.x & 63) & ~(G - 1);
-    const uint64_t group_mask = (G == 64) ? ~0ull : ((1ull << G) - 1);
-    for (uint32_t s = 1; s < f; ++s) {
-      const uint32_t ts = __shfl(t, s, G);
-      const bool hit = static_cast<uint32_t>(lane) < s && x == ts;
-      const uint64_t votes = (__ballot(hit) >> group_base) & group_mask;
-      if (static_cast<uint32_t>(lane) == s && votes != 0) x = j;
-    }
-    uint32_t rank = 0;
-    for (uint32_t s = 0; s < f; ++s) rank += (__shfl(x, s, G) < x) ? 1u : 0u;
+    const uint32_t base = static_cast<uint32_t>(d - fanout);
+    uint32_t x = ~0u, rank = 0;
+    if (static_cast<uint32_t>(lane) < f)
+      x = draw_below(k0, k1, static_cast<uint32_t>(v), static_cast<uint32_t>(layer), lane, base + lane + 1);
+    floyd_resolve<G>(x, rank, base, f, lane, &s_x[threadIdx.x - lane]);
     if (static_cast<uint32_t>(lane) < f) {
       pos = off + static_cast<int32_t>(rank);
       u = g.indices[begin + x];
@@ -607,16 +641,34 @@ __global__ __launch_bounds__(kScanBlock) void k_assign(AssignArgs a, CsrArgs ga,
   }
 }
 
-// The destinations [p0, p1) of router w (span destinations each; the last
-// routers may be empty) and their edges [e0, e1).
+// Destinations per router: the hop's actual destinations split evenly over
+// all its routers.  The plan gives every hop enough routers for its
+// capacity, so an even share never exceeds a relabel tile.  (With shares of
+// the full capacity each, only n_dst / cap_dst of the routers had work: 143
+// of 242, on 143 of 256 CUs, for 39k of 66k destinations; with 256 even
+// shares and the Floyd passes above k_sample_route went from 25.4 to 14.8 us
+// there, k_rank from 15.2 to 11.9 us.)
+__device__ __forceinline__ int32_t router_span(int32_t n_dst, int32_t routers) {
+  const int32_t n = n_dst > 0 ? n_dst : 0;
+  const int32_t span = static_cast<int32_t>((static_cast<int64_t>(n) + routers - 1) / routers);
+  return span < 1 ? 1 : span;
+}
+
+// The destinations [p0, p1) of router w (the last routers may be empty).
+__device__ __forceinline__ void router_dsts(int w, int32_t routers, int32_t n_dst, int32_t& p0, int32_t& p1) {
+  const int32_t span = router_span(n_dst, routers);
+  const int64_t a = static_cast<int64_t>(w) * span;
+  p0 = static_cast<int32_t>(a < n_dst ? a : n_dst);
+  p1 = static_cast<int32_t>(a + span < n_dst ? a + span : n_dst);
+}
+
+// The same and their edges [e0, e1).
 struct RouterRange {
   int32_t p0, p1, e0, e1;
 };
-__device__ __forceinline__ RouterRange router_range(int w, int32_t span, int32_t n_dst, const int32_t* indptr) {
+__device__ __forceinline__ RouterRange router_range(int w, int32_t routers, int32_t n_dst, const int32_t* indptr) {
   RouterRange r;
-  const int64_t a = static_cast<int64_t>(w) * span;
-  r.p0 = static_cast<int32_t>(a < n_dst ? a : n_dst);
-  r.p1 = static_cast<int32_t>(a + span < n_dst ? a + span : n_dst);
+  router_dsts(w, routers, n_dst, r.p0, r.p1);
   r.e0 = indptr[r.p0];
   r.e1 = indptr[r.p1];
   return r;
@@ -659,7 +711,7 @@ __global__ __launch_bounds__(kRouteBlock) void k_route(RouteArgs a) {
   const int w = blockIdx.x;
   const int P = a.owners;
   const int32_t n_dst = load_size(&a.sizes[kNDst]);
-  const RouterRange r = router_range(w, a.span, n_dst, a.indptr);
+  const RouterRange r = router_range(w, a.routers, n_dst, a.indptr);
   const int32_t E = r.e1 - r.e0;
   const int32_t M = E + (r.p1 - r.p0);   // <= kMaxRouteEntries (host-checked span and fan-out)
   int32_t key[kRouteItems];
@@ -684,7 +736,8 @@ __global__ __launch_bounds__(kRouteBlock) void k_route(RouteArgs a) {
   __syncthreads();
   block_scan_inplace<kRouteBlock>(s_hist, P + 1, s_wave);
   const int64_t region = static_cast<int64_t>(r.e0) + r.p0;
-  for (int b = threadIdx.x; b <= P; b += kRouteBlock) a.off[static_cast<int64_t>(b) * a.routers + w] = s_hist[b];
+  for (int b = threadIdx.x; b <= P; b += kRouteBlock)
+    a.off[static_cast<int64_t>(b) * a.routers + w] = static_cast<uint16_t>(s_hist[b]);
   if (threadIdx.x == 0) a.rs[w] = static_cast<int32_t>(region);
 #pragma unroll
   for (int k = 0; k < kRouteItems; ++k) {
@@ -695,99 +748,74 @@ __global__ __launch_bounds__(kRouteBlock) void k_route(RouteArgs a) {
   }
 }
 
-// Floyd's rule for one group of G lanes whose lane i < f holds its draw
-// t_i in [0, j_i], j_i = base + i: in draw order, x_s = t_s unless an
-// earlier x already equals t_s, then x_s = j_s.  On return x is lane i's
-// slot x_i and rank the number of slots below it (its position in the
-// sorted row).  Groups of up to 16 lanes broadcast all draws once and
-// resolve the rule in registers (no dependent cross-lane steps); wider
-// groups resolve it with one group vote per step.
-template <int G>
-__device__ __forceinline__ void floyd_resolve(uint32_t& x, uint32_t& rank, uint32_t base, uint32_t f, int lane,
-                                              int group_base, uint64_t group_mask) {
-  if constexpr (G <= 16) {
-    uint32_t t[G], xs[G];
-#pragma unroll
-    for (int q = 0; q < G; ++q) t[q] = __shfl(x, q, G);
-#pragma unroll
-    for (int q = 0; q < G; ++q) {
-      bool hit = false;
-#pragma unroll
-      for (int r = 0; r < q; ++r) hit |= xs[r] == t[q];
-      xs[q] = hit ? base + q : t[q];
-    }
-    uint32_t mine = 0;
-#pragma unroll
-    for (int q = 0; q < G; ++q) mine = q == lane ? xs[q] : mine;
-    rank = 0;
-#pragma unroll
-    for (int q = 0; q < G; ++q) rank += (static_cast<uint32_t>(q) < f && xs[q] < mine) ? 1u : 0u;
-    x = mine;
-  } else {
-    const uint32_t t0 = x, j = base + lane;
-    for (uint32_t q = 1; q < f; ++q) {
-      const uint32_t tq = __shfl(t0, q, G);
-      const bool hit = static_cast<uint32_t>(lane) < q && x == tq;
-      const uint64_t votes = (__ballot(hit) >> group_base) & group_mask;
-      if (static_cast<uint32_t>(lane) == q && votes != 0) x = j;
-    }
-    rank = 0;
-    for (uint32_t q = 0; q < f; ++q) rank += (__shfl(x, q, G) < x) ? 1u : 0u;
-  }
-}
-
 // Sampling and routing in one kernel, for fan-outs up to 64 (G lanes per
-// destination as in k_sample): router w first resolves its share of the
-// previous hop's deferred local ids, loads its span of destinations (id,
-// block row offset, CSR row) into LDS with one batch of reads, samples
-// them in rounds of kRouteBlock / G destinations (all rounds' draws first,
-// then all their neighbour reads in one batch), writes the sampled ids and
-// keeps them in LDS, and routes them with the destinations as k_route does.
+// destination as in k_sample_table): router w loads its share of the
+// destinations (id, block row offset, CSR row) into LDS with two rounds of
+// independent reads (the previous hop's deferred local ids ride along),
+// samples them in rounds of kRouteBlock / G destinations (all rounds' draws
+// first, then all their neighbour reads in one batch), writes the sampled
+// ids and keeps them in LDS, and routes them with the destinations as
+// k_route does.
 constexpr int kSampleRounds = 8;   // span * G < 2 * (edges per tile) <= 8192 lanes
 template <int G, bool WIDE>
 __global__ __launch_bounds__(kRouteBlock) void k_sample_route(CsrArgs ga, SampleArgs a, RouteArgs ra) {
   __shared__ int32_t s_v[kMaxSpan];
-  __shared__ int32_t s_off[kMaxSpan];
+  __shared__ int32_t s_off[kMaxSpan + 1];
   __shared__ int32_t s_deg[kMaxSpan];
   __shared__ int64_t s_beg[kMaxSpan];
   __shared__ int32_t s_key[kMaxRouteEntries];
   __shared__ int32_t s_hist[kMaxOwners + 1];
   __shared__ int32_t s_wave[kRouteBlock / 64];
+  __shared__ __attribute__((aligned(16))) uint32_t s_x[kRouteBlock];
+  static_assert(kMaxSpan <= kRouteBlock, "one destination per thread");
   const CsrView g = view(ga);
   const int w = blockIdx.x;
   const int tid = threadIdx.x;
-  // the previous hop's deferred local ids (grid-stride; none on the first hop)
-  {
-    const int32_t n_prev = load_size(&a.fix.sizes[kNnz]);
-    const int64_t stride = static_cast<int64_t>(gridDim.x) * kRouteBlock;
-    for (int64_t e = static_cast<int64_t>(w) * kRouteBlock + tid; e < n_prev; e += stride) {
-      DeferredItem it = deferred_read(a.fix, e);
-      deferred_fetch(a.fix, it);
-      deferred_store(a.fix, e, it);
-    }
-  }
+  const int P = ra.owners;
+  // the previous hop's deferred local ids (grid-stride; none on the first
+  // hop): the first one of every thread is read beside the router's own
+  const int64_t fix_stride = static_cast<int64_t>(gridDim.x) * kRouteBlock;
+  const int64_t fix_e = static_cast<int64_t>(w) * kRouteBlock + tid;
   const int32_t n_dst = load_size(&a.sizes[kNDst]);
-  const RouterRange r = router_range(w, ra.span, n_dst, a.indptr);
-  const int32_t E = r.e1 - r.e0;
-  const int32_t K = r.p1 - r.p0;   // <= span <= kMaxSpan
-  for (int t = tid; t < K; t += kRouteBlock) {
-    const int32_t v = a.ids[r.p0 + t];
-    const int32_t off = a.indptr[r.p0 + t];
-    const bool valid = valid_vertex(v, g.num_nodes);
-    int64_t b, e;
-    row_range_t<WIDE>(g, valid ? v : 0, b, e);
+  DeferredItem it = deferred_read(a.fix, fix_e);
+  for (int b = tid; b <= P; b += kRouteBlock) s_hist[b] = 0;
+  int32_t p0, p1;
+  router_dsts(w, ra.routers, n_dst, p0, p1);
+  const int32_t K = p1 - p0;   // <= kMaxSpan
+  // thread t <= K: destination p0 + t's id and block row offset (t = K: the
+  // end of the router's edges)
+  const int32_t t0 = tid <= K ? tid : K;
+  const int32_t v = a.ids[p0 + (tid < K ? tid : 0)];
+  const int32_t off0 = a.indptr[p0 + t0];
+  const int32_t off_end = a.indptr[p1];   // (the same for all)
+  const bool valid = valid_vertex(v, g.num_nodes);
+  int64_t row_b, row_e;
+  row_range_t<WIDE>(g, valid ? v : 0, row_b, row_e);
+  deferred_fetch(a.fix, it);
+  if (tid < K) {
     if (!valid && a.check_seeds) raise_status(a.status, GMB_STATUS_ERANGE);
-    s_v[t] = v;
-    s_off[t] = off;
-    s_beg[t] = b;
-    s_deg[t] = valid ? static_cast<int32_t>(e - b) : 0;
-    s_key[E + t] = v;
+    s_v[tid] = v;
+    s_off[tid] = off0;
+    s_beg[tid] = row_b;
+    s_deg[tid] = valid ? static_cast<int32_t>(row_e - row_b) : 0;
+  }
+  if (tid == 0) s_off[K] = off_end;
+  deferred_store(a.fix, fix_e, it);
+  for (int64_t e = fix_e + fix_stride; e < it.n; e += fix_stride) {
+    DeferredItem more = deferred_read(a.fix, e);
+    deferred_fetch(a.fix, more);
+    deferred_store(a.fix, e, more);
   }
   __syncthreads();
+  RouterRange r;
+  r.p0 = p0;
+  r.p1 = p1;
+  r.e0 = s_off[0];
+  r.e1 = off_end;
+  const int32_t E = r.e1 - r.e0;
+  if (tid < K) s_key[E + tid] = v;
   // draws: lane task q = tid + k * kRouteBlock is lane q % G of destination q / G
   const int lane = tid & (G - 1);
-  const int group_base = (tid & 63) & ~(G - 1);
-  const uint64_t group_mask = (G == 64) ? ~0ull : ((1ull << G) - 1);
   const uint32_t f = static_cast<uint32_t>(a.fanout);
   int32_t pos[kSampleRounds];
   int64_t slot[kSampleRounds];
@@ -804,11 +832,11 @@ __global__ __launch_bounds__(kRouteBlock) void k_sample_route(CsrArgs ga, Sample
         slot[k] = s_beg[t] + lane;
       }
     } else {
-      uint32_t x = 0, rank = 0;
+      uint32_t x = ~0u, rank = 0;
       if (static_cast<uint32_t>(lane) < f)
         x = draw_below(a.k0, a.k1, static_cast<uint32_t>(s_v[t]), static_cast<uint32_t>(a.layer), lane,
                        static_cast<uint32_t>(d) - f + lane + 1);
-      floyd_resolve<G>(x, rank, static_cast<uint32_t>(d) - f, f, lane, group_base, group_mask);
+      floyd_resolve<G>(x, rank, static_cast<uint32_t>(d) - f, f, lane, &s_x[tid - lane]);
       if (static_cast<uint32_t>(lane) < f) {
         pos[k] = s_off[t] + static_cast<int32_t>(rank);
         slot[k] = s_beg[t] + x;
@@ -826,9 +854,7 @@ __global__ __launch_bounds__(kRouteBlock) void k_sample_route(CsrArgs ga, Sample
     if (!valid_vertex(u[k], g.num_nodes)) raise_status(a.status, GMB_STATUS_ERANGE);
   }
   // routing (see k_route), the keys from LDS
-  const int P = ra.owners;
   const int32_t M = E + K;
-  for (int b = tid; b <= P; b += kRouteBlock) s_hist[b] = 0;
   __syncthreads();
   int32_t key[kRouteItems];
   uint32_t bucket[kRouteItems];
@@ -845,7 +871,8 @@ __global__ __launch_bounds__(kRouteBlock) void k_sample_route(CsrArgs ga, Sample
   __syncthreads();
   block_scan_inplace<kRouteBlock>(s_hist, P + 1, s_wave);
   const int64_t region = static_cast<int64_t>(r.e0) + r.p0;
-  for (int b = tid; b <= P; b += kRouteBlock) ra.off[static_cast<int64_t>(b) * ra.routers + w] = s_hist[b];
+  for (int b = tid; b <= P; b += kRouteBlock)
+    ra.off[static_cast<int64_t>(b) * ra.routers + w] = static_cast<uint16_t>(s_hist[b]);
   if (tid == 0) ra.rs[w] = static_cast<int32_t>(region);
 #pragma unroll
   for (int k = 0; k < kRouteItems; ++k) {
@@ -856,22 +883,27 @@ __global__ __launch_bounds__(kRouteBlock) void k_sample_route(CsrArgs ga, Sample
   }
 }
 
-// Owner b.  Its pairs are group b of every router's region; s_seg holds
-// the running count over routers, s_start the group's address.  Each
-// vertex key keeps in LDS the minimum of its values: a known vertex's local
-// id (< kEdgeTag) wins over any edge, else the smallest edge position.
-// Answer per edge: its known local id, kFirstOccurrence if it is the
-// vertex's first edge, else -(e0 + 1) with e0 the first edge.  Two
-// destinations with the same id (a repeated seed) are reported (EDUP).
-// The pairs are read in chunks of kOwnerBlock * kOwnerItems, each thread
-// issuing its reads as one batch, once to insert and once to answer (the
-// second time from the L2).  If the table overflows (more distinct keys
-// than slots, possible only when the owner's pair count exceeds its
-// table), the owner redoes its pairs through the per-vertex table of the
-// sampler state: atomicMin, a barrier, the read-back, and the slots reset;
-// only this owner ever touches those slots, so the state stays clear.
+// Owner b.  Its pairs are group b of every router's region (a segment of
+// a few pairs per router).  Each vertex key keeps in LDS the minimum of its
+// values: a known vertex's local id (< kEdgeTag) wins over any edge, else
+// the smallest edge position.  Answer per edge: its known local id,
+// kFirstOccurrence if it is the vertex's first edge, else -(e0 + 1) with e0
+// the first edge.  Two destinations with the same id (a repeated seed) are
+// reported (EDUP).
+// 2^lane_log lanes take a segment, kOwnerSegs segments in flight per lane
+// group, so a lane's first pairs cost two rounds of reads (the segment's
+// offsets, its pair) and stay in registers for the answers; a segment's
+// further pairs, and the segments past kOwnerSegs per group, are read again
+// (from the L2).  11.1 us on 256 owners of 2.3k pairs from 256 routers;
+// finding every pair's segment by a scan of the segment lengths and a binary
+// search in LDS took 12.3 us, and an LDS copy of the pairs that this needs no
+// more.
+// If the table overflows (more distinct keys than slots), the owner redoes
+// its pairs through the per-vertex table of the sampler state: atomicMin, a
+// barrier, the read-back, and the slots reset; only this owner ever touches
+// those slots, so the state stays clear.
 constexpr int kOwnerBlock = 1024;
-constexpr int kOwnerItems = 4;
+constexpr int kOwnerSegs = 4;
 constexpr int32_t kFirstOccurrence = INT32_MIN;
 constexpr int32_t kEmptyKey = INT32_MIN;
 
@@ -881,159 +913,135 @@ __device__ __forceinline__ int32_t owner_answer(uint32_t best, uint32_t val) {
   return -static_cast<int32_t>(best & ~kEdgeTag) - 1;
 }
 
+// kOwnerSegs segments of a lane group: their starts and lengths, and this
+// lane's first pair of each (val 0, key -1 past the segment's end).
+struct OwnerSegs {
+  int32_t start[kOwnerSegs], len[kOwnerSegs];
+  uint2 pr[kOwnerSegs];
+};
+
 __global__ __launch_bounds__(kOwnerBlock) void k_owner(OwnerArgs a) {
-  __shared__ int32_t s_seg[kMaxRouters + 1];
-  __shared__ int32_t s_start[kMaxRouters];
-  __shared__ int32_t s_key[kOwnerSlots];
-  __shared__ uint32_t s_val[kOwnerSlots];
-  constexpr int kChunk = kOwnerBlock * kOwnerItems;
-  __shared__ uint2 s_pair[kChunk];   // the first chunk's pairs and positions, kept for the answers
-  __shared__ int32_t s_at[kChunk];
-  __shared__ int32_t s_wave[kOwnerBlock / 64];
+  __shared__ __attribute__((aligned(16))) int32_t s_key[kOwnerSlots];
+  __shared__ __attribute__((aligned(16))) uint32_t s_val[kOwnerSlots];
   __shared__ int s_overflow;
-  constexpr int kRouterItems = kMaxRouters / kOwnerBlock;
   const int b = blockIdx.x;
   const int W = a.routers;
-  const int64_t row = static_cast<int64_t>(b) * W;
-  {
-    int32_t lo[kRouterItems], hi[kRouterItems], rs[kRouterItems];
+  const int C = a.max_slots, shift = 32 - (31 - __clz(C));
+  const int lanes = 1 << a.lane_log;
+  const int lane = threadIdx.x & (lanes - 1), group = threadIdx.x >> a.lane_log;
+  const int groups = kOwnerBlock >> a.lane_log;
+  const uint16_t* off0 = a.off + static_cast<int64_t>(b) * W;   // segment w: [off0[w], off0[W + w]) of region w
+  auto load_segs = [&](int w0, OwnerSegs& sg) {
+    int32_t lo[kOwnerSegs], hi[kOwnerSegs], rs[kOwnerSegs];
 #pragma unroll
-    for (int k = 0; k < kRouterItems; ++k) {
-      const int w = threadIdx.x + k * kOwnerBlock;
+    for (int k = 0; k < kOwnerSegs; ++k) {
+      const int w = w0 + group + k * groups;
       const int wc = w < W ? w : 0;
-      lo[k] = a.off[row + wc];
-      hi[k] = a.off[row + W + wc];
+      lo[k] = off0[wc];
+      hi[k] = off0[W + wc];
       rs[k] = a.rs[wc];
     }
 #pragma unroll
-    for (int k = 0; k < kRouterItems; ++k) {
-      const int w = threadIdx.x + k * kOwnerBlock;
-      if (w < W) {
-        s_seg[w] = hi[k] - lo[k];
-        s_start[w] = rs[k] + lo[k];
-      }
+    for (int k = 0; k < kOwnerSegs; ++k) {
+      sg.len[k] = w0 + group + k * groups < W ? hi[k] - lo[k] : 0;
+      sg.start[k] = rs[k] + lo[k];
     }
+  };
+  auto load_pairs = [&](OwnerSegs& sg) {
+#pragma unroll
+    for (int k = 0; k < kOwnerSegs; ++k) sg.pr[k] = a.pairs[lane < sg.len[k] ? sg.start[k] + lane : 0];
+#pragma unroll
+    for (int k = 0; k < kOwnerSegs; ++k)
+      if (lane >= sg.len[k]) sg.pr[k] = make_uint2(0xFFFFFFFFu, 0u);
+  };
+  // every pair of the segments: f(position, pair)
+  auto for_pairs = [&](const OwnerSegs& sg, auto&& f) {
+#pragma unroll
+    for (int k = 0; k < kOwnerSegs; ++k) {
+      if (lane < sg.len[k]) f(sg.start[k] + lane, sg.pr[k]);
+      for (int32_t i = lane + lanes; i < sg.len[k]; i += lanes) f(sg.start[k] + i, a.pairs[sg.start[k] + i]);
+    }
+  };
+  const int step = groups * kOwnerSegs;
+  // every pair of the owner; the first round's segments are kept in `first`
+  OwnerSegs first;
+  auto for_all = [&](auto&& f) {
+    for_pairs(first, f);
+    for (int w0 = step; w0 < W; w0 += step) {
+      OwnerSegs sg;
+      load_segs(w0, sg);
+      load_pairs(sg);
+      for_pairs(sg, f);
+    }
+  };
+  load_segs(0, first);
+  for (int i = threadIdx.x; i < C / 4; i += kOwnerBlock) {   // C >= 64
+    reinterpret_cast<int4*>(s_key)[i] = make_int4(kEmptyKey, kEmptyKey, kEmptyKey, kEmptyKey);
+    reinterpret_cast<uint4*>(s_val)[i] = make_uint4(kEmpty, kEmpty, kEmpty, kEmpty);
   }
   if (threadIdx.x == 0) s_overflow = 0;
+  load_pairs(first);
   __syncthreads();
-  const int32_t M = block_scan_inplace<kOwnerBlock>(s_seg, W, s_wave);
-  if (threadIdx.x == 0) s_seg[W] = M;
-  // table size: a power of two >= 2 M (load <= 1/2), 64 .. kOwnerSlots
-  int logc = 6;
-  while ((1 << logc) < 2 * static_cast<int64_t>(M) && (1 << logc) < a.max_slots) ++logc;
-  const int C = 1 << logc, shift = 32 - logc;
-  for (int i = threadIdx.x; i < C; i += kOwnerBlock) {
-    s_key[i] = kEmptyKey;
-    s_val[i] = kEmpty;
-  }
-  __syncthreads();
-  // pair i of this owner: router w with s_seg[w] <= i < s_seg[w + 1]
-  auto pair_index = [&](int32_t i) -> int64_t {
-    int lo = 0, hi = W;   // s_seg[lo] <= i < s_seg[hi]
-    while (hi - lo > 1) {
-      const int mid = (lo + hi) >> 1;
-      if (s_seg[mid] <= i) lo = mid;
-      else hi = mid;
-    }
-    return static_cast<int64_t>(s_start[lo]) + (i - s_seg[lo]);
-  };
-  for (int32_t base = 0; base < M; base += kChunk) {
-    uint2 pr[kOwnerItems];
-    int64_t at[kOwnerItems];
-#pragma unroll
-    for (int k = 0; k < kOwnerItems; ++k) {
-      const int32_t i = base + threadIdx.x + k * kOwnerBlock;
-      at[k] = i < M ? pair_index(i) : 0;
-      pr[k] = a.pairs[at[k]];
-    }
-#pragma unroll
-    for (int k = 0; k < kOwnerItems; ++k) {
-      const int32_t i = base + threadIdx.x + k * kOwnerBlock;
-      if (base == 0) {
-        s_pair[i] = pr[k];
-        s_at[i] = static_cast<int32_t>(at[k]);
+  for_all([&](int32_t, const uint2& pr) {
+    const int32_t key = static_cast<int32_t>(pr.x);
+    if (key < 0) return;
+    uint32_t h = slot_of(pr.x, shift);
+    for (int probes = 0;; ++probes) {
+      int32_t cur = s_key[h];
+      if (cur == kEmptyKey) {
+        cur = atomicCAS(&s_key[h], kEmptyKey, key);
+        if (cur == kEmptyKey) cur = key;
       }
-      const int32_t key = static_cast<int32_t>(pr[k].x);
-      if (i >= M || key < 0) continue;
-      uint32_t h = slot_of(pr[k].x, shift);
-      for (int probes = 0;; ++probes) {
-        int32_t cur = s_key[h];
-        if (cur == kEmptyKey) {
-          cur = atomicCAS(&s_key[h], kEmptyKey, key);
-          if (cur == kEmptyKey) cur = key;
-        }
-        if (cur == key) {
-          const uint32_t old = atomicMin(&s_val[h], pr[k].y);
-          if (pr[k].y < kEdgeTag && old < kEdgeTag && old != pr[k].y) raise_status(a.status, GMB_STATUS_EDUP);
-          break;
-        }
-        if (probes + 1 >= C) {
-          s_overflow = 1;
-          break;
-        }
-        h = (h + 1) & (C - 1);
+      if (cur == key) {
+        const uint32_t old = atomicMin(&s_val[h], pr.y);
+        if (pr.y < kEdgeTag && old < kEdgeTag && old != pr.y) raise_status(a.status, GMB_STATUS_EDUP);
+        break;
       }
+      if (probes + 1 >= C) {
+        s_overflow = 1;
+        break;
+      }
+      h = (h + 1) & (C - 1);
     }
-  }
+  });
   __syncthreads();
   if (!s_overflow) {
-    for (int32_t base = 0; base < M; base += kChunk) {
-      uint2 pr[kOwnerItems];
-      int64_t at[kOwnerItems];
-#pragma unroll
-      for (int k = 0; k < kOwnerItems; ++k) {
-        const int32_t i = base + threadIdx.x + k * kOwnerBlock;
-        if (base == 0) {   // the first chunk from LDS
-          at[k] = s_at[i];
-          pr[k] = s_pair[i];
-        } else {
-          at[k] = i < M ? pair_index(i) : 0;
-          pr[k] = a.pairs[at[k]];
-        }
-      }
-#pragma unroll
-      for (int k = 0; k < kOwnerItems; ++k) {
-        const int32_t i = base + threadIdx.x + k * kOwnerBlock;
-        if (i >= M || !(pr[k].y & kEdgeTag)) continue;
-        int32_t ans = 0;   // an id outside the graph: local id 0
-        if (static_cast<int32_t>(pr[k].x) >= 0) {
-          uint32_t h = slot_of(pr[k].x, shift);
-          for (int probes = 0; probes < C; ++probes, h = (h + 1) & (C - 1)) {
-            if (s_key[h] == static_cast<int32_t>(pr[k].x)) {
-              ans = owner_answer(s_val[h], pr[k].y);
-              break;
-            }
+    for_all([&](int32_t at, const uint2& pr) {
+      if (!(pr.y & kEdgeTag)) return;
+      int32_t ans = 0;   // an id outside the graph: local id 0
+      if (static_cast<int32_t>(pr.x) >= 0) {
+        uint32_t h = slot_of(pr.x, shift);
+        for (int probes = 0; probes < C; ++probes, h = (h + 1) & (C - 1)) {
+          if (s_key[h] == static_cast<int32_t>(pr.x)) {
+            ans = owner_answer(s_val[h], pr.y);
+            break;
           }
         }
-        a.res[at[k]] = ans;
       }
-    }
+      a.res[at] = ans;
+    });
     return;
   }
   // overflow: the same through the state's per-vertex table
-  for (int32_t i = threadIdx.x; i < M; i += kOwnerBlock) {
-    const uint2 pr = a.pairs[pair_index(i)];
-    if (static_cast<int32_t>(pr.x) < 0) continue;
+  for_all([&](int32_t, const uint2& pr) {
+    if (static_cast<int32_t>(pr.x) < 0) return;
     const uint32_t old = atomicMin(&a.table[pr.x], pr.y);
     if (pr.y < kEdgeTag && old < kEdgeTag && old != pr.y) raise_status(a.status, GMB_STATUS_EDUP);
-  }
+  });
   __threadfence();
   __syncthreads();
-  for (int32_t i = threadIdx.x; i < M; i += kOwnerBlock) {
-    const int64_t at = pair_index(i);
-    const uint2 pr = a.pairs[at];
-    if (!(pr.y & kEdgeTag)) continue;
+  for_all([&](int32_t at, const uint2& pr) {
+    if (!(pr.y & kEdgeTag)) return;
     int32_t ans = 0;
     if (static_cast<int32_t>(pr.x) >= 0)
       ans = owner_answer(__hip_atomic_load(&a.table[pr.x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), pr.y);
     a.res[at] = ans;
-  }
+  });
   __threadfence();
   __syncthreads();
-  for (int32_t i = threadIdx.x; i < M; i += kOwnerBlock) {
-    const uint2 pr = a.pairs[pair_index(i)];
+  for_all([&](int32_t, const uint2& pr) {
     if (static_cast<int32_t>(pr.x) >= 0) a.table[pr.x] = kEmpty;
-  }
+  });
 }
 
 // Hop h's relabel, one workgroup per router, routers taken in ticket order
@@ -1045,19 +1053,17 @@ __global__ __launch_bounds__(kOwnerBlock) void k_owner(OwnerArgs a) {
 // repeat of a vertex new in this hop takes the local id from LDS when the
 // first occurrence is in the same router's range, else it keeps the
 // answer -(e0 + 1) and the next kernel on the stream copies local[e0].
+constexpr int kRankBlock = 512;
 template <int NV, bool WIDE, int ITEMS>
-__global__ __launch_bounds__(kScanBlock) void k_rank(RankArgs a, CsrArgs ga, int32_t* ids, uint32_t* status) {
-  constexpr int T = kScanBlock * ITEMS;
+__global__ __launch_bounds__(kRankBlock) void k_rank(RankArgs a, CsrArgs ga, int32_t* ids, uint32_t* status) {
+  constexpr int T = kScanBlock * ITEMS;      // most edges of a router
+  constexpr int kPer = (T / kRankBlock) | 1;   // entries per thread, at most
+  constexpr int kBatch = 4;                  // pairs a thread reads at once
   __shared__ int s_tile;
   __shared__ int32_t s_excl[NV];
-  __shared__ int32_t s_wave[NV * (kScanBlock / 64)];
-  // edge j of the router at slot(j): one pad word after every ITEMS
-  // entries, so that a thread's ITEMS consecutive entries start ITEMS + 1
-  // words after its neighbour's (an odd stride: no two lanes of a wave on
-  // one bank)
-  auto slot = [](int32_t j) { return j + j / ITEMS; };
-  __shared__ int32_t s_key[T + T / ITEMS];
-  __shared__ int32_t s_res[T + T / ITEMS];   // the answers; then the new vertices' local ids
+  __shared__ int32_t s_wave[NV * (kRankBlock / 64)];
+  __shared__ int32_t s_key[T];
+  __shared__ int32_t s_res[T];   // the answers; then the new vertices' local ids
   const CsrView g = view(ga);
   int32_t basev[NV];
 #pragma unroll
@@ -1065,50 +1071,53 @@ __global__ __launch_bounds__(kScanBlock) void k_rank(RankArgs a, CsrArgs ga, int
   const int32_t n_dst = load_size(&a.sizes[kNDst]);
   const int tile = claim_tile(a.ticket, &s_tile);
   const int num_tiles = gridDim.x;
-  const RouterRange r = router_range(tile, a.span, n_dst, a.indptr0);
-  const int32_t E = r.e1 - r.e0;            // <= T (host-checked span)
+  const RouterRange r = router_range(tile, num_tiles, n_dst, a.indptr0);
+  const int32_t E = r.e1 - r.e0;            // <= T (the plan's router count)
   const int32_t M = E + (r.p1 - r.p0);
   const int64_t region = static_cast<int64_t>(r.e0) + r.p0;
-  {
-    // the region (at most 2 T entries: the edges and the destinations) in
-    // one batch of reads per thread
-    uint2 pr[2 * ITEMS];
-    int32_t an[2 * ITEMS];
+  // the region (the edges and the destinations, at most 2 T entries)
+  for (int32_t i0 = 0; i0 < M; i0 += kBatch * kRankBlock) {   // uniform
+    uint2 pr[kBatch];
+    int32_t an[kBatch];
 #pragma unroll
-    for (int k = 0; k < 2 * ITEMS; ++k) {
-      const int32_t i = threadIdx.x + k * kScanBlock;
+    for (int k = 0; k < kBatch; ++k) {
+      const int32_t i = i0 + threadIdx.x + k * kRankBlock;
       const int64_t at = i < M ? region + i : 0;
       pr[k] = a.pairs[at];
       an[k] = a.res[at];
     }
 #pragma unroll
-    for (int k = 0; k < 2 * ITEMS; ++k) {
-      const int32_t i = threadIdx.x + k * kScanBlock;
+    for (int k = 0; k < kBatch; ++k) {
+      const int32_t i = i0 + threadIdx.x + k * kRankBlock;
       const int32_t j = static_cast<int32_t>(pr[k].y & ~kEdgeTag) - r.e0;
       if (i < M && (pr[k].y & kEdgeTag) && j >= 0 && j < E) {
-        s_key[slot(j)] = static_cast<int32_t>(pr[k].x);
-        s_res[slot(j)] = an[k];
+        s_key[j] = static_cast<int32_t>(pr[k].x);
+        s_res[j] = an[k];
       }
     }
   }
   __syncthreads();
-  const int base = threadIdx.x * ITEMS;
-  int32_t u[ITEMS], ans[ITEMS];
+  // each thread scans `per` consecutive edges, the router's edges split
+  // evenly; an odd count, so that the lanes' LDS reads (stride per) fall on
+  // different banks
+  const int32_t per = ((E + kRankBlock - 1) / kRankBlock) | 1;   // <= kPer
+  const int base = threadIdx.x * per;
+  int32_t u[kPer], ans[kPer];
 #pragma unroll
-  for (int q = 0; q < ITEMS; ++q) {
-    const bool in = base + q < E;
-    u[q] = in ? s_key[slot(base + q)] : -1;
-    ans[q] = in ? s_res[slot(base + q)] : 0;
+  for (int q = 0; q < kPer; ++q) {
+    const bool in = q < per && base + q < E;
+    u[q] = in ? s_key[base + q] : -1;
+    ans[q] = in ? s_res[base + q] : 0;
   }
   uint32_t flags = 0;
 #pragma unroll
-  for (int q = 0; q < ITEMS; ++q)
+  for (int q = 0; q < kPer; ++q)
     if (ans[q] == kFirstOccurrence) flags |= 1u << q;
   // the new vertices' degrees for the later hops, in one round of reads
   // (other items read vertex 0's row: one line for all of them)
   int32_t deg[ITEMS];
 #pragma unroll
-  for (int q = 0; q < ITEMS; ++q) {
+  for (int q = 0; q < kPer; ++q) {
     deg[q] = 0;
     if constexpr (NV > 1) {
       int64_t b, e;
@@ -1122,9 +1131,9 @@ __global__ __launch_bounds__(kScanBlock) void k_rank(RankArgs a, CsrArgs ga, int
   for (int v = 1; v < NV; ++v) {
     sum[v] = 0;
 #pragma unroll
-    for (int q = 0; q < ITEMS; ++q) sum[v] += ((flags >> q) & 1u) ? clamp_degree(deg[q], a.fanout[v]) : 0;
+    for (int q = 0; q < kPer; ++q) sum[v] += ((flags >> q) & 1u) ? clamp_degree(deg[q], a.fanout[v]) : 0;
   }
-  block_exclusive_scan_multi<kScanBlock, NV>(sum, thr, total, s_wave);
+  block_exclusive_scan_multi<kRankBlock, NV>(sum, thr, total, s_wave);
   if (threadIdx.x < 64) {
     int32_t ex[NV];
     const bool ok = tile_lookback_multi<NV>(a.tiles, a.tile_stride, tile, total, ex);
@@ -1144,11 +1153,11 @@ __global__ __launch_bounds__(kScanBlock) void k_rank(RankArgs a, CsrArgs ga, int
 #pragma unroll
   for (int v = 1; v < NV; ++v) run[v] = basev[v] + excl[v] + thr[v];
 #pragma unroll
-  for (int q = 0; q < ITEMS; ++q) {
+  for (int q = 0; q < kPer; ++q) {
     if ((flags >> q) & 1u) {
       ids[rk] = u[q];
       a.local[r.e0 + base + q] = rk;
-      s_res[slot(base + q)] = rk;
+      s_res[base + q] = rk;
 #pragma unroll
       for (int v = 1; v < NV; ++v) {
         a.indptr[v][rk] = run[v];
@@ -1159,12 +1168,12 @@ __global__ __launch_bounds__(kScanBlock) void k_rank(RankArgs a, CsrArgs ga, int
   }
   __syncthreads();
 #pragma unroll
-  for (int q = 0; q < ITEMS; ++q) {
-    if (base + q >= E || ((flags >> q) & 1u)) continue;
+  for (int q = 0; q < kPer; ++q) {
+    if (q >= per || base + q >= E || ((flags >> q) & 1u)) continue;
     int32_t loc = ans[q];   // a known vertex's local id
     if (loc < 0) {
       const int32_t e0 = -(loc + 1);   // the first occurrence, earlier than this edge
-      if (e0 >= r.e0 && e0 < r.e1) loc = s_res[slot(e0 - r.e0)];
+      if (e0 >= r.e0 && e0 < r.e1) loc = s_res[e0 - r.e0];
     }
     a.local[r.e0 + base + q] = loc;
   }
@@ -1368,7 +1377,7 @@ hipError_t launch_route(const RouteArgs& a, hipStream_t s) {
 
 hipError_t launch_sample_route(const CsrArgs& g, const SampleArgs& sa, const RouteArgs& ra, hipStream_t s) {
   if (ra.routers < 1 || ra.routers > kMaxRouters || ra.owners < 1 || ra.owners > kMaxOwners ||
-      ra.span < 1 || ra.span > kMaxSpan || sa.fanout < 1 || sa.fanout > 64)
+      sa.fanout < 1 || sa.fanout > 64)
     return hipErrorInvalidValue;
   const dim3 grid(static_cast<unsigned>(ra.routers)), block(kRouteBlock);
 #define GMB_LAUNCH_SR(G)                                                                         \
@@ -1390,8 +1399,8 @@ hipError_t launch_sample_route(const CsrArgs& g, const SampleArgs& sa, const Rou
 }
 
 hipError_t launch_owner(const OwnerArgs& a, hipStream_t s) {
-  if (a.routers < 1 || a.routers > kMaxRouters || a.owners < 1 || a.owners > kMaxOwners || a.max_slots < 64 ||
-      a.max_slots > kOwnerSlots || (a.max_slots & (a.max_slots - 1)))
+  if (a.routers < 1 || a.routers > kMaxRouters || a.owners < 1 || a.owners > kMaxOwners || a.lane_log < 2 ||
+      a.lane_log > 6 || a.max_slots < 64 || a.max_slots > kOwnerSlots || (a.max_slots & (a.max_slots - 1)))
     return hipErrorInvalidValue;
   hipLaunchKernelGGL(k_owner, dim3(static_cast<unsigned>(a.owners)), dim3(kOwnerBlock), 0, s, a);
   return hipGetLastError();
@@ -1402,7 +1411,7 @@ hipError_t launch_rank(const RankArgs& a, int num_values, const CsrArgs& g, int 
   if (routers < 1 || routers > kMaxRouters) return hipErrorInvalidValue;
   const unsigned grid = static_cast<unsigned>(routers);
 #define GMB_RANK_I(V, W, I) \
-  hipLaunchKernelGGL((k_rank<V, W, I>), dim3(grid), dim3(kScanBlock), 0, s, a, g, ids, status)
+  hipLaunchKernelGGL((k_rank<V, W, I>), dim3(grid), dim3(kRankBlock), 0, s, a, g, ids, status)
 #define GMB_RANK_W(V, W)                       \
   switch (items) {                             \
     case 2: GMB_RANK_I(V, W, 2); break;        \
