@@ -80,6 +80,31 @@ struct SamplePlan {
 
 constexpr int kTotalsWords = GMB_MAX_LAYERS;
 
+// The owners' LDS table size: kOwnerSlots, or a smaller power of two from
+// the environment variable GMB_OWNER_TABLE_SLOTS (64 .. kOwnerSlots), a test
+// hook that makes owners overflow into the state table so that path runs on
+// small inputs.  While it is set the last hop dedups by owners whatever its
+// size.
+const char* owner_hook() { return std::getenv("GMB_OWNER_TABLE_SLOTS"); }
+int32_t owner_slots() {
+  const char* v = owner_hook();
+  if (!v) return gmb::kOwnerSlots;
+  const long x = std::strtol(v, nullptr, 10);
+  int32_t slots = 64;
+  while (slots < x && slots < gmb::kOwnerSlots) slots *= 2;
+  return slots;
+}
+
+// Largest edge capacity at which the last hop, too, dedups through the
+// per-vertex table: two kernels instead of the owners' three, whose fixed
+// cost is the larger, while the table's random accesses grow with the edges.
+// sample_blocks on the 2.4M-vertex graph, table against owners: 31 k edges of
+// capacity 36.0 / 47.5 us, 127 k 44.7 / 53.7, 253 k 52.7 / 56.8, 384 k 57.2 /
+// 57.7, 507 k 65.7 / 62.6, 990 k 87.8 / 75.5 us; the line is drawn below the
+// crossing, since a larger graph's table spreads over more lines.
+constexpr int64_t kTableLastNnz = 262144;
+
+
 // Fills the plan; returns GMB_OK or an argument error (message set).
 int plan_sampling(int32_t num_seeds, const int32_t* fanouts, int32_t num_layers, int64_t num_nodes,
                   SamplePlan* plan) {
@@ -110,12 +135,15 @@ int plan_sampling(int32_t num_seeds, const int32_t* fanouts, int32_t num_layers,
     if (hp.cap_nnz >= kMaxInt32 || hp.cap_src >= kMaxInt32 || hp.cap_nnz + hp.cap_dst >= kMaxInt32)
       return fail(GMB_EINVAL, "hop %d: capacity %lld edges / %lld sources exceeds 2^31-1", h,
                   static_cast<long long>(hp.cap_nnz), static_cast<long long>(hp.cap_src));
-    // The hops before the last dedup through the per-vertex table while
-    // their fan-outs allow the group sampler (few edges, few table lines);
-    // the last hop, and every hop after one that cannot, by owners.  The
-    // relabel scan of hop h carries 1 + (later hops) values.
+    // The hops before the last, and a small last hop, dedup through the
+    // per-vertex table while their fan-outs allow the group sampler (few
+    // edges, few table lines); a larger last hop, and every hop after one
+    // that cannot, by owners.  The relabel scan of hop h carries 1 + (later
+    // hops) values.
     hp.items = gmb::scan_items_for(hp.cap_nnz);
-    hp.table = h + 1 < num_layers && hp.fanout <= 64 && (h == 0 || p.hop[h - 1].table);
+    const bool last = h + 1 == num_layers;
+    hp.table = hp.fanout <= 64 && (h == 0 || p.hop[h - 1].table) &&
+               (!last || (hp.cap_nnz <= kTableLastNnz && !owner_hook()));
     if (hp.table) {
       hp.tile_stride = gmb::scan_tiles(hp.cap_nnz, hp.items);
     } else {
@@ -217,19 +245,6 @@ int check_sampling(const gmb_csr* csr, const int32_t* seeds, int32_t num_seeds, 
   const size_t need = kStateHeader + align_up(sizeof(uint32_t) * static_cast<size_t>(csr->num_nodes));
   if (state_bytes < need) return fail(GMB_ENOSPC, "state holds %zu bytes, %zu needed", state_bytes, need);
   return GMB_OK;
-}
-
-// The owners' LDS table size limit: kOwnerSlots, or a smaller power of two
-// from the environment variable GMB_OWNER_TABLE_SLOTS (64 .. kOwnerSlots), a
-// test hook that makes owners overflow into the state table so that path
-// runs on small inputs.
-int32_t owner_slots() {
-  const char* v = std::getenv("GMB_OWNER_TABLE_SLOTS");
-  if (!v) return gmb::kOwnerSlots;
-  const long x = std::strtol(v, nullptr, 10);
-  int32_t slots = 64;
-  while (slots < x && slots < gmb::kOwnerSlots) slots *= 2;
-  return slots;
 }
 
 int enqueue_validation(const gmb_csr* csr, const gmb_blocks* b, uint32_t* status, hipStream_t s);

@@ -17,10 +17,11 @@
 // degree pass of its own.
 //
 // Dedup, two ways.  The hops before the last are small (a few thousand to
-// a few tens of thousands of edges); they dedup through a per-vertex table
+// a few tens of thousands of edges); they, and a last hop of few edges, dedup
+// through a per-vertex table
 // in the sampler state: each sampled edge lowers its vertex's slot to its
 // own position (atomicMin), and the relabel scan numbers the edges that
-// still find their own position there.  The last hop holds almost all the
+// still find their own position there.  A large last hop holds almost all the
 // edges, and a table touched once per edge costs a 128-byte line per 4-byte
 // access from every XCD's L2 (and a memory-side atomic per new vertex).
 // So its edges (and its destinations, the vertices known so far) are routed
@@ -32,7 +33,7 @@
 // per call:
 //   k_seed_scan   (one workgroup) seeds -> ids; degree scans of segment 0
 //                 for all hops; clears the look-back words
-//   table hops (all but the last, fan-outs up to 64):
+//   table hops (all but a large last one, fan-outs up to 64):
 //   k_sample_table(h)  Floyd's algorithm per destination, one lane per
 //                 draw, Philox-keyed draws; sampled slots ranked in the
 //                 group and written in slot order; each vertex's first
@@ -41,7 +42,7 @@
 //   k_assign(h)   scan of the "first occurrence" flags (new vertex number
 //                 n_dst + rank) together with the degree scans of the new
 //                 vertices for the later hops; every edge's local id
-//   owner hops (the last, and any hop after one with a fan-out above 64):
+//   owner hops (a large last one, and any hop after a fan-out above 64):
 //   k_sample_route(h)  "routers": each takes a span of destinations (a
 //                 contiguous range of edges), samples them as above and
 //                 writes its edges and its destinations, grouped by owner,

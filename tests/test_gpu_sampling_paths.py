@@ -1,0 +1,56 @@
+"""The sampler's kernels at the sizes where their dispatch changes: the last
+hop through the state's table or through owners (forced on small inputs with
+GMB_OWNER_TABLE_SLOTS), every group width of the fan-out, one seed, tile and
+router remainders, and the edge capacity at which the last hop changes its
+dedup.  Every block must equal the oracle's bit for bit, and the state must
+be clear afterwards."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+if not torch.cuda.is_available():
+    pytest.skip("no GPU on this machine", allow_module_level=True)
+
+import paper_2010_05337_amd as gmb  # noqa: E402
+from gpu_util import assert_blocks_equal, csr_on_device, gpu_blocks  # noqa: E402
+
+
+@pytest.fixture(scope="module")
+def graph(dg):
+    return dg.rmat(15, 30_000, 250_000, (0.57, 0.19, 0.19), 9)
+
+
+@pytest.mark.parametrize("owners", [False, True], ids=["table", "owners"])
+@pytest.mark.parametrize("fanouts, num_seeds", [
+    ([1], 1), ([8], 257), ([9, 3], 33), ([17, 16], 255), ([4, 32], 64), ([33, 2], 100), ([64], 513),
+    ([15, 10, 5], 97), ([3, 1, 4, 2], 300)])
+def test_dedup_paths_bitexact(orc, dg, graph, fanouts, num_seeds, owners, monkeypatch):
+    if owners:
+        monkeypatch.setenv("GMB_OWNER_TABLE_SLOTS", "8192")
+    for wide in (False, True):
+        print(f"fanouts {fanouts}, {num_seeds} seeds, owners {owners}, wide {wide}", flush=True)
+        csr = csr_on_device(graph, wide)
+        seeds = dg.permutation(graph.num_nodes, 4)[:num_seeds]
+        for key in (3, 2**63 + 7):
+            _, host = gpu_blocks(csr, seeds, fanouts, key)
+            assert_blocks_equal(host, orc.sample_blocks(graph.indptr, graph.indices, seeds, fanouts, key), f"key {key}")
+        csr.check_status()
+        assert bool((csr.state[256:256 + 4 * graph.num_nodes].view(torch.int32) == -1).all())
+        gpu_blocks(csr, np.concatenate([seeds, seeds[:1]]), fanouts, 5)   # a repeated seed
+        with pytest.raises(gmb.GmbError) as e:
+            csr.check_status()
+        assert e.value.code == -5
+
+
+@pytest.mark.parametrize("num_seeds", [16384, 16385])
+def test_last_hop_at_the_dedup_threshold(orc, dg, graph, num_seeds):
+    """16 picks of 16,384 seeds: an edge capacity of 2^18, the largest that
+    the table takes; one seed more goes to the owners."""
+    print(f"{num_seeds} seeds", flush=True)
+    csr = csr_on_device(graph)
+    seeds = dg.permutation(graph.num_nodes, 4)[:num_seeds]
+    _, host = gpu_blocks(csr, seeds, [16], 11)
+    assert_blocks_equal(host, orc.sample_blocks(graph.indptr, graph.indices, seeds, [16], 11))
+    csr.check_status()
