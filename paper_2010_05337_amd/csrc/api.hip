@@ -309,7 +309,10 @@ int run_sampling(const gmb_csr* csr, const int32_t* seeds, int32_t num_seeds, in
     sa.fanout[h] = hops[h].fanout;
   }
   const uint32_t k0 = static_cast<uint32_t>(seed), k1 = static_cast<uint32_t>(seed >> 32);
-  hipError_t e = gmb::launch_seed_scan(sa, num_layers, g, s);
+  const bool seed_sample = p.hop[0].table && gmb::seed_sample_fits(num_seeds, num_layers, p.hop[0].fanout);
+  hipError_t e = seed_sample ? gmb::launch_seed_sample(sa, num_layers, g, hops[0].nbr, table, status,
+                                                       p.hop[0].layer, k0, k1, s)
+                             : gmb::launch_seed_scan(sa, num_layers, g, s);
   if (e != hipSuccess) return hip_fail(e, "seed launch");
   uint2* pairs = reinterpret_cast<uint2*>(scr + p.off_pairs);
   int32_t* answers = reinterpret_cast<int32_t*>(scr + p.off_res);
@@ -321,7 +324,7 @@ int run_sampling(const gmb_csr* csr, const int32_t* seeds, int32_t num_seeds, in
     gmb::DeferredArgs fix{hops[0].local, hops[0].sizes + 3 - gmb::kNnz, 1};
     if (h > 0) fix = gmb::DeferredArgs{hops[h - 1].local, hops[h - 1].sizes, std::max<int64_t>(hops[h - 1].cap_nnz, 1)};
     if (hp.table) {
-      e = gmb::launch_sample_table(g, ids, hops[h], table, status, k0, k1, h == 0 ? 1 : 0, fix, s);
+      if (h > 0 || !seed_sample) e = gmb::launch_sample_table(g, ids, hops[h], table, status, k0, k1, h == 0 ? 1 : 0, fix, s);
       if (e != hipSuccess) return hip_fail(e, "sample launch");
       gmb::AssignArgs aa{};
       aa.nbr = hops[h].nbr;

@@ -181,6 +181,10 @@ struct ValidateArgs {
 // sample.hip
 hipError_t launch_state_init(uint32_t* table, uint32_t* status, int64_t num_nodes, hipStream_t s);
 hipError_t launch_seed_scan(const SeedArgs& a, int num_values, const CsrArgs& g, hipStream_t s);
+// The same with the first hop's sampling (a table hop), where it fits.
+bool seed_sample_fits(int32_t num_seeds, int num_values, int fanout);
+hipError_t launch_seed_sample(const SeedArgs& a, int num_values, const CsrArgs& g, int32_t* nbr, uint32_t* table,
+                              uint32_t* status, int layer, uint32_t k0, uint32_t k1, hipStream_t s);
 // Table hops (fan-outs up to 64): sampling with the first-edge atomics on
 // the state's table, then the relabel scan.
 hipError_t launch_sample_table(const CsrArgs& g, const int32_t* ids, const HopArgs& h, uint32_t* table,

@@ -32,7 +32,9 @@
 // relabel scan numbers the first occurrences in edge order.  The kernels,
 // per call:
 //   k_seed_scan   (one workgroup) seeds -> ids; degree scans of segment 0
-//                 for all hops; clears the look-back words
+//                 for all hops; clears the look-back words (in one launch
+//                 with the first table hop's sampling, k_seed_sample, up to
+//                 8192 seeds and three hops)
 //   table hops (all but a large last one, fan-outs up to 64):
 //   k_sample_table(h)  Floyd's algorithm per destination, one lane per
 //                 draw, Philox-keyed draws; sampled slots ranked in the
@@ -306,6 +308,32 @@ __device__ __forceinline__ void floyd_resolve(uint32_t& x, uint32_t& rank, uint3
   for (int r = 0; r < G; ++r) rank += v[r] < x ? 1u : 0u;
 }
 
+// Lane `lane` of a destination's G lanes: the CSR slot it samples and the
+// slot's place in the block's row (-1: the lane has none).  d: v's degree.
+template <int G>
+__device__ __forceinline__ void sample_slot(int64_t d, int fanout, int32_t v, int layer, uint32_t k0, uint32_t k1,
+                                            int lane, uint32_t* s_x, int32_t& place, int64_t& slot) {
+  place = -1;
+  slot = 0;
+  if (d <= fanout) {
+    if (lane < d) {
+      place = lane;
+      slot = lane;
+    }
+    return;
+  }
+  const uint32_t f = static_cast<uint32_t>(fanout);
+  const uint32_t base = static_cast<uint32_t>(d - fanout);
+  uint32_t x = ~0u, rank = 0;
+  if (static_cast<uint32_t>(lane) < f)
+    x = draw_below(k0, k1, static_cast<uint32_t>(v), static_cast<uint32_t>(layer), lane, base + lane + 1);
+  floyd_resolve<G>(x, rank, base, f, lane, s_x);
+  if (static_cast<uint32_t>(lane) < f) {
+    place = static_cast<int32_t>(rank);
+    slot = x;
+  }
+}
+
 // Sampling of a hop whose dedup runs through the state's per-vertex table
 // (the small hops before the last: few edges, so few table lines).
 // G lanes per destination (G >= fanout, G a power of two <= 64): lane i
@@ -352,26 +380,134 @@ __global__ __launch_bounds__(256) void k_sample_table(CsrArgs ga, const int32_t*
   if (!valid) return;   // an invalid vertex's clamped degree was 0
   const int64_t d = end - begin;
 
-  int32_t pos = -1, u = 0;
-  if (d <= fanout) {
-    if (lane < d) {
-      pos = off + lane;
-      u = g.indices[begin + lane];
+  int32_t place;
+  int64_t slot;
+  sample_slot<G>(d, fanout, v, layer, k0, k1, lane, &s_x[threadIdx.x - lane], place, slot);
+  if (place >= 0) emit_edge_table(off + place, g.indices[begin + slot], nbr, table, g.num_nodes, status);
+  if (seed_old < kEdgeTag) raise_status(status, GMB_STATUS_EDUP);
+}
+
+// The seed scan and the first hop's sampling in one launch, when the first
+// hop dedups through the table (up to kSeedSampleSeeds seeds).  Workgroup w
+// samples the seeds [w D, (w + 1) D), D = BLOCK / G.  It needs the degree
+// scans up to its own seeds only, and computes them itself: it reads every
+// seed before its last one (from the L2 after the first workgroup's reads),
+// so no workgroup waits for another; each writes its own seeds' ids and block
+// row offsets, the last one the totals.  Its own seeds' rows are then in LDS
+// already.  ITEMS seeds per thread and scan chunk: 1 spreads up to BLOCK
+// seeds over all waves, 4 keeps larger batches to few chunks.
+// One launch and two rounds of reads fewer than k_seed_scan followed by
+// k_sample_table: 5.4 + 4.9 -> 8.4 us at 1000 seeds and fan-out 5, 15.5 + 7.4 ->
+// 13.6 us at 4000 and 10.  Above 8192 seeds every workgroup would read too many.
+constexpr int kSeedSampleSeeds = 8192;
+template <int G, int NV, bool WIDE, int ITEMS>
+__global__ __launch_bounds__(1024) void k_seed_sample(SeedArgs a, CsrArgs ga, int32_t* nbr, uint32_t* table,
+                                                      uint32_t* status, int layer, uint32_t k0, uint32_t k1) {
+  constexpr int BLOCK = 1024, D = BLOCK / G;
+  __shared__ int32_t s_wave[NV * (BLOCK / 64)];
+  __shared__ int32_t s_v[D], s_off[D];
+  __shared__ int64_t s_beg[D], s_end[D];
+  __shared__ __attribute__((aligned(16))) uint32_t s_x[BLOCK];
+  const CsrView g = view(ga);
+  const int tid = threadIdx.x;
+  const int32_t B = a.num_seeds;   // >= 1
+  const int32_t p0 = blockIdx.x * D;
+  const int32_t p1 = p0 + D < B ? p0 + D : B;   // this workgroup's seeds
+  // the chunk base .. base + BLOCK * ITEMS of the scan; the last one holds
+  // all of this workgroup's seeds (D divides its length)
+  int32_t running[NV], excl[NV], sd[ITEMS], deg[ITEMS];
+  int32_t first = 0;   // this thread's first seed of the last chunk
+#pragma unroll
+  for (int v = 0; v < NV; ++v) running[v] = 0;
+  for (int32_t base = 0;; base += BLOCK * ITEMS) {
+    first = base + tid * ITEMS;
+    int64_t rb[ITEMS], re[ITEMS];
+#pragma unroll
+    for (int q = 0; q < ITEMS; ++q) sd[q] = a.seeds[first + q < p1 ? first + q : p1 - 1];
+#pragma unroll
+    for (int q = 0; q < ITEMS; ++q) {
+      const bool ok = first + q < p1 && valid_vertex(sd[q], g.num_nodes);
+      row_range_t<WIDE>(g, ok ? sd[q] : 0, rb[q], re[q]);
+      if (!ok) re[q] = rb[q];
+      deg[q] = static_cast<int32_t>(re[q] - rb[q]);
     }
-  } else {
-    const uint32_t f = static_cast<uint32_t>(fanout);
-    const uint32_t base = static_cast<uint32_t>(d - fanout);
-    uint32_t x = ~0u, rank = 0;
-    if (static_cast<uint32_t>(lane) < f)
-      x = draw_below(k0, k1, static_cast<uint32_t>(v), static_cast<uint32_t>(layer), lane, base + lane + 1);
-    floyd_resolve<G>(x, rank, base, f, lane, &s_x[threadIdx.x - lane]);
-    if (static_cast<uint32_t>(lane) < f) {
-      pos = off + static_cast<int32_t>(rank);
-      u = g.indices[begin + x];
+    int32_t sum[NV], total[NV];
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+      sum[v] = 0;
+#pragma unroll
+      for (int q = 0; q < ITEMS; ++q) sum[v] += clamp_degree(deg[q], a.fanout[v]);
+    }
+    block_exclusive_scan_multi<BLOCK, NV>(sum, excl, total, s_wave);
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+      excl[v] += running[v];
+      running[v] += total[v];
+    }
+    if (base + BLOCK * ITEMS >= p1) {
+      int32_t run = excl[0];
+#pragma unroll
+      for (int q = 0; q < ITEMS; ++q) {
+        const int32_t t = first + q - p0;
+        if (t >= 0 && first + q < p1) {
+          s_v[t] = sd[q];
+          s_off[t] = run;
+          s_beg[t] = rb[q];
+          s_end[t] = re[q];
+        }
+        run += clamp_degree(deg[q], a.fanout[0]);
+      }
+      break;
+    }
+  }
+  __syncthreads();
+  // the sampling, as in k_sample_table
+  const int t = tid / G, lane = tid & (G - 1);
+  uint32_t seed_old = kEmpty;
+  int32_t pos = -1, u = 0;
+  if (p0 + t < p1) {
+    const int32_t v = s_v[t];
+    if (valid_vertex(v, g.num_nodes)) {
+      if (lane == 0) seed_old = atomicMin(&table[v], static_cast<uint32_t>(p0 + t));
+      int32_t place;
+      int64_t slot;
+      sample_slot<G>(s_end[t] - s_beg[t], a.fanout[0], v, layer, k0, k1, lane, &s_x[tid - lane], place, slot);
+      if (place >= 0) {
+        pos = s_off[t] + place;
+        u = g.indices[s_beg[t] + slot];
+      }
+    } else if (lane == 0) {
+      raise_status(status, GMB_STATUS_ERANGE);
     }
   }
   if (pos >= 0) emit_edge_table(pos, u, nbr, table, g.num_nodes, status);
   if (seed_old < kEdgeTag) raise_status(status, GMB_STATUS_EDUP);
+  // the stores come last: on gfx9 the same counter tracks loads and stores,
+  // so earlier ones would hold up the waits for the reads above
+#pragma unroll
+  for (int q = 0; q < ITEMS; ++q) {
+    const int32_t p = first + q;
+    if (p >= p0 && p < p1) {
+      a.ids[p] = sd[q];
+#pragma unroll
+      for (int v = 0; v < NV; ++v) a.indptr[v][p] = excl[v];
+    }
+#pragma unroll
+    for (int v = 0; v < NV; ++v) excl[v] += clamp_degree(deg[q], a.fanout[v]);
+  }
+  const int64_t stride = static_cast<int64_t>(gridDim.x) * BLOCK;
+  for (int64_t i = static_cast<int64_t>(blockIdx.x) * BLOCK + tid; i < a.num_zero; i += stride) a.zero[i] = 0;
+  if (blockIdx.x == gridDim.x - 1) {   // its scans cover every seed
+    for (int i = tid; i < a.num_size_words; i += BLOCK) a.sizes[i] = 0;
+    __syncthreads();
+    if (tid == 0) {
+#pragma unroll
+      for (int v = 0; v < NV; ++v) a.totals[v] = running[v];   // segment 0's edges of hop v
+      a.sizes[a.first_sizes + kNDst] = B;
+      a.sizes[a.first_sizes + kNnz] = running[0];
+      a.indptr[0][B] = running[0];
+    }
+  }
 }
 
 // Fan-outs from 65 to 64 I: one wave per destination (grid-stride), I
@@ -817,7 +953,6 @@ __global__ __launch_bounds__(kRouteBlock) void k_sample_route(CsrArgs ga, Sample
   if (tid < K) s_key[E + tid] = v;
   // draws: lane task q = tid + k * kRouteBlock is lane q % G of destination q / G
   const int lane = tid & (G - 1);
-  const uint32_t f = static_cast<uint32_t>(a.fanout);
   int32_t pos[kSampleRounds];
   int64_t slot[kSampleRounds];
 #pragma unroll
@@ -826,22 +961,11 @@ __global__ __launch_bounds__(kRouteBlock) void k_sample_route(CsrArgs ga, Sample
     slot[k] = 0;
     const int32_t t = (tid + k * kRouteBlock) / G;
     if (k * kRouteBlock >= K * G || t >= K) continue;   // the first test is uniform
-    const int32_t d = s_deg[t];
-    if (d <= a.fanout) {
-      if (lane < d) {
-        pos[k] = s_off[t] + lane;
-        slot[k] = s_beg[t] + lane;
-      }
-    } else {
-      uint32_t x = ~0u, rank = 0;
-      if (static_cast<uint32_t>(lane) < f)
-        x = draw_below(a.k0, a.k1, static_cast<uint32_t>(s_v[t]), static_cast<uint32_t>(a.layer), lane,
-                       static_cast<uint32_t>(d) - f + lane + 1);
-      floyd_resolve<G>(x, rank, static_cast<uint32_t>(d) - f, f, lane, &s_x[tid - lane]);
-      if (static_cast<uint32_t>(lane) < f) {
-        pos[k] = s_off[t] + static_cast<int32_t>(rank);
-        slot[k] = s_beg[t] + x;
-      }
+    int32_t place;
+    sample_slot<G>(s_deg[t], a.fanout, s_v[t], a.layer, a.k0, a.k1, lane, &s_x[tid - lane], place, slot[k]);
+    if (place >= 0) {
+      pos[k] = s_off[t] + place;
+      slot[k] += s_beg[t];
     }
   }
   int32_t u[kSampleRounds];
@@ -1282,6 +1406,38 @@ hipError_t launch_seed_scan(const SeedArgs& a, int num_values, const CsrArgs& g,
     default: return hipErrorInvalidValue;
   }
 #undef GMB_SEED
+  return hipGetLastError();
+}
+
+bool seed_sample_fits(int32_t num_seeds, int num_values, int fanout) {
+  return num_seeds >= 1 && num_seeds <= kSeedSampleSeeds && num_values <= 3 && fanout <= 64;
+}
+
+hipError_t launch_seed_sample(const SeedArgs& a, int num_values, const CsrArgs& g, int32_t* nbr, uint32_t* table,
+                              uint32_t* status, int layer, uint32_t k0, uint32_t k1, hipStream_t s) {
+  const int f = a.fanout[0];
+  if (!seed_sample_fits(a.num_seeds, num_values, f)) return hipErrorInvalidValue;
+#define GMB_SS_L(G, V, W, I)                                                                                   \
+  hipLaunchKernelGGL((k_seed_sample<G, V, W, I>), dim3(grid_for(static_cast<int64_t>(a.num_seeds) * G, 1024)), \
+                     dim3(1024), 0, s, a, g, nbr, table, status, layer, k0, k1)
+#define GMB_SS_I(G, V, W) \
+  if (a.num_seeds <= 1024) GMB_SS_L(G, V, W, 1); else GMB_SS_L(G, V, W, 4)
+#define GMB_SS_W(G, V) \
+  if (g.wide) { GMB_SS_I(G, V, true); } else { GMB_SS_I(G, V, false); }
+#define GMB_SS_G(V)                       \
+  if (f <= 8) { GMB_SS_W(8, V) }          \
+  else if (f <= 16) { GMB_SS_W(16, V) }   \
+  else if (f <= 32) { GMB_SS_W(32, V) }   \
+  else { GMB_SS_W(64, V) }
+  switch (num_values) {
+    case 1: { GMB_SS_G(1) } break;
+    case 2: { GMB_SS_G(2) } break;
+    default: { GMB_SS_G(3) } break;
+  }
+#undef GMB_SS_G
+#undef GMB_SS_W
+#undef GMB_SS_I
+#undef GMB_SS_L
   return hipGetLastError();
 }
 

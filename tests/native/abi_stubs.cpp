@@ -14,6 +14,13 @@ namespace gmb {
 
 hipError_t launch_state_init(uint32_t*, uint32_t*, int64_t, hipStream_t) { return hipSuccess; }
 hipError_t launch_seed_scan(const SeedArgs&, int, const CsrArgs&, hipStream_t) { return hipSuccess; }
+bool seed_sample_fits(int32_t num_seeds, int num_values, int fanout) {
+  return num_seeds >= 1 && num_seeds <= 8192 && num_values <= 3 && fanout <= 64;
+}
+hipError_t launch_seed_sample(const SeedArgs&, int, const CsrArgs&, int32_t*, uint32_t*, uint32_t*, int, uint32_t,
+                              uint32_t, hipStream_t) {
+  return hipSuccess;
+}
 hipError_t launch_sample_table(const CsrArgs&, const int32_t*, const HopArgs&, uint32_t*, uint32_t*, uint32_t,
                                uint32_t, int, const DeferredArgs&, hipStream_t) {
   return hipSuccess;

@@ -54,3 +54,24 @@ def test_last_hop_at_the_dedup_threshold(orc, dg, graph, num_seeds):
     _, host = gpu_blocks(csr, seeds, [16], 11)
     assert_blocks_equal(host, orc.sample_blocks(graph.indptr, graph.indices, seeds, [16], 11))
     csr.check_status()
+
+
+@pytest.mark.parametrize("fanouts, num_seeds", [
+    ([5], 1024), ([2, 3], 1025), ([2, 20], 4096), ([1, 2, 9], 4097), ([2, 5], 8192), ([2, 5], 8193), ([40], 6001)])
+def test_seed_scan_with_the_first_hop(orc, dg, graph, fanouts, num_seeds):
+    """The seeds' scan inside the first hop's kernel: one or four seeds per
+    thread, several scan chunks, up to the size where the scan is a kernel of
+    its own again; an id outside the graph is reported."""
+    print(f"fanouts {fanouts}, {num_seeds} seeds", flush=True)
+    for wide in (False, True):
+        csr = csr_on_device(graph, wide)
+        seeds = dg.permutation(graph.num_nodes, 8)[:num_seeds]
+        _, host = gpu_blocks(csr, seeds, fanouts, 21)
+        assert_blocks_equal(host, orc.sample_blocks(graph.indptr, graph.indices, seeds, fanouts, 21))
+        csr.check_status()
+        bad = seeds.copy()
+        bad[num_seeds // 2] = graph.num_nodes
+        gpu_blocks(csr, bad, fanouts, 21)
+        with pytest.raises(gmb.GmbError) as e:
+            csr.check_status()
+        assert e.value.code == -4
