@@ -708,166 +708,267 @@ bool launch_parts_for(const int32_t* sizes, const float* hs, const float* ag, co
   return true;
 }
 
-// bf16 with the weight slab resident in LDS (same scheme as the fp32 slab
-// kernel, on v_mfma_f32_16x16x32_bf16).  Lane l (q = l/16) supplies
-// A[l%16][32c + 8q .. +7] and B[32c + 8q .. +7][l%16] of chunk c and holds
-// C[4q + r][l%16].  The slab keeps the workgroup's BN = 16 J columns of
-// [W_self; W_neigh] for all 2 d_in rows (zero past 2 d_in and past d_out)
-// in operand order, Bp[((c * 4 + q) * BN + n) * 8 + s] = W[32c + 8q + s][n],
-// so a lane reads its eight k values with one 16-byte LDS read; its A
-// operand is one 16-byte global read (d_in % 8 == 0, so a group of eight k
-// never straddles [h_v | mean]).  Each wave computes 16 rows x BN columns,
-// the workgroup 64 rows, persistent over row tiles with the next tile's A
-// reads issued as soon as each chunk's MFMAs are; fp32 accumulation, bias
-// and ReLU, then fp32 or bf16 (round to nearest even) output.
+// bf16 with the weight slab resident in LDS, on v_mfma_f32_16x16x32_bf16.
+// A workgroup of eight waves owns BN = 16 J output columns and keeps those
+// columns of [W_self; W_neigh] in LDS; it walks over tiles of 128 rows (16 per
+// wave), persistent, the next tile's A reads issued as soon as each chunk's
+// products are.  The reduction runs over groups of eight k: `gh` groups of
+// h_v, then gh of the mean, gh = ceil(d_in / 8); chunk c takes the groups 4c
+// + q, q = lane / 16.  Group g of a half starts at k = 8 g, the last one at
+// d_in - 8 with its first elements (which the group before it holds) zeroed in
+// both operands, so every A operand is one 16-byte read inside its row
+// (misaligned when d_in % 8 != 0, which global loads allow) whatever d_in >= 8.
+//
+// Operand order: the slab holds Bp[(g * BN + n) * 8 + s] = W[k(g) + s][n],
+// one 16-byte LDS read per lane, chunk and column subtile.  W goes in as the
+// first operand, so lane (q, i) ends with out[row i][16 j + 4 q .. + 3]: four
+// adjacent columns, one 8- or 16-byte store where N allows it.
+//
+// The fill: an item is eight k of four adjacent columns, eight 8-byte loads
+// (N % 4 == 0) transposed by byte permutes into four 16-byte LDS words.
+// (Writing the transpose as 2-byte LDS words cost most of the kernel: eight
+// lanes on one bank.)
+//
+// What bounds it: the reads of h_v and the mean and the writes of the
+// output at 41k rows (42 MB: 15.0 us, 2.8 TB/s; 33.0 us before, with four
+// waves and the 2-byte fill), latency at few rows: 4000 rows, 2 x 256 -> 47
+// 20.0 -> 11.9 us, 1000 rows, 2 x 256 -> 172 20.4 -> 8.9 us.
+constexpr int kBf16Waves = 8;
+constexpr int kBf16Rows = 16 * kBf16Waves;
+
+constexpr int bf16_slab_bytes(int nch, int j) { return nch * 4 * 16 * j * 8 * 2; }
+
+__device__ __forceinline__ uint4 load16_any(const uint16_t* p) {
+  uint4 x;
+  __builtin_memcpy(&x, p, 16);
+  return x;
+}
+
 template <int NCH, int J>
-__global__ __launch_bounds__(256) void k_linear_bf16_slab(const int32_t* sizes,
-                                                          const uint16_t* __restrict__ Hs,
-                                                          const uint16_t* __restrict__ Ag,
-                                                          const uint16_t* __restrict__ Ws,
-                                                          const uint16_t* __restrict__ Wn,
-                                                          const float* __restrict__ bias, int K, int N,
-                                                          int relu, int out_f32, int wvec,
-                                                          void* __restrict__ out) {
+__global__ __launch_bounds__(64 * kBf16Waves) void k_linear_bf16_slab(
+    const int32_t* sizes, const uint16_t* __restrict__ Hs, const uint16_t* __restrict__ Ag,
+    const uint16_t* __restrict__ Ws, const uint16_t* __restrict__ Wn, const float* __restrict__ bias, int d_in, int N,
+    int relu, int out_f32, int avec, int wquad, int ovec, void* __restrict__ out) {
   constexpr int BN = 16 * J;
-  __shared__ __attribute__((aligned(16))) uint16_t Bp[NCH * 4 * BN * 8];
+  constexpr int THREADS = 64 * kBf16Waves;
+  constexpr int GROUPS = NCH * 4;
+  __shared__ __attribute__((aligned(16))) uint16_t Bp[GROUPS * BN * 8];
+  __shared__ __attribute__((aligned(16))) float s_bias[BN];
   const int32_t M = load_size(&sizes[kNDst]);
-  const int row_tiles = (M + 63) / 64;
+  const int row_tiles = (M + kBf16Rows - 1) / kBf16Rows;
   if (static_cast<int>(blockIdx.x) >= row_tiles) return;
   const int n0 = blockIdx.y * BN;
-  const int K2 = 2 * K;
-  // slab fill: thread item = (k, 8 consecutive columns); one 16-byte read
-  // of a weight row when the row is vector-aligned and inside the matrix,
-  // else element-wise with zero padding
-  constexpr int kItems = NCH * 32 * (BN / 8);
-  for (int base = 0; base < kItems; base += 256 * 4) {
-    uint4 v[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int idx = base + u * 256 + threadIdx.x;
-      const int k = idx / (BN / 8), n8 = idx % (BN / 8);
-      const int gn = n0 + 8 * n8;
-      const bool in_k = idx < kItems && k < K2;
-      const uint16_t* row = (k < K ? Ws + static_cast<int64_t>(k) * N
-                                   : Wn + static_cast<int64_t>(in_k ? k - K : 0) * N);
-      // every read is unconditional (clamped column), zeros selected after
-      if (wvec) {   // uniform: N % 8 == 0 and 16-byte aligned rows
-        uint4 x = *reinterpret_cast<const uint4*>(row + (gn < N ? gn : 0));
-        asm volatile("" : "+v"(x.x), "+v"(x.y), "+v"(x.z), "+v"(x.w));
-        v[u] = (in_k && gn < N) ? x : make_uint4(0u, 0u, 0u, 0u);
-      } else {
-        uint32_t e[8];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) e[i] = row[gn + i < N ? gn + i : N - 1];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          asm volatile("" : "+v"(e[i]));
-          e[i] = (in_k && gn + i < N) ? e[i] : 0u;
-        }
-        v[u] = make_uint4(e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16));
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int idx = base + u * 256 + threadIdx.x;
-      if (idx >= kItems) continue;
-      const int k = idx / (BN / 8), n8 = idx % (BN / 8);
-      const int c = k >> 5, q = (k >> 3) & 3, sl = k & 7;
-      const uint32_t w[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
-#pragma unroll
-      for (int i = 0; i < 8; ++i)
-        Bp[((c * 4 + q) * BN + 8 * n8 + i) * 8 + sl] = static_cast<uint16_t>(w[i >> 1] >> (16 * (i & 1)));
-    }
-  }
-  __syncthreads();
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int q = lane >> 4, r16 = lane & 15;
-  auto tile_rows = [&](int rt, const uint16_t*& hrow, const uint16_t*& grow) {
-    const int row = rt * 64 + wave * 16 + r16;
-    const int64_t arow = row < M ? row : M - 1;
-    hrow = Hs + arow * K;
-    grow = Ag + arow * K;
+  const int gh = (d_in + 7) / 8;                // groups per half
+  const int cut = 8 * gh - d_in;                // elements zeroed in a half's last group
+  // group g: its half's array (0: self, 1: mean; -1: past both) and first k
+  auto group_k = [&](int g, int& half) {
+    half = g < gh ? 0 : (g < 2 * gh ? 1 : -1);
+    const int gi = g - (half > 0 ? gh : 0);
+    return half < 0 ? 0 : (gi == gh - 1 ? d_in - 8 : 8 * gi);
   };
-  auto load_frag = [&](const uint16_t* hrow, const uint16_t* grow, int c) -> bf16x8 {
-    const int k = 32 * c + 8 * q;
-    const bool in = k < K2;
-    const uint16_t* p = (k < K ? hrow + k : grow + (in ? k - K : 0));
-    uint4 x = *reinterpret_cast<const uint4*>(p);
-    asm volatile("" : "+v"(x.x), "+v"(x.y), "+v"(x.z), "+v"(x.w));
-    if (!in) x = make_uint4(0u, 0u, 0u, 0u);
+  // A: issue the read of chunk c of this lane's row; finish after use is near
+  auto tile_rows = [&](int rt, const uint16_t*& hrow, const uint16_t*& grow) {
+    const int row = rt * kBf16Rows + wave * 16 + r16;
+    const int64_t arow = row < M ? row : M - 1;   // a row past the end is not stored
+    hrow = Hs + arow * d_in;
+    grow = Ag + arow * d_in;
+  };
+  auto load_frag = [&](const uint16_t* hrow, const uint16_t* grow, int c, int ql) -> uint4 {
+    int half;
+    const int k = group_k(4 * c + ql, half);
+    const uint16_t* p = (half > 0 ? grow : hrow) + k;
+    return avec ? *reinterpret_cast<const uint4*>(p) : load16_any(p);
+  };
+  // a half's last group loses its first `cut` elements; past the halves: zero
+  auto frag = [&](uint4 x, int c) -> bf16x8 {
+    const int g = 4 * c + q;
+    if (4 * c + 3 >= 2 * gh && g >= 2 * gh) x = make_uint4(0u, 0u, 0u, 0u);
+    if (cut) {   // uniform
+      const bool tail = g == gh - 1 || g == 2 * gh - 1;
+      uint32_t w[4] = {x.x, x.y, x.z, x.w};
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const uint32_t m = (2 * i >= cut ? 0x0000FFFFu : 0u) | (2 * i + 1 >= cut ? 0xFFFF0000u : 0u);
+        w[i] = tail ? w[i] & m : w[i];
+      }
+      x = make_uint4(w[0], w[1], w[2], w[3]);
+    }
     return __builtin_bit_cast(bf16x8, x);
   };
-  bf16x8 a[NCH];
-  {
+  // the first tile's reads go out before the fill's, where the registers
+  // allow both
+  constexpr bool kEarlyA = NCH <= 16;
+  uint4 a[NCH];
+  auto first_a = [&]() {
     const uint16_t *hrow, *grow;
     tile_rows(blockIdx.x, hrow, grow);
 #pragma unroll
-    for (int c = 0; c < NCH; ++c) a[c] = load_frag(hrow, grow, c);
-  }
-  float bv[J];
+    for (int c = 0; c < NCH; ++c) a[c] = load_frag(hrow, grow, c, q);
+  };
+  if constexpr (kEarlyA) first_a();
+  // slab fill: item (g, quad n4)
+  constexpr int kItems = GROUPS * BN / 4;
+  constexpr int kPer = (kItems + THREADS - 1) / THREADS;
+  constexpr int kMost = NCH <= 8 ? 4 : 2;   // items in flight per thread
+  constexpr int kBatch = kPer < kMost ? kPer : kMost;
+#pragma unroll 1
+  for (int u0 = 0; u0 < kPer; u0 += kBatch) {
+    uint2 v[kBatch][8];
 #pragma unroll
-  for (int j = 0; j < J; ++j) {
-    const int col = n0 + j * 16 + r16;
-    bv[j] = bias[col < N ? col : N - 1];
+    for (int u = 0; u < kBatch; ++u) {
+      const int it = (u0 + u) * THREADS + threadIdx.x;
+      const int g = it / (BN / 4), n = n0 + 4 * (it % (BN / 4));
+      int half;
+      const int k = group_k(it < kItems ? g : GROUPS, half);
+      const uint16_t* base = (half > 0 ? Wn : Ws) + static_cast<int64_t>(k) * N;
+      if (wquad) {   // uniform: N % 4 == 0 and 8-byte aligned matrices
+        const uint16_t* p = base + (n < N ? n : 0);
+#pragma unroll
+        for (int s8 = 0; s8 < 8; ++s8) v[u][s8] = *reinterpret_cast<const uint2*>(p + static_cast<int64_t>(s8) * N);
+      } else {
+        int col[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) col[i] = n + i < N ? n + i : N - 1;
+#pragma unroll
+        for (int s8 = 0; s8 < 8; ++s8) {
+          const uint16_t* p = base + static_cast<int64_t>(s8) * N;
+          const uint32_t e0 = p[col[0]], e1 = p[col[1]], e2 = p[col[2]], e3 = p[col[3]];
+          v[u][s8] = make_uint2(e0 | (e1 << 16), e2 | (e3 << 16));
+        }
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) {
+      const int it = (u0 + u) * THREADS + threadIdx.x;
+      if (it >= kItems) continue;
+      const int g = it / (BN / 4), n = n0 + 4 * (it % (BN / 4));
+      const bool last = g == gh - 1 || g == 2 * gh - 1;
+      const bool in = g < 2 * gh;
+#pragma unroll
+      for (int s8 = 0; s8 < 8; ++s8) {   // zero rows outside the halves, zero columns past N
+        const bool row = in && !(last && s8 < cut);
+        v[u][s8].x = row && n < N ? v[u][s8].x & (n + 1 < N ? ~0u : 0xFFFFu) : 0u;
+        v[u][s8].y = row && n + 2 < N ? v[u][s8].y & (n + 3 < N ? ~0u : 0xFFFFu) : 0u;
+      }
+      uint4* dst = reinterpret_cast<uint4*>(&Bp[it * 4 * 8]);
+      auto pack = [&](auto get, uint32_t sel) {
+        return make_uint4(__builtin_amdgcn_perm(get(1), get(0), sel), __builtin_amdgcn_perm(get(3), get(2), sel),
+                          __builtin_amdgcn_perm(get(5), get(4), sel), __builtin_amdgcn_perm(get(7), get(6), sel));
+      };
+      dst[0] = pack([&](int i) { return v[u][i].x; }, 0x05040100u);
+      dst[1] = pack([&](int i) { return v[u][i].x; }, 0x07060302u);
+      dst[2] = pack([&](int i) { return v[u][i].y; }, 0x05040100u);
+      dst[3] = pack([&](int i) { return v[u][i].y; }, 0x07060302u);
+    }
   }
+  for (int i = threadIdx.x; i < BN; i += THREADS) s_bias[i] = bias[n0 + i < N ? n0 + i : N - 1];
+  if constexpr (!kEarlyA) first_a();
+  __syncthreads();
   for (int rt = blockIdx.x; rt < row_tiles; rt += gridDim.x) {
     const uint16_t *hnext, *gnext;
     tile_rows(rt + gridDim.x, hnext, gnext);
+    const bool more = rt + static_cast<int>(gridDim.x) < row_tiles;   // uniform
     floatx4 acc[J];
 #pragma unroll
     for (int j = 0; j < J; ++j) acc[j] = floatx4{0.f, 0.f, 0.f, 0.f};
-    auto load_b = [&](int c, bf16x8 (&b)[J]) {
+    // the slab's fragments one chunk ahead of their products (the barriers
+    // keep the compiler from reading the whole slab into registers at once)
+    auto load_w = [&](int c, bf16x8 (&w)[J]) {
 #pragma unroll
       for (int j = 0; j < J; ++j)
-        b[j] = *reinterpret_cast<const bf16x8*>(&Bp[((c * 4 + q) * BN + j * 16 + r16) * 8]);
+        w[j] = *reinterpret_cast<const bf16x8*>(&Bp[((c * 4 + q) * BN + j * 16 + r16) * 8]);
     };
-    bf16x8 b0[J], b1[J];
-    load_b(0, b0);
+    constexpr bool kAhead = J * NCH < 128;   // (the widest tiling has no registers for it)
+    bf16x8 w0[J], w1[kAhead ? J : 1];
+    if constexpr (kAhead) load_w(0, w0);
+    int ql = q;   // opaque per tile: the chunks' offsets are not kept in registers
+    asm volatile("" : "+v"(ql));
 #pragma unroll
     for (int c = 0; c < NCH; ++c) {
-      bf16x8 (&bc)[J] = (c & 1) ? b1 : b0;
-      bf16x8 (&bn)[J] = (c & 1) ? b0 : b1;
-      if (c + 1 < NCH) load_b(c + 1, bn);
+      bf16x8 (&w)[J] = *(kAhead && (c & 1) ? reinterpret_cast<bf16x8 (*)[J]>(&w1) : &w0);
+      if constexpr (kAhead) {
+        if (c + 1 < NCH) load_w(c + 1, *((c & 1) ? &w0 : reinterpret_cast<bf16x8 (*)[J]>(&w1)));
+      } else {
+        load_w(c, w0);
+      }
       __builtin_amdgcn_sched_barrier(0);
+      const bf16x8 x = frag(a[c], c);
 #pragma unroll
-      for (int j = 0; j < J; ++j) acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[c], bc[j], acc[j], 0, 0, 0);
-      a[c] = load_frag(hnext, gnext, c);
+      for (int j = 0; j < J; ++j) acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[j], x, acc[j], 0, 0, 0);
+      if (more) a[c] = load_frag(hnext, gnext, c, ql);
     }
-    const int row0 = rt * 64 + wave * 16 + 4 * q;
+    const int row = rt * kBf16Rows + wave * 16 + r16;
+    if (row < M) {
 #pragma unroll
-    for (int j = 0; j < J; ++j) {
-      const int col = n0 + j * 16 + r16;
+      for (int j = 0; j < J; ++j) {
+        const int col = n0 + j * 16 + 4 * q;
+        const float4 b4 = *reinterpret_cast<const float4*>(&s_bias[j * 16 + 4 * q]);
+        float z[4] = {acc[j][0] + b4.x, acc[j][1] + b4.y, acc[j][2] + b4.z, acc[j][3] + b4.w};
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        float z = acc[j][r] + bv[j];
-        if (relu) z = z > 0.f ? z : 0.f;
-        if (row0 + r < M && col < N) {
-          const int64_t o = static_cast<int64_t>(row0 + r) * N + col;
-          if (out_f32) static_cast<float*>(out)[o] = z;
-          else static_cast<uint16_t*>(out)[o] = f32_to_bf16(z);
+        for (int r = 0; r < 4; ++r)
+          if (relu) z[r] = z[r] > 0.f ? z[r] : 0.f;
+        const int64_t o = static_cast<int64_t>(row) * N + col;
+        if (ovec) {   // uniform: N % 4 == 0 and the output aligned to four values
+          if (col < N) {
+            if (out_f32) {
+              *reinterpret_cast<float4*>(static_cast<float*>(out) + o) = make_float4(z[0], z[1], z[2], z[3]);
+            } else {
+              uint2 p;
+              p.x = f32_to_bf16(z[0]) | (static_cast<uint32_t>(f32_to_bf16(z[1])) << 16);
+              p.y = f32_to_bf16(z[2]) | (static_cast<uint32_t>(f32_to_bf16(z[3])) << 16);
+              *reinterpret_cast<uint2*>(static_cast<uint16_t*>(out) + o) = p;
+            }
+          }
+        } else {
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            if (col + r < N) {
+              if (out_f32) static_cast<float*>(out)[o + r] = z[r];
+              else static_cast<uint16_t*>(out)[o + r] = f32_to_bf16(z[r]);
+            }
         }
       }
     }
   }
 }
 
-template <int NCH>
+template <int NCH, int J>
 void launch_bf16_slab(const int32_t* sizes, const uint16_t* hs, const uint16_t* ag, const uint16_t* ws,
                       const uint16_t* wn, const float* bias, int K, int N, int relu, int out_f32,
                       void* out, int64_t cap_rows, hipStream_t s) {
-  constexpr int J = 4, BN = 64;
-  constexpr int lds = NCH * 4 * BN * 8 * 2;
-  constexpr int by_lds = (160 * 1024) / lds;
-  const int per_cu = by_lds < 1 ? 1 : (by_lds > kSlabBlocksBf16 ? kSlabBlocksBf16 : by_lds);
+  constexpr int BN = 16 * J;
+  constexpr int per_cu = bf16_slab_bytes(NCH, J) <= 72 * 1024 ? kSlabBlocksBf16 : 1;
   const int col_tiles = (N + BN - 1) / BN;
-  int64_t rows = (cap_rows + 63) / 64;
-  const int64_t want = (256 * per_cu + col_tiles - 1) / col_tiles;
+  int64_t rows = (cap_rows + kBf16Rows - 1) / kBf16Rows;
+  const int64_t want = (kComputeUnits * per_cu + col_tiles - 1) / col_tiles;
   if (rows > want) rows = want;
   if (rows < 1) rows = 1;
-  const uintptr_t walign = reinterpret_cast<uintptr_t>(ws) | reinterpret_cast<uintptr_t>(wn);
-  const int wvec = (N % 8 == 0 && walign % 16 == 0) ? 1 : 0;
-  hipLaunchKernelGGL((k_linear_bf16_slab<NCH, J>), dim3(static_cast<unsigned>(rows), col_tiles), dim3(256), 0,
-                     s, sizes, hs, ag, ws, wn, bias, K, N, relu, out_f32, wvec, out);
+  const int avec = K % 8 == 0 && (reinterpret_cast<uintptr_t>(hs) | reinterpret_cast<uintptr_t>(ag)) % 16 == 0;
+  const int wquad = N % 4 == 0 && (reinterpret_cast<uintptr_t>(ws) | reinterpret_cast<uintptr_t>(wn)) % 8 == 0;
+  const int ovec = N % 4 == 0 && reinterpret_cast<uintptr_t>(out) % (out_f32 ? 16 : 8) == 0;
+  hipLaunchKernelGGL((k_linear_bf16_slab<NCH, J>), dim3(static_cast<unsigned>(rows), col_tiles),
+                     dim3(64 * kBf16Waves), 0, s, sizes, hs, ag, ws, wn, bias, K, N, relu, out_f32, avec, wquad, ovec,
+                     out);
+}
+
+// The column width: as wide as the LDS allows (an A row is read once per
+// column tile) while the tiles at capacity still give every CU a workgroup.
+template <int NCH>
+void launch_bf16_slab_for(const int32_t* sizes, const uint16_t* hs, const uint16_t* ag, const uint16_t* ws,
+                          const uint16_t* wn, const float* bias, int K, int N, int relu, int out_f32, void* out,
+                          int64_t cap_rows, hipStream_t s) {
+  const int64_t row_tiles = (cap_rows + kBf16Rows - 1) / kBf16Rows;
+  auto enough = [&](int j) { return row_tiles * ((N + 16 * j - 1) / (16 * j)) >= kComputeUnits; };
+#define GMB_SLAB16_J(JJ) launch_bf16_slab<NCH, JJ>(sizes, hs, ag, ws, wn, bias, K, N, relu, out_f32, out, cap_rows, s)
+  if constexpr (NCH <= 16)
+    if (enough(8)) return GMB_SLAB16_J(8);
+  if constexpr (NCH <= 32)
+    if (enough(4)) return GMB_SLAB16_J(4);
+  if (enough(2)) return GMB_SLAB16_J(2);
+  GMB_SLAB16_J(1);
+#undef GMB_SLAB16_J
 }
 
 }  // namespace
@@ -898,11 +999,10 @@ hipError_t launch_sage_linear(const int32_t* sizes, const void* h_self, const vo
     const uint16_t* ag = static_cast<const uint16_t*>(agg);
     const uint16_t* ws = static_cast<const uint16_t*>(w_self);
     const uint16_t* wn = static_cast<const uint16_t*>(w_neigh);
-    const uintptr_t align = reinterpret_cast<uintptr_t>(hs) | reinterpret_cast<uintptr_t>(ag);
-    const int nch = (2 * d_in + 31) / 32;
-    if (d_in % 8 == 0 && align % 16 == 0 && nch <= 40) {
+    const int nch = (2 * ((d_in + 7) / 8) + 3) / 4;
+    if (d_in >= 8 && nch <= 40) {
 #define GMB_SLAB16(C) \
-  launch_bf16_slab<C>(sizes, hs, ag, ws, wn, bias, d_in, d_out, relu, out_f32, out, cap_rows, s)
+  launch_bf16_slab_for<C>(sizes, hs, ag, ws, wn, bias, d_in, d_out, relu, out_f32, out, cap_rows, s)
       if (nch <= 2) GMB_SLAB16(2);
       else if (nch <= 4) GMB_SLAB16(4);
       else if (nch <= 8) GMB_SLAB16(8);

@@ -1,0 +1,56 @@
+"""The linear layers at the sizes where their kernels change: widths that no
+vector load divides, the last group of eight k overlapping the one before,
+ragged row and column tiles, every column width of the slab."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+if not torch.cuda.is_available():
+    pytest.skip("no GPU on this machine", allow_module_level=True)
+
+import paper_2010_05337_amd as gmb  # noqa: E402
+from gpu_util import csr_on_device, to_torch_feats, to_torch_weights  # noqa: E402
+from test_gpu_parity import TOL_BF16, _forward_case  # noqa: E402
+
+
+@pytest.fixture(scope="module")
+def graph(dg):
+    return dg.rmat(15, 30_000, 250_000, (0.57, 0.19, 0.19), 9)
+
+
+@pytest.mark.parametrize("d_in, d_out, rows", [
+    (8, 5, 1), (9, 7, 127), (75, 41, 300), (33, 130, 4000), (250, 255, 17001), (128, 256, 17000), (31, 64, 9000),
+    (256, 172, 1000), (320, 47, 5000), (513, 10, 200)])
+def test_linear_bf16_widths(orc, dg, graph, d_in, d_out, rows):
+    """One layer of d_in -> d_out over `rows` destinations (the 2e-2 of every
+    bf16 forward: the mean is rounded to bf16)."""
+    print(f"bf16 {d_in} -> {d_out}, {rows} rows", flush=True)
+    feats = dg.features(graph.num_nodes, d_in, 5, "bf16")
+    w = dg.sage_weights([d_in, d_out], 6, "bf16")
+    _forward_case(orc, dg, graph, feats, w, dg.permutation(graph.num_nodes, 7)[:rows], [5], 8, TOL_BF16)
+
+
+@pytest.mark.parametrize("dtype", ["bf16"])
+@pytest.mark.parametrize("d_in", [9, 75, 101])
+def test_linear_infinities_stay_in_their_element(dg, graph, dtype, d_in):
+    """An infinite feature gives infinities of its weights' signs, no NaN, at
+    every position (the elements that two groups of the reduction read, too).
+    No edges: the mean is zero."""
+    n, d_out = 40, 20
+
+    class G:
+        num_nodes, indptr, indices = 128, np.zeros(129, np.int64), np.zeros(0, np.int32)
+    feats = to_torch_feats(dg.features(128, d_in, 3, dtype))
+    seeds = torch.arange(n, dtype=torch.int32, device="cuda")
+    for i in range(n):
+        feats[i, i % d_in] = float("inf") if i % 3 else float("-inf")
+    w = to_torch_weights(dg.sage_weights([d_in, d_out], 6, dtype))
+    blocks = gmb.sample_blocks(csr_on_device(G), seeds, [5], 1)
+    x = gmb.gather_features(blocks, feats)
+    out = gmb.sage_forward(blocks, x, w).cpu()
+    wm = w.w_self[0].float().cpu()
+    for i in range(n):
+        want = torch.sign(wm[i % d_in]) * (float("inf") if i % 3 else float("-inf"))
+        assert torch.equal(out[i], want), i
