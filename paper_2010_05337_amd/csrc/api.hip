@@ -179,7 +179,9 @@ int plan_sampling(int32_t num_seeds, const int32_t* fanouts, int32_t num_layers,
     }
     hp.tiles_word = zero_words;
     zero_words += hp.tile_stride * (num_layers - h);
-    hp.ticket_word = zero_words++;
+    zero_words = (zero_words + 15) / 16 * 16;   // the tickets on lines of their own
+    hp.ticket_word = zero_words;
+    zero_words += gmb::kScanTicketWords / 2;
     cap_dst = hp.cap_src;
   }
   p.cap_ids = p.hop[num_layers - 1].cap_src;
@@ -836,8 +838,8 @@ int plan_backward_f32(const gmb_blocks* b, const gmb_sage_weights* w, BackwardPl
   off = align_up(off + 4 * part);
   p.off_lossrows = off;
   off = align_up(off + 4 * static_cast<size_t>(std::max(b->num_seeds, 1)));
-  p.cnt_len = static_cast<int64_t>((src + 1) / 2 * 2);
-  p.scan_len = 2 + 2 * gmb::csc_scan_tiles(static_cast<int64_t>(src));
+  p.cnt_len = static_cast<int64_t>((src + 31) / 32 * 32);   // the scan states on lines of their own
+  p.scan_len = (gmb::kScanTicketWords + 2 + 2 * gmb::csc_scan_tiles(static_cast<int64_t>(src)) + 31) / 32 * 32;
   p.clear_len = p.cnt_len + static_cast<int64_t>(std::max(L - first, 0)) * p.scan_len;
   p.off_cnt = off;
   off = align_up(off + 4 * static_cast<size_t>(p.clear_len));

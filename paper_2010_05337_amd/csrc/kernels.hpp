@@ -34,6 +34,8 @@ struct HopArgs {
   int layer;
 };
 
+// 32-bit words of one scan's tile tickets (scan.hpp), start zeroed
+constexpr int kScanTicketWords = 256;
 constexpr int kScanBlock = 256;
 // Items per thread of a relabel tile (kScanBlock threads): 2, 4, 8 or 16.
 // Small hops take small tiles so that their random reads spread over many
@@ -297,7 +299,7 @@ hipError_t launch_dgrad(const int32_t* sizes, const float* dZ, int ldz, int d_ou
                         const int32_t* indptr, const int32_t* local, int64_t cap_nnz, int32_t fanout, int32_t* cnt,
                         hipStream_t s);
 // look-back tiles of the transpose scan over cap_src sources; its state
-// (the tile ticket, the long-row count, then 2 words per tile) must start
+// (the tile tickets, the long-row count, then 2 words per tile) must start
 // zeroed; long_rows holds cap_src ints
 int64_t csc_scan_tiles(int64_t cap_src);
 // With table != NULL the pull applies table[ids[u]] -= lr * g instead of

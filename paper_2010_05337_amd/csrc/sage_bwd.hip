@@ -1398,22 +1398,23 @@ hipError_t launch_mean_backward(const int32_t* sizes, const int32_t* indptr, con
                                 int64_t num_nodes, float lr, const WgradArgs* defer, const ReduceArgs* fold,
                                 hipStream_t s) {
   const EdgeView ev{indptr, local, cap_nnz, fanout};
-  // scan_state: [0] the tile ticket, [1] the long-row count, then the
+  // scan_state: the tile tickets, the long-row count, a pad word, then the
   // look-back words
+  uint32_t* n_long = scan_state + kTicketWords;
   const int scan_blocks = static_cast<int>(csc_scan_tiles(cap_src));
   const WgradArgs no_wg{};
   const int wg_blocks = defer ? defer->parts * defer->ytiles * defer->ztiles : 0;
   const dim3 scan_grid(static_cast<unsigned>(scan_blocks + wg_blocks));
-  uint64_t* words = reinterpret_cast<uint64_t*>(scan_state + 2);
+  uint64_t* words = reinterpret_cast<uint64_t*>(n_long + 2);
   if (!defer)
     hipLaunchKernelGGL(k_csc_scan<0>, scan_grid, dim3(256), 0, s, sizes, cnt, off, pos, scan_state, words,
-                       scan_state + 1, long_rows, scan_blocks, no_wg);
+                       n_long, long_rows, scan_blocks, no_wg);
   else if (defer->vec)
     hipLaunchKernelGGL(k_csc_scan<1>, scan_grid, dim3(256), 0, s, sizes, cnt, off, pos, scan_state, words,
-                       scan_state + 1, long_rows, scan_blocks, *defer);
+                       n_long, long_rows, scan_blocks, *defer);
   else
     hipLaunchKernelGGL(k_csc_scan<2>, scan_grid, dim3(256), 0, s, sizes, cnt, off, pos, scan_state, words,
-                       scan_state + 1, long_rows, scan_blocks, *defer);
+                       n_long, long_rows, scan_blocks, *defer);
   const int64_t slots = std::max<int64_t>(cap_dst, 1) * std::max(fanout, 1);
   const int fill_blocks = static_cast<int>(grid_of(slots, 1 << 16));
   const ReduceArgs no_red{};
@@ -1425,7 +1426,7 @@ hipError_t launch_mean_backward(const int32_t* sizes, const int32_t* indptr, con
     constexpr int kG = GMB_PULL_UPDATE_G, kR = GMB_PULL_UPDATE_R, kE = GMB_PULL_UPDATE_E;
     const unsigned rows = grid_of((std::max<int64_t>(cap_src, 1) + kR - 1) / kR * kG, 1 << 30);
     hipLaunchKernelGGL((k_pull_update<kG, kR, kE>), dim3(rows + kLongGrid), dim3(256), 0, s, sizes, off, csc,
-                       cap_nnz, dM, dH, d, table, ids, num_nodes, lr, static_cast<int>(rows), scan_state + 1,
+                       cap_nnz, dM, dH, d, table, ids, num_nodes, lr, static_cast<int>(rows), n_long,
                        long_rows);
     return hipGetLastError();
   }
@@ -1437,7 +1438,7 @@ hipError_t launch_mean_backward(const int32_t* sizes, const int32_t* indptr, con
   const unsigned rows = grid_of(std::max<int64_t>(cap_src, 1) * G, 1 << 30);
 #define GMB_PULL(GG)                                                                                     \
   hipLaunchKernelGGL((k_pull_mean<GG>), dim3(rows + kLongGrid), dim3(256), 0, s, sizes, off, csc, cap_nnz, dM, \
-                     out, d, dH, static_cast<int>(rows), scan_state + 1, long_rows)
+                     out, d, dH, static_cast<int>(rows), n_long, long_rows)
   switch (G) {
     case 4: GMB_PULL(4); break;
     case 8: GMB_PULL(8); break;

@@ -73,6 +73,8 @@ namespace gmb {
 
 namespace {
 
+static_assert(kTicketWords == kScanTicketWords, "the plans' ticket space");
+
 __device__ __forceinline__ CsrView view(const CsrArgs& a) {
   return CsrView{a.indptr, a.indices, a.num_nodes, a.wide};
 }

@@ -4,10 +4,10 @@
 // "Single-pass parallel prefix scan with decoupled look-back", NVIDIA
 // technical report NVR-2016-002): every tile publishes its aggregate at
 // once, then walks back over its predecessors until it meets one that has
-// published an inclusive prefix.  Tiles are numbered in the order in which
-// workgroups start (an atomic ticket), so a tile only ever waits on tiles
-// that are already running, and every tile publishes its aggregate before
-// it waits: every wait ends.  The wait is still bounded (kLookbackSpins
+// published an inclusive prefix.  Tiles are numbered by tickets
+// (claim_tile), so that a tile only ever waits on tiles that run or are next
+// to start, and every tile publishes its aggregate before it waits: every
+// wait ends.  The wait is still bounded (kLookbackSpins
 // sleeps); a tile that runs out reports it, publishes a wrong prefix (so
 // its successors still finish) and goes on.
 #pragma once
@@ -148,9 +148,29 @@ __device__ bool tile_lookback_multi(uint64_t* tiles, int64_t stride, int tile,
 }
 
 // Claims the next tile number for this workgroup (thread 0 takes a ticket,
-// the block reads it from LDS).
-__device__ __forceinline__ int claim_tile(uint32_t* counter, int* s_tile) {
-  if (threadIdx.x == 0) *s_tile = static_cast<int>(atomicAdd(counter, 1u));
+// the block reads it from LDS).  Tickets on one counter are served one after
+// another, about 13 ns each, so a scan's last tile started microseconds
+// after its first (256 tiles 3.3 us); kTicketShards counters on lines of
+// their own serve the workgroups b = s mod kTicketShards: shard s's k-th ticket
+// is tile kTicketShards k + s, so the tiles of the first n workgroups are 0
+// .. n - 1 as before.
+//
+// Every wait still ends: let T, in shard s, be the smallest unfinished tile.
+// If it runs, all its predecessors have finished, so it finishes.  If it has
+// not started, the workgroups of shard s that have are tiles below T (a shard
+// gives its tickets in the order in which they are asked for), so they have
+// finished and hold nothing; workgroups go round robin over the 8 XCDs, so
+// shard s has an XCD to itself and its next workgroup, which becomes T, is not
+// kept out by waiting ones of other shards.  Where workgroups start in order
+// (on one XCD, too), tile numbers are workgroup numbers and the same holds.
+constexpr int kTicketShards = 8;
+constexpr int kTicketStride = 32;   // uint32 words between the shards' counters
+constexpr int kTicketWords = kTicketShards * kTicketStride;
+__device__ __forceinline__ int claim_tile(uint32_t* counters, int* s_tile) {
+  if (threadIdx.x == 0) {
+    const uint32_t shard = blockIdx.x % kTicketShards;
+    *s_tile = static_cast<int>(atomicAdd(&counters[shard * kTicketStride], 1u) * kTicketShards + shard);
+  }
   __syncthreads();
   return *s_tile;
 }
