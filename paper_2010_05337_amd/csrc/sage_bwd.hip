@@ -829,7 +829,6 @@ void k_csc_scan(const int32_t* __restrict__ sizes, int32_t* __restrict__ cnt, in
     }
   }
   __shared__ int s_tile;
-  __shared__ int32_t s_excl;
   __shared__ int32_t smem[4];
   const int32_t n = load_size(&sizes[kNSrc]);
   const int ntiles = (n + kScanTile - 1) / kScanTile;
@@ -866,14 +865,9 @@ void k_csc_scan(const int32_t* __restrict__ sizes, int32_t* __restrict__ cnt, in
   const int32_t x[1] = {sum};
   int32_t excl[1], total[1];
   block_exclusive_scan_multi<256, 1>(x, excl, total, smem);
-  if (threadIdx.x < 64) {
-    const int32_t agg[1] = {total[0]};
-    int32_t ex[1];
-    tile_lookback_multi<1>(words, 0, tile, agg, ex);
-    if (threadIdx.x == 0) s_excl = ex[0];
-  }
-  __syncthreads();
-  int32_t o = s_excl + excl[0];
+  int32_t before[1];
+  tile_prefix<256, 1>(words, 0, tile, ntiles, total, before, smem);
+  int32_t o = before[0] + excl[0];
 #pragma unroll
   for (int v = 0; v < kScanVec; ++v) {
     const int32_t a = i0 + 4 * v;
@@ -895,7 +889,7 @@ void k_csc_scan(const int32_t* __restrict__ sizes, int32_t* __restrict__ cnt, in
         }
     }
   }
-  if (tile == ntiles - 1 && threadIdx.x == 0) off[n] = s_excl + total[0];
+  if (tile == ntiles - 1 && threadIdx.x == 0) off[n] = before[0] + total[0];
   // sources with long lists (hubs) go to the list the workgroup-per-row
   // kernel takes (the per-row kernels skip them); after the look-back, so
   // that the successors' waits do not include it; one atomic per wave and

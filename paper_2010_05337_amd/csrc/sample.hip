@@ -665,7 +665,6 @@ template <int NV, bool WIDE, int ITEMS>
 __global__ __launch_bounds__(kScanBlock) void k_assign(AssignArgs a, CsrArgs ga, int32_t* ids,
                                                        uint32_t* table, uint32_t* status) {
   __shared__ int s_tile;
-  __shared__ int32_t s_excl[NV];
   __shared__ int32_t s_wave[NV * (kScanBlock / 64)];
   __shared__ int32_t s_pos[(kScanBlock * ITEMS)];
   const CsrView g = view(ga);
@@ -714,18 +713,8 @@ __global__ __launch_bounds__(kScanBlock) void k_assign(AssignArgs a, CsrArgs ga,
     for (int q = 0; q < ITEMS; ++q) sum[v] += ((flags >> q) & 1u) ? clamp_degree(deg[q], a.fanout[v]) : 0;
   }
   block_exclusive_scan_multi<kScanBlock, NV>(sum, thr, total, s_wave);
-  if (threadIdx.x < 64) {
-    int32_t ex[NV];
-    const bool ok = tile_lookback_multi<NV>(a.tiles, a.tile_stride, tile, total, ex);
-    if (threadIdx.x == 0) {
-      if (!ok) raise_status(status, GMB_STATUS_INTERNAL);
-#pragma unroll
-      for (int v = 0; v < NV; ++v) s_excl[v] = ex[v];
-    }
-  }
-  __syncthreads();
-#pragma unroll
-  for (int v = 0; v < NV; ++v) excl[v] = s_excl[v];
+  if (!tile_prefix<kScanBlock, NV>(a.tiles, a.tile_stride, tile, num_tiles, total, excl, s_wave) && threadIdx.x == 0)
+    raise_status(status, GMB_STATUS_INTERNAL);
 
   // new vertices: position, ids, table, local id, later hops' row offsets
   int32_t r = n_dst + excl[0] + thr[0];
@@ -1187,7 +1176,6 @@ __global__ __launch_bounds__(kRankBlock) void k_rank(RankArgs a, CsrArgs ga, int
   constexpr int kPer = (T / kRankBlock) | 1;   // entries per thread, at most
   constexpr int kBatch = 4;                  // pairs a thread reads at once
   __shared__ int s_tile;
-  __shared__ int32_t s_excl[NV];
   __shared__ int32_t s_wave[NV * (kRankBlock / 64)];
   __shared__ int32_t s_key[T];
   __shared__ int32_t s_res[T];   // the answers; then the new vertices' local ids
@@ -1261,18 +1249,8 @@ __global__ __launch_bounds__(kRankBlock) void k_rank(RankArgs a, CsrArgs ga, int
     for (int q = 0; q < kPer; ++q) sum[v] += ((flags >> q) & 1u) ? clamp_degree(deg[q], a.fanout[v]) : 0;
   }
   block_exclusive_scan_multi<kRankBlock, NV>(sum, thr, total, s_wave);
-  if (threadIdx.x < 64) {
-    int32_t ex[NV];
-    const bool ok = tile_lookback_multi<NV>(a.tiles, a.tile_stride, tile, total, ex);
-    if (threadIdx.x == 0) {
-      if (!ok) raise_status(status, GMB_STATUS_INTERNAL);
-#pragma unroll
-      for (int v = 0; v < NV; ++v) s_excl[v] = ex[v];
-    }
-  }
-  __syncthreads();
-#pragma unroll
-  for (int v = 0; v < NV; ++v) excl[v] = s_excl[v];
+  if (!tile_prefix<kRankBlock, NV>(a.tiles, a.tile_stride, tile, num_tiles, total, excl, s_wave) && threadIdx.x == 0)
+    raise_status(status, GMB_STATUS_INTERNAL);
 
   // new vertices: position, ids, local id, later hops' row offsets
   int32_t rk = n_dst + excl[0] + thr[0];

@@ -1,5 +1,9 @@
 // Block-wide and single-pass device-wide exclusive scans (device side).
 //
+// Every tile of a device-wide scan publishes its aggregate before it waits
+// for its predecessors': a flat read of all of them in short scans
+// (tile_prefix), else a look-back.
+//
 // The device-wide scan is a decoupled look-back scan (Merrill & Garland,
 // "Single-pass parallel prefix scan with decoupled look-back", NVIDIA
 // technical report NVR-2016-002): every tile publishes its aggregate at
@@ -145,6 +149,76 @@ __device__ bool tile_lookback_multi(uint64_t* tiles, int64_t stride, int tile,
       publish_tile(tiles + a * stride, tile, kTilePrefix | static_cast<uint32_t>(exclusive[a] + aggregate[a]));
   }
   return ok;
+}
+
+// The tile's exclusive prefixes, by the whole block of BLOCK threads (every
+// thread must call it; `smem` holds NV * BLOCK/64 ints; the prefixes are
+// returned to every thread).  Up to kFlatTiles tiles the walk is flat: a tile
+// publishes its aggregates, and its threads read those of all its
+// predecessors at once (thread i the tiles i, i + BLOCK, ...) and add them up,
+// so a tile waits for one round trip after its slowest predecessor's
+// aggregate.  The look-back by one wave takes a round trip per 64
+// predecessors when all tiles run side by side and no prefix is published
+// yet: k_rank over 512 routers 12.2 -> 11.4 us (over 256 the same).  The flat
+// walk reads tiles^2 / 2 words, so longer scans look back.  `num_tiles` must be
+// the same for all tiles of a scan.
+constexpr int kFlatTiles = 1024;
+template <int BLOCK, int NV>
+__device__ __forceinline__ bool tile_prefix(uint64_t* tiles, int64_t stride, int tile, int num_tiles,
+                                            const int32_t (&aggregate)[NV], int32_t (&exclusive)[NV], int32_t* smem) {
+  constexpr int W = BLOCK / 64;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  bool ok = true;
+  int32_t sum[NV];
+  if (num_tiles <= kFlatTiles) {   // uniform
+    if (threadIdx.x == 0) {
+#pragma unroll
+      for (int a = 0; a < NV; ++a)
+        publish_tile(tiles + a * stride, tile, kTileAggregate | static_cast<uint32_t>(aggregate[a]));
+    }
+#pragma unroll
+    for (int a = 0; a < NV; ++a) sum[a] = 0;
+    int spins = 0;
+    for (int t = threadIdx.x; t < tile; t += BLOCK) {
+      for (;;) {
+        uint64_t w[NV];
+        bool pending = false;
+#pragma unroll
+        for (int a = 0; a < NV; ++a)
+          w[a] = __hip_atomic_load(&tiles[a * stride + t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+        for (int a = 0; a < NV; ++a) pending |= w[a] == 0;
+        if (!pending || ++spins > kLookbackSpins) {
+          ok &= !pending;
+#pragma unroll
+          for (int a = 0; a < NV; ++a) sum[a] += static_cast<int32_t>(static_cast<uint32_t>(w[a]));
+          break;
+        }
+        __builtin_amdgcn_s_sleep(1);
+      }
+    }
+#pragma unroll
+    for (int a = 0; a < NV; ++a) {
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) sum[a] += __shfl_xor(sum[a], o, 64);
+    }
+  } else {
+#pragma unroll
+    for (int a = 0; a < NV; ++a) sum[a] = 0;
+    if (wave == 0) ok = tile_lookback_multi<NV>(tiles, stride, tile, aggregate, sum);
+  }
+  if (lane == 0) {
+#pragma unroll
+    for (int a = 0; a < NV; ++a) smem[a * W + wave] = sum[a];
+  }
+  const bool all = __syncthreads_and(ok) != 0;
+#pragma unroll
+  for (int a = 0; a < NV; ++a) {
+    exclusive[a] = 0;
+#pragma unroll
+    for (int w = 0; w < W; ++w) exclusive[a] += smem[a * W + w];
+  }
+  return all;
 }
 
 // Claims the next tile number for this workgroup (thread 0 takes a ticket,
