@@ -2,10 +2,13 @@
 // pull of the mini-batch's vertex features from the key-value store,
 // DistDGL Section III-C, here a local copy in HBM).
 //
-// A group of G lanes copies one row with the widest access the row's
-// alignment allows (16-byte loads for 400-byte fp32x100 and 256-byte
-// bf16x128 rows); every group keeps U rows in flight before it stores, so
-// each wave has U independent row reads outstanding.
+// A group of G lanes copies one row in 16-byte chunks (shorter accesses only
+// for rows below 16 bytes); every group keeps U rows in flight before it
+// stores, so each wave has U independent row reads outstanding.  Rows need no
+// alignment (global accesses may be misaligned), and the last chunk of a row
+// that 16 does not divide starts 16 bytes before the row's end: it rewrites
+// bytes of the chunk before it with the same values.  A row of 75 fp32 is so
+// 19 chunks of one pass of 32 lanes; 4-byte accesses took two passes of 64.
 #include "common.hpp"
 #include "kernels.hpp"
 
@@ -35,9 +38,10 @@ __device__ __forceinline__ void opaque_vec(V& x) {
 // compiler drain every outstanding load before the next one.
 template <typename V, int G, int U>
 __global__ __launch_bounds__(256) void k_gather(const int32_t* __restrict__ ids, const int32_t* n_dev,
-                                                int64_t n_cap, const V* __restrict__ feats,
-                                                int64_t num_nodes, int cpr, V* __restrict__ out,
+                                                int64_t n_cap, const char* __restrict__ feats,
+                                                int64_t num_nodes, int64_t row_bytes, char* __restrict__ out,
                                                 uint32_t* status) {
+  const int cpr = static_cast<int>((row_bytes + sizeof(V) - 1) / sizeof(V));
   int64_t n = n_cap;
   if (n_dev) {
     const int32_t m = load_size(n_dev);
@@ -66,15 +70,18 @@ __global__ __launch_bounds__(256) void k_gather(const int32_t* __restrict__ ids,
       id[u] = in[u] ? id[u] : 0;
     }
     for (int c = lane; c < cpr; c += G) {
+      const int64_t at = c + 1 < cpr ? static_cast<int64_t>(c) * sizeof(V) : row_bytes - static_cast<int64_t>(sizeof(V));
       V val[U];
 #pragma unroll
-      for (int u = 0; u < U; ++u) val[u] = feats[static_cast<int64_t>(id[u]) * cpr + c];
+      for (int u = 0; u < U; ++u)
+        __builtin_memcpy(&val[u], feats + static_cast<int64_t>(id[u]) * row_bytes + at, sizeof(V));
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         opaque_vec(val[u]);
         const int64_t r = row + u * stride;
-        if (r < n) out[r * cpr + c] = in[u] ? val[u] : V{};
+        const V x = in[u] ? val[u] : V{};
+        if (r < n) __builtin_memcpy(out + r * row_bytes + at, &x, sizeof(V));
       }
     }
   }
@@ -83,8 +90,9 @@ __global__ __launch_bounds__(256) void k_gather(const int32_t* __restrict__ ids,
 
 template <typename V>
 hipError_t dispatch(const int32_t* ids, const int32_t* n_dev, int64_t n_cap, const void* feats,
-                    int64_t num_nodes, int cpr, void* out, uint32_t* status, hipStream_t s) {
+                    int64_t num_nodes, int64_t row_bytes, void* out, uint32_t* status, hipStream_t s) {
   constexpr int U = 4;
+  const int64_t cpr = (row_bytes + sizeof(V) - 1) / sizeof(V);
   int G = 64;
   if (cpr <= 4) G = 4;
   else if (cpr <= 8) G = 8;
@@ -95,15 +103,18 @@ hipError_t dispatch(const int32_t* ids, const int32_t* n_dev, int64_t n_cap, con
   if (blocks > GMB_GATHER_MAX_BLOCKS) blocks = GMB_GATHER_MAX_BLOCKS;
   if (blocks < 1) blocks = 1;
   const dim3 grid(static_cast<unsigned>(blocks)), block(256);
-  const V* f = static_cast<const V*>(feats);
-  V* o = static_cast<V*>(out);
+  const char* f = static_cast<const char*>(feats);
+  char* o = static_cast<char*>(out);
+#define GMB_GATHER(GG) \
+  hipLaunchKernelGGL((k_gather<V, GG, U>), grid, block, 0, s, ids, n_dev, n_cap, f, num_nodes, row_bytes, o, status)
   switch (G) {
-    case 4: hipLaunchKernelGGL((k_gather<V, 4, U>), grid, block, 0, s, ids, n_dev, n_cap, f, num_nodes, cpr, o, status); break;
-    case 8: hipLaunchKernelGGL((k_gather<V, 8, U>), grid, block, 0, s, ids, n_dev, n_cap, f, num_nodes, cpr, o, status); break;
-    case 16: hipLaunchKernelGGL((k_gather<V, 16, U>), grid, block, 0, s, ids, n_dev, n_cap, f, num_nodes, cpr, o, status); break;
-    case 32: hipLaunchKernelGGL((k_gather<V, 32, U>), grid, block, 0, s, ids, n_dev, n_cap, f, num_nodes, cpr, o, status); break;
-    default: hipLaunchKernelGGL((k_gather<V, 64, U>), grid, block, 0, s, ids, n_dev, n_cap, f, num_nodes, cpr, o, status); break;
+    case 4: GMB_GATHER(4); break;
+    case 8: GMB_GATHER(8); break;
+    case 16: GMB_GATHER(16); break;
+    case 32: GMB_GATHER(32); break;
+    default: GMB_GATHER(64); break;
   }
+#undef GMB_GATHER
   return hipGetLastError();
 }
 
@@ -112,14 +123,10 @@ hipError_t dispatch(const int32_t* ids, const int32_t* n_dev, int64_t n_cap, con
 hipError_t launch_gather(const int32_t* ids, const int32_t* n_dev, int64_t n_cap, const void* feats,
                          int64_t num_nodes, int64_t row_bytes, void* out, uint32_t* status,
                          hipStream_t s) {
-  const uintptr_t align = reinterpret_cast<uintptr_t>(feats) | reinterpret_cast<uintptr_t>(out);
-  if (row_bytes % 16 == 0 && align % 16 == 0)
-    return dispatch<uint4>(ids, n_dev, n_cap, feats, num_nodes, static_cast<int>(row_bytes / 16), out, status, s);
-  if (row_bytes % 8 == 0 && align % 8 == 0)
-    return dispatch<uint2>(ids, n_dev, n_cap, feats, num_nodes, static_cast<int>(row_bytes / 8), out, status, s);
-  if (row_bytes % 4 == 0 && align % 4 == 0)
-    return dispatch<uint32_t>(ids, n_dev, n_cap, feats, num_nodes, static_cast<int>(row_bytes / 4), out, status, s);
-  return dispatch<uint16_t>(ids, n_dev, n_cap, feats, num_nodes, static_cast<int>(row_bytes / 2), out, status, s);
+  if (row_bytes >= 16) return dispatch<uint4>(ids, n_dev, n_cap, feats, num_nodes, row_bytes, out, status, s);
+  if (row_bytes >= 8) return dispatch<uint2>(ids, n_dev, n_cap, feats, num_nodes, row_bytes, out, status, s);
+  if (row_bytes >= 4) return dispatch<uint32_t>(ids, n_dev, n_cap, feats, num_nodes, row_bytes, out, status, s);
+  return dispatch<uint16_t>(ids, n_dev, n_cap, feats, num_nodes, row_bytes, out, status, s);
 }
 
 }  // namespace gmb

@@ -102,7 +102,7 @@ struct LinearOp {
   int quad_b;   // N % 4 == 0 and 16-byte aligned matrices: the slab takes load_b8x4
   static constexpr bool kQuadCapable = true;
   static constexpr bool kEarlyA = true;   // the first tile's A loads overlap the slab's
-  __host__ __device__ int k2() const { return 2 * K; }
+  static constexpr bool kFixA = false;    // A's values need no masking
   __host__ __device__ int n() const { return N; }
   __host__ __device__ int64_t ldo() const { return N; }
   __device__ void a_rows(int64_t row, const float*& p0, const float*& p1) const {
@@ -150,19 +150,108 @@ struct LinearOp {
   __device__ float* out_at(int64_t row, int col) const { return out + row * N + col; }
 };
 
+// The forward linear for any d_in from 8: the k run over groups of eight, gh
+// = ceil(d_in / 8) groups of h_v, then gh of the mean.  Group g of a half
+// starts at k = 8 g, the last one at d_in - 8, with its first `cut` = 8 gh -
+// d_in elements (the group before holds them) zeroed in A and in B; so every
+// read of A is 16 bytes inside the row, misaligned where d_in % 4 != 0 (global
+// reads may be).  75 -> 100 on 2.6k rows: 27.6 us on the general kernel, 5.3
+// here.  Infinite operands give what that kernel gave (plain).
+struct LinearAnyOp {
+  const float* Hs;
+  const float* Ag;
+  const float* Ws;
+  const float* Wn;
+  const float* bias_v;
+  int d_in, gh, N, relu;
+  float* out;
+  int quad_b;   // N % 4 == 0 and 16-byte aligned matrices
+  static constexpr bool kQuadCapable = true;
+  static constexpr bool kEarlyA = true;
+  static constexpr bool kFixA = true;
+  __host__ __device__ int n() const { return N; }
+  __host__ __device__ int64_t ldo() const { return N; }
+  // first k of group g within its half; half: 0 h_v, 1 the mean, -1 past both
+  __device__ int group_k(int g, int& half) const {
+    half = g < gh ? 0 : (g < 2 * gh ? 1 : -1);
+    const int gi = g - (half > 0 ? gh : 0);
+    return half < 0 ? 0 : (gi == gh - 1 ? d_in - 8 : 8 * gi);
+  }
+  __device__ void a_rows(int64_t row, const float*& p0, const float*& p1) const {
+    p0 = Hs + row * d_in;
+    p1 = Ag + row * d_in;
+  }
+  __device__ float4 load_a4(const float* p0, const float* p1, int k) const {
+    int half;
+    const int kk = group_k(k >> 3, half) + (k & 4);
+    float4 x;
+    __builtin_memcpy(&x, pick_ptr(half > 0, p1, p0) + kk, 16);
+    return x;
+  }
+  // the eight values of the group at k (a multiple of 8), zeroed where they
+  // belong to another group or to none
+  __device__ void fix_a(float4& lo, float4& hi, int k) const {
+    const int g = k >> 3;
+    const int cut = g >= 2 * gh ? 8 : ((g == gh - 1 || g == 2 * gh - 1) ? 8 * gh - d_in : 0);
+    float v[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+#pragma unroll
+    for (int s = 0; s < 8; ++s) v[s] = s < cut ? 0.f : v[s];
+    lo = make_float4(v[0], v[1], v[2], v[3]);
+    hi = make_float4(v[4], v[5], v[6], v[7]);
+  }
+  // one entry of A B in plain fp32
+  __device__ float plain(int64_t row, int col) const {
+    float z = 0.f;
+    for (int k = 0; k < d_in; ++k)
+      z += Hs[row * d_in + k] * Ws[static_cast<int64_t>(k) * N + col] +
+           Ag[row * d_in + k] * Wn[static_cast<int64_t>(k) * N + col];
+    return z;
+  }
+  __device__ void load_b8(bool item, int k0, int gn, float (&w)[8], bool (&in)[8]) const {
+    const int g = k0 >> 3;
+    int half;
+    const int kb = group_k(item ? g : 2 * gh, half);
+    const int cut = (g == gh - 1 || g == 2 * gh - 1) ? 8 * gh - d_in : 0;
+    const bool cols = item & (gn < N);
+    const float* src = pick_ptr(half > 0, Wn, Ws) + static_cast<int64_t>(kb) * N + (cols ? gn : 0);
+#pragma unroll
+    for (int s8 = 0; s8 < 8; ++s8) {
+      in[s8] = cols & (half >= 0) & (s8 >= cut);
+      w[s8] = src[static_cast<int64_t>(s8) * N];
+    }
+  }
+  __device__ void load_b8x4(bool item, int k0, int gn, float (&w)[4][8], bool (&in)[8]) const {
+    const int g = k0 >> 3;
+    int half;
+    const int kb = group_k(item ? g : 2 * gh, half);
+    const int cut = (g == gh - 1 || g == 2 * gh - 1) ? 8 * gh - d_in : 0;
+    const bool cols = item & (gn < N);
+    const float* src = pick_ptr(half > 0, Wn, Ws) + static_cast<int64_t>(kb) * N + (cols ? gn : 0);
+#pragma unroll
+    for (int s8 = 0; s8 < 8; ++s8) {
+      in[s8] = cols & (half >= 0) & (s8 >= cut);
+      const float4 x = *reinterpret_cast<const float4*>(src + static_cast<int64_t>(s8) * N);
+      w[0][s8] = x.x; w[1][s8] = x.y; w[2][s8] = x.z; w[3][s8] = x.w;
+    }
+  }
+  __device__ float bias(int col) const { return bias_v[col < N ? col : N - 1]; }
+  __device__ float act(float z) const { return relu ? (z > 0.f ? z : 0.f) : z; }
+  __device__ float* out_at(int64_t row, int col) const { return out + row * N + col; }
+};
+
 // The input gradient: A = dZ (d_out columns, row stride ldz), B = [W_self;
 // W_neigh]^T (B[k][nn] = W[nn][k], 2 d_in columns), the result's columns
 // nn < d_in to dH and the others to dM (row stride d_in each).
 struct DgradOp {
   static constexpr bool kQuadCapable = false;   // its eight k are one contiguous run already
   static constexpr bool kEarlyA = false;        // (the largest tiling has no registers to spare for it)
+  static constexpr bool kFixA = false;
   const float* dZ;
   const float* Ws;
   const float* Wn;
   int ldz, d_out, d_in;
   float* dH;
   float* dM;
-  __host__ __device__ int k2() const { return d_out; }
   __host__ __device__ int n() const { return 2 * d_in; }
   __host__ __device__ int64_t ldo() const { return d_in; }
   __device__ void a_rows(int64_t row, const float*& p0, const float*& p1) const {
@@ -225,6 +314,10 @@ __device__ __forceinline__ void parts_gemm(const Op& op, int32_t M) {
   };
   auto load4 = [&](const float* hrow, const float* grow, int k) -> float4 { return op.load_a4(hrow, grow, k); };
   auto chunk_of = [&](int i) { return SPLIT > 1 ? wave + WAVES * i : i; };
+  auto cut_a = [&](float4 lo, float4 hi, int i, bf16x8 (&part)[3]) {   // the A values of chunk i
+    if constexpr (Op::kFixA) op.fix_a(lo, hi, chunk_of(i) * 32 + 8 * q);
+    split8(lo, hi, part);
+  };
   float4 a[R][MYCH][2];
   const float* hr[R];
   const float* gr[R];
@@ -328,13 +421,29 @@ __device__ __forceinline__ void parts_gemm(const Op& op, int32_t M) {
   floatx4 held[SPLIT > 1 ? PER_THREAD : R][SPLIT > 1 ? 1 : J];
   int held_rt = -1;
   const int64_t ld = op.ldo();
+  bool bad = false;   // (kFixA) a NaN among the values of this lane's entries
+  auto note = [&](float v) {
+    if constexpr (Op::kFixA) bad |= v != v;
+  };
   auto store4 = [&](int row0, int col, const floatx4& v, float b) {
     if (col >= N) return;
     float* o = op.out_at(row0, col);
     const bool full = row0 + 4 <= M;
 #pragma unroll
     for (int r = 0; r < 4; ++r)
-      if (full || row0 + r < M) o[static_cast<int64_t>(r) * ld] = op.act(v[r] + b);
+      if (full || row0 + r < M) {
+        note(v[r]);
+        o[static_cast<int64_t>(r) * ld] = op.act(v[r] + b);
+      }
+  };
+  // (kFixA) the cut turns an infinite operand into NaN parts: a lane that
+  // met a NaN takes its entries again as plain fp32 sums
+  auto redo = [&](int row0, int col) {
+    if constexpr (Op::kFixA) {
+#pragma unroll 1
+      for (int r = 0; r < 4; ++r)
+        if (row0 + r < M && col < N) *op.out_at(row0 + r, col) = op.act(op.plain(row0 + r, col) + op.bias(col));
+    }
   };
   auto store_held = [&]() {
     if (held_rt < 0) return;
@@ -356,12 +465,30 @@ __device__ __forceinline__ void parts_gemm(const Op& op, int32_t M) {
           for (int j = 0; j < J; ++j) {
             float* o = op.out_at(row0, n0 + j * 16 + r16);
 #pragma unroll
-            for (int r = 0; r < 4; ++r) o[static_cast<int64_t>(r) * ld] = op.act(held[f][j][r] + bv[j]);
+            for (int r = 0; r < 4; ++r) {
+              note(held[f][j][r]);
+              o[static_cast<int64_t>(r) * ld] = op.act(held[f][j][r] + bv[j]);
+            }
           }
         } else {
 #pragma unroll
           for (int j = 0; j < J; ++j) store4(row0, n0 + j * 16 + r16, held[f][j], bv[j]);
         }
+      }
+    }
+    if constexpr (Op::kFixA) {
+      if (__any(bad)) {
+        if (bad) {
+          if constexpr (SPLIT > 1) {
+#pragma unroll 1
+            for (int e = threadIdx.x; e < ENTRIES; e += THREADS)
+              redo(frag_row0(held_rt, e / (J * 64)) + 4 * ((e % 64) >> 4), n0 + ((e / 64) % J) * 16 + (e & 15));
+          } else {
+#pragma unroll 1
+            for (int e = 0; e < R * J; ++e) redo(frag_row0(held_rt, e / J) + 4 * q, n0 + (e % J) * 16 + r16);
+          }
+        }
+        bad = false;
       }
     }
   };
@@ -393,7 +520,7 @@ __device__ __forceinline__ void parts_gemm(const Op& op, int32_t M) {
     // issue between the matrix-core ones)
     bf16x8 p0[R][3], p1[R][3];
 #pragma unroll
-    for (int f = 0; f < R; ++f) split8(a[f][0][0], a[f][0][1], p0[f]);
+    for (int f = 0; f < R; ++f) cut_a(a[f][0][0], a[f][0][1], 0, p0[f]);
 #pragma unroll
     for (int f = 0; f < R; ++f) {
       const int k = chunk_of(0) * 32 + 8 * q;
@@ -417,7 +544,7 @@ __device__ __forceinline__ void parts_gemm(const Op& op, int32_t M) {
       __builtin_amdgcn_sched_barrier(0);
       if (i + 1 < MYCH) {
 #pragma unroll
-        for (int f = 0; f < R; ++f) split8(a[f][i + 1][0], a[f][i + 1][1], pn[f]);
+        for (int f = 0; f < R; ++f) cut_a(a[f][i + 1][0], a[f][i + 1][1], i + 1, pn[f]);
       }
       if (chunk_of(i) < NCH) {   // uniform: depends on the wave index only
 #pragma unroll

@@ -39,7 +39,8 @@ __device__ __forceinline__ void opaque(float4& x) {
 template <int VEC>
 __device__ __forceinline__ void load_chunk(const float* p, float (&v)[VEC]) {
   if constexpr (VEC == 4) {
-    const float4 x = *reinterpret_cast<const float4*>(p);
+    float4 x;
+    __builtin_memcpy(&x, p, 16);   // rows need no alignment
     v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w;
   } else {
 #pragma unroll
@@ -50,7 +51,8 @@ __device__ __forceinline__ void load_chunk(const float* p, float (&v)[VEC]) {
 template <int VEC>
 __device__ __forceinline__ void load_chunk(const uint16_t* p, float (&v)[VEC]) {
   if constexpr (VEC == 8) {
-    const uint4 x = *reinterpret_cast<const uint4*>(p);
+    uint4 x;
+    __builtin_memcpy(&x, p, 16);
     const uint32_t w[4] = {x.x, x.y, x.z, x.w};
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -66,7 +68,8 @@ __device__ __forceinline__ void load_chunk(const uint16_t* p, float (&v)[VEC]) {
 template <int VEC>
 __device__ __forceinline__ void store_chunk(float* p, const float (&v)[VEC]) {
   if constexpr (VEC == 4) {
-    *reinterpret_cast<float4*>(p) = make_float4(v[0], v[1], v[2], v[3]);
+    const float4 x = make_float4(v[0], v[1], v[2], v[3]);
+    __builtin_memcpy(p, &x, 16);
   } else {
 #pragma unroll
     for (int i = 0; i < VEC; ++i) p[i] = v[i];
@@ -81,7 +84,7 @@ __device__ __forceinline__ void store_chunk(uint16_t* p, const float (&v)[VEC]) 
     x.y = f32_to_bf16(v[2]) | (static_cast<uint32_t>(f32_to_bf16(v[3])) << 16);
     x.z = f32_to_bf16(v[4]) | (static_cast<uint32_t>(f32_to_bf16(v[5])) << 16);
     x.w = f32_to_bf16(v[6]) | (static_cast<uint32_t>(f32_to_bf16(v[7])) << 16);
-    *reinterpret_cast<uint4*>(p) = x;
+    __builtin_memcpy(p, &x, 16);
   } else {
 #pragma unroll
     for (int i = 0; i < VEC; ++i) p[i] = f32_to_bf16(v[i]);
@@ -103,11 +106,14 @@ __global__ __launch_bounds__(256) void k_mean(const int32_t* sizes, const int32_
   const int32_t n_dst = load_size(&sizes[kNDst]);
   if (row >= n_dst) return;   // the whole group leaves together
   const int32_t k = end - beg;
-  const int chunks = d / VEC;
+  // the last chunk of a width that VEC does not divide starts VEC before the
+  // row's end (the elements it shares with the chunk before get the same
+  // sums, in the same order)
+  const int chunks = (d + VEC - 1) / VEC;
   const int passes = (chunks + G - 1) / G;
   for (int cc = 0; cc < passes; ++cc) {
     const int c = cc * G + lane;
-    const int cl = c < chunks ? c : chunks - 1;
+    const int at = c + 1 < chunks ? c * VEC : d - VEC;
     float acc[VEC];
 #pragma unroll
     for (int i = 0; i < VEC; ++i) acc[i] = 0.f;
@@ -127,7 +133,7 @@ __global__ __launch_bounds__(256) void k_mean(const int32_t* sizes, const int32_
         float x[U][VEC];
 #pragma unroll
         for (int u = 0; u < U; ++u)
-          load_chunk<VEC>(H + static_cast<int64_t>(id[u]) * d + cl * VEC, x[u]);
+          load_chunk<VEC>(H + static_cast<int64_t>(id[u]) * d + at, x[u]);
 #pragma unroll
         for (int u = 0; u < U; ++u) {
           const bool in = u0 + u < n_here;
@@ -145,14 +151,14 @@ __global__ __launch_bounds__(256) void k_mean(const int32_t* sizes, const int32_
 #pragma unroll
       for (int i = 0; i < VEC; ++i) acc[i] = acc[i] / kf;
     }
-    if (c < chunks) store_chunk<VEC>(M + row * d + c * VEC, acc);
+    if (c < chunks) store_chunk<VEC>(M + row * d + at, acc);
   }
 }
 
 template <typename T, int VEC>
 hipError_t mean_dispatch(const int32_t* sizes, const int32_t* indptr, const int32_t* local, const void* h,
                          int d, void* m, int64_t cap_dst, int fanout, int64_t max_id, hipStream_t s) {
-  const int chunks = d / VEC;
+  const int chunks = (d + VEC - 1) / VEC;
   int G = 64;
   if (chunks <= 4) G = 4;
   else if (chunks <= 8) G = 8;
@@ -663,20 +669,17 @@ void launch_slab_for(const int32_t* sizes, const float* hs, const float* ag, con
     launch_slab<NCH, 2, 4>(sizes, hs, ag, ws, wn, bias, K, N, relu, out, cap_rows, s);
 }
 
-template <int NCH, int J, int R, int SPLIT, int WAVES>
+template <class Op, int NCH, int J, int R, int SPLIT, int WAVES>
 __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVES / 4, WAVES / 4)))
-void k_linear_f32_parts(const int32_t* sizes, parts::LinearOp op) {
-  parts::parts_gemm<parts::LinearOp, NCH, J, R, SPLIT, WAVES>(op, load_size(&sizes[kNDst]));
+void k_linear_f32_parts(const int32_t* sizes, Op op) {
+  parts::parts_gemm<Op, NCH, J, R, SPLIT, WAVES>(op, load_size(&sizes[kNDst]));
 }
 
-template <int NCH, int J, int R, int SPLIT, int WAVES>
-void launch_parts(const int32_t* sizes, const float* hs, const float* ag, const float* ws, const float* wn,
-                  const float* bias, int K, int N, int relu, float* out, int64_t cap_rows, hipStream_t s) {
+template <int NCH, int J, int R, int SPLIT, int WAVES, class Op>
+void launch_parts(const int32_t* sizes, const Op& op, int64_t cap_rows, hipStream_t s) {
   static_assert(parts::parts_lds_bytes(NCH, J, R, SPLIT, WAVES) <= 160 * 1024, "slab exceeds the LDS");
-  const bool quad = N % 4 == 0 && (reinterpret_cast<uintptr_t>(ws) | reinterpret_cast<uintptr_t>(wn)) % 16 == 0;
-  const parts::LinearOp op{hs, ag, ws, wn, bias, K, N, relu, out, quad ? 1 : 0};
-  hipLaunchKernelGGL((k_linear_f32_parts<NCH, J, R, SPLIT, WAVES>), (parts::parts_grid<J, R, SPLIT, WAVES>(cap_rows, N)),
-                     dim3(64 * WAVES), 0, s, sizes, op);
+  hipLaunchKernelGGL((k_linear_f32_parts<Op, NCH, J, R, SPLIT, WAVES>),
+                     (parts::parts_grid<J, R, SPLIT, WAVES>(cap_rows, op.n())), dim3(64 * WAVES), 0, s, sizes, op);
 }
 
 // Tiling of the part-product kernel, from timings of the three layer shapes
@@ -689,23 +692,34 @@ void launch_parts(const int32_t* sizes, const float* hs, const float* ag, const 
 // tiles of 32 columns when there are enough rows, else 16.  Returns false
 // where the fp32 slab kernel is the faster choice (wide K on many rows:
 // the eight-wave tiling would not fit its registers).
-template <int NCH>
-bool launch_parts_for(const int32_t* sizes, const float* hs, const float* ag, const float* ws,
-                      const float* wn, const float* bias, int K, int N, int relu, float* out,
-                      int64_t cap_rows, hipStream_t s) {
+template <int NCH, class Op>
+bool launch_parts_for(const int32_t* sizes, const Op& op, int64_t cap_rows, hipStream_t s) {
+  const int N = op.n();
   const int64_t big_tiles = ((cap_rows + 127) / 128) * ((N + 63) / 64);
   if (big_tiles >= 2 * 256) {
     if constexpr (NCH <= 8) {
-      launch_parts<NCH, 4, 1, 1, 8>(sizes, hs, ag, ws, wn, bias, K, N, relu, out, cap_rows, s);
+      launch_parts<NCH, 4, 1, 1, 8>(sizes, op, cap_rows, s);
       return true;
     }
     return false;
   }
   if (cap_rows * N > (int64_t{1} << 18))
-    launch_parts<NCH, 2, 1, 4, 8>(sizes, hs, ag, ws, wn, bias, K, N, relu, out, cap_rows, s);
+    launch_parts<NCH, 2, 1, 4, 8>(sizes, op, cap_rows, s);
   else
-    launch_parts<NCH, 1, 1, 4, 8>(sizes, hs, ag, ws, wn, bias, K, N, relu, out, cap_rows, s);
+    launch_parts<NCH, 1, 1, 4, 8>(sizes, op, cap_rows, s);
   return true;
+}
+
+template <class Op>
+bool launch_parts_op(const int32_t* sizes, const Op& op, int nch, int64_t cap_rows, hipStream_t s) {
+  if (nch <= 1) return launch_parts_for<1>(sizes, op, cap_rows, s);
+  if (nch <= 2) return launch_parts_for<2>(sizes, op, cap_rows, s);
+  if (nch <= 4) return launch_parts_for<4>(sizes, op, cap_rows, s);
+  if (nch <= 7) return launch_parts_for<7>(sizes, op, cap_rows, s);
+  if (nch <= 8) return launch_parts_for<8>(sizes, op, cap_rows, s);
+  if (nch <= 12) return launch_parts_for<12>(sizes, op, cap_rows, s);
+  if (nch <= 16) return launch_parts_for<16>(sizes, op, cap_rows, s);
+  return false;
 }
 
 // bf16 with the weight slab resident in LDS, on v_mfma_f32_16x16x32_bf16.
@@ -976,14 +990,11 @@ void launch_bf16_slab_for(const int32_t* sizes, const uint16_t* hs, const uint16
 hipError_t launch_mean_aggregate(const int32_t* sizes, const int32_t* indptr, const int32_t* local,
                                  const void* h, int d, int bf16, void* agg, int64_t cap_dst,
                                  int fanout, int64_t max_id, hipStream_t s) {
-  const uintptr_t align = reinterpret_cast<uintptr_t>(h) | reinterpret_cast<uintptr_t>(agg);
   if (bf16) {
-    if (d % 8 == 0 && align % 16 == 0)
-      return mean_dispatch<uint16_t, 8>(sizes, indptr, local, h, d, agg, cap_dst, fanout, max_id, s);
+    if (d >= 8) return mean_dispatch<uint16_t, 8>(sizes, indptr, local, h, d, agg, cap_dst, fanout, max_id, s);
     return mean_dispatch<uint16_t, 1>(sizes, indptr, local, h, d, agg, cap_dst, fanout, max_id, s);
   }
-  if (d % 4 == 0 && align % 16 == 0)
-    return mean_dispatch<float, 4>(sizes, indptr, local, h, d, agg, cap_dst, fanout, max_id, s);
+  if (d >= 4) return mean_dispatch<float, 4>(sizes, indptr, local, h, d, agg, cap_dst, fanout, max_id, s);
   return mean_dispatch<float, 1>(sizes, indptr, local, h, d, agg, cap_dst, fanout, max_id, s);
 }
 
@@ -1024,22 +1035,18 @@ hipError_t launch_sage_linear(const int32_t* sizes, const void* h_self, const vo
     const uintptr_t align = reinterpret_cast<uintptr_t>(hs) | reinterpret_cast<uintptr_t>(ag);
     const int nch = (2 * d_in + 15) / 16;
     const int nch32 = (2 * d_in + 31) / 32;
-    if (d_in % 4 == 0 && align % 16 == 0 && nch32 <= 16) {
-      float* o = static_cast<float*>(out);
-      bool done;
-#define GMB_PARTS(C) done = launch_parts_for<C>(sizes, hs, ag, ws, wn, bias, d_in, d_out, relu, o, cap_rows, s)
-      if (nch32 <= 1) GMB_PARTS(1);
-      else if (nch32 <= 2) GMB_PARTS(2);
-      else if (nch32 <= 4) GMB_PARTS(4);
-      else if (nch32 <= 7) GMB_PARTS(7);
-      else if (nch32 <= 8) GMB_PARTS(8);
-      else if (nch32 <= 12) GMB_PARTS(12);
-      else GMB_PARTS(16);
-#undef GMB_PARTS
-      if (done) return hipGetLastError();
+    float* o = static_cast<float*>(out);
+    const bool quad = d_out % 4 == 0 && (reinterpret_cast<uintptr_t>(ws) | reinterpret_cast<uintptr_t>(wn)) % 16 == 0;
+    // d_in % 4 == 0 runs h_v and the mean together as 2 d_in of k; other
+    // widths pad each to a multiple of eight
+    if (d_in % 4 == 0 && align % 16 == 0) {
+      const parts::LinearOp op{hs, ag, ws, wn, bias, d_in, d_out, relu, o, quad ? 1 : 0};
+      if (launch_parts_op(sizes, op, nch32, cap_rows, s)) return hipGetLastError();
+    } else if (d_in >= 8) {
+      const parts::LinearAnyOp op{hs, ag, ws, wn, bias, d_in, (d_in + 7) / 8, d_out, relu, o, quad ? 1 : 0};
+      if (launch_parts_op(sizes, op, (2 * op.gh + 3) / 4, cap_rows, s)) return hipGetLastError();
     }
     if (d_in % 4 == 0 && align % 16 == 0 && nch <= 40) {
-      float* o = static_cast<float*>(out);
 #define GMB_SLAB(C) launch_slab_for<C>(sizes, hs, ag, ws, wn, bias, d_in, d_out, relu, o, cap_rows, s)
       if (nch <= 2) GMB_SLAB(2);
       else if (nch <= 4) GMB_SLAB(4);
