@@ -747,10 +747,10 @@ struct BackwardPlan {
   int64_t scan_len;                            // ints of one layer's scan state
   int64_t clear_len;                           // ints cleared at the start (counters + scan states)
   size_t total;
-  // bf16 models: fp32 copies of what the backward reads (the forward
-  // workspace laid out for fp32, block 0's destination rows of x, the
-  // matrices), after the fp32 backward's own workspace
-  size_t off_shadow, off_x32, off_w32[GMB_MAX_LAYERS][2];
+  // bf16 models: fp32 copies of what the upper layers' products read (in a
+  // forward workspace laid out for fp32; their matrices), after the fp32
+  // backward's own workspace
+  size_t off_shadow, off_w32[GMB_MAX_LAYERS][2];
   size_t fp32_total;
 };
 
@@ -760,11 +760,12 @@ struct BackwardPlan {
 int plan_backward_f32(const gmb_blocks* b, const gmb_sage_weights* w, BackwardPlan* plan, bool embed);
 
 // The fp32 weights struct of a bf16 model's training step: the same dims
-// and biases, the matrices at the fp32 copies of the plan in `ws`.
+// and biases, the upper layers' matrices at the fp32 copies of the plan in
+// `ws`.
 gmb_sage_weights widened_weights(const gmb_sage_weights* w, const BackwardPlan& p, char* ws) {
   gmb_sage_weights w32 = *w;
   w32.dtype = GMB_F32;
-  for (int l = 0; l < w->num_layers; ++l) {
+  for (int l = 1; l < w->num_layers; ++l) {   // (layer 0 has no input gradient: its matrices are not read)
     w32.w_self[l] = ws + p.off_w32[l][0];
     w32.w_neigh[l] = ws + p.off_w32[l][1];
   }
@@ -787,9 +788,7 @@ int plan_backward(const gmb_blocks* b, const gmb_sage_weights* w, BackwardPlan* 
   p.fp32_total = p.total;
   p.off_shadow = off;
   off = align_up(off + fp32.total);
-  p.off_x32 = off;
-  off = align_up(off + 4 * static_cast<size_t>(std::max<int64_t>(b->blk[0].cap_dst, 1)) * w->dims[0]);
-  for (int l = 0; l < w->num_layers; ++l)
+  for (int l = 1; l < w->num_layers; ++l)
     for (int k = 0; k < 2; ++k) {
       p.off_w32[l][k] = off;
       off = align_up(off + 4 * static_cast<size_t>(w->dims[l]) * w->dims[l + 1]);
@@ -872,12 +871,20 @@ int check_grads(const gmb_sage_grads* g, const gmb_sage_weights* w) {
 // products take the part-product kernel of their own launch).
 constexpr int64_t kFoldScanSources = 262144;
 
+// What the fp32 backward of a bf16 model reads in bf16: layer 0's input and
+// mean, and the hidden outputs as the ReLU masks.
+struct Bf16Sources {
+  const void* x;
+  const void* mean;
+  const void* hidden[GMB_MAX_LAYERS];
+};
+
 // The backward from the loss down; with table != NULL layer 0's input
 // gradient is applied to the embedding rows of block 0's sources.
 int run_backward(const gmb_blocks* blocks, const void* x, const gmb_sage_weights* weights, const float* logits,
                  const int32_t* labels, const void* fwd_ws, size_t fwd_ws_bytes, const gmb_sage_grads* grads,
                  float* loss, void* ws, size_t ws_bytes, float* table, int64_t num_nodes, float emb_lr,
-                 void* stream) {
+                 void* stream, const Bf16Sources* lo = nullptr) {
   const bool embed = table != nullptr;
   BackwardPlan p;
   int st = plan_backward(blocks, weights, &p, embed);
@@ -894,9 +901,11 @@ int run_backward(const gmb_blocks* blocks, const void* x, const gmb_sage_weights
   const hipStream_t s = as_stream(stream);
   const int L = weights->num_layers;
   if (weights->dtype == GMB_BF16 && blocks->num_seeds > 0) {
-    // a bf16 model: widen what the backward reads to fp32 (block 0's
-    // destination rows of x, every layer's mean and hidden output in the
-    // fp32 layout, the matrices), then the fp32 backward on the copies
+    // a bf16 model: layer 0's weight gradient and the ReLU masks read x, the
+    // mean and the hidden outputs as they are; what the upper layers' products
+    // read (their destination rows, a tenth of the rows, and their matrices)
+    // is widened to fp32, in the fp32 layout.  (Widening all of it took 18 us
+    // of a hubs2m iteration, this 5.7 us.)
     if (!x) return fail(GMB_EINVAL, "x is NULL");
     char* base = static_cast<char*>(ws);
     const gmb_sage_weights w32 = widened_weights(weights, p, base);
@@ -911,22 +920,24 @@ int run_backward(const gmb_blocks* blocks, const void* x, const gmb_sage_weights
       wa.cap_rows[wa.count] = cap_rows;
       wa.cols[wa.count++] = cols;
     };
-    const gmb_block& b0 = blocks->blk[0];
-    add(x, base + p.off_x32, b0.sizes + gmb::kNDst, std::max<int64_t>(b0.cap_dst, 1), weights->dims[0]);
-    for (int l = 0; l < L; ++l) {
+    Bf16Sources lo{};
+    lo.x = x;
+    lo.mean = fsrc + fp.off_agg[0];
+    for (int l = 1; l < L; ++l) {
       const gmb_block& bk = blocks->blk[l];
-      add(fsrc + fp.off_agg[l], base + p.off_shadow + f32.off_agg[l], bk.sizes + gmb::kNDst,
-          std::max<int64_t>(bk.cap_dst, 1), weights->dims[l]);
-      if (l + 1 < L)
-        add(fsrc + fp.off_hidden[l], base + p.off_shadow + f32.off_hidden[l], bk.sizes + gmb::kNDst,
-            std::max<int64_t>(bk.cap_dst, 1), weights->dims[l + 1]);
+      const int64_t rows = std::max<int64_t>(bk.cap_dst, 1);
+      lo.hidden[l - 1] = fsrc + fp.off_hidden[l - 1];
+      add(fsrc + fp.off_agg[l], base + p.off_shadow + f32.off_agg[l], bk.sizes + gmb::kNDst, rows, weights->dims[l]);
+      add(lo.hidden[l - 1], base + p.off_shadow + f32.off_hidden[l - 1], bk.sizes + gmb::kNDst, rows, weights->dims[l]);
       add(weights->w_self[l], base + p.off_w32[l][0], nullptr, weights->dims[l], weights->dims[l + 1]);
       add(weights->w_neigh[l], base + p.off_w32[l][1], nullptr, weights->dims[l], weights->dims[l + 1]);
     }
-    hipError_t e = gmb::launch_widen(wa, s);
-    if (e != hipSuccess) return hip_fail(e, "widen launch");
-    return run_backward(blocks, base + p.off_x32, &w32, logits, labels, base + p.off_shadow, f32.total, grads, loss,
-                        ws, p.fp32_total, nullptr, 0, 0.f, stream);
+    if (wa.count > 0) {
+      hipError_t e = gmb::launch_widen(wa, s);
+      if (e != hipSuccess) return hip_fail(e, "widen launch");
+    }
+    return run_backward(blocks, x, &w32, logits, labels, base + p.off_shadow, f32.total, grads, loss, ws, p.fp32_total,
+                        nullptr, 0, 0.f, stream, &lo);
   }
   if (blocks->num_seeds == 0) {
     // an empty batch: the mean over no seeds is taken as 0, so are the
@@ -978,7 +989,8 @@ int run_backward(const gmb_blocks* blocks, const void* x, const gmb_sage_weights
     const bool beside_scan = below && bk.cap_src <= kFoldScanSources;
     gmb::WgradArgs defer{};
     gmb::ReduceArgs fold{};
-    e = gmb::launch_wgrad(bk.sizes, h_in, m, d_in, cur, p.ldz[l], d_out, std::max<int64_t>(bk.cap_dst, 1), part,
+    const bool first_lo = lo && l == 0;
+    e = gmb::launch_wgrad(bk.sizes, first_lo ? lo->x : h_in, first_lo ? lo->mean : m, first_lo ? 1 : 0, d_in, cur, p.ldz[l], d_out, std::max<int64_t>(bk.cap_dst, 1), part,
                           grads->d_self[l], grads->d_neigh[l], grads->d_bias[l], top ? loss_rows : nullptr,
                           blocks->num_seeds, top ? loss : nullptr, beside_scan ? &defer : nullptr,
                           below ? &fold : nullptr, s);
@@ -994,8 +1006,8 @@ int run_backward(const gmb_blocks* blocks, const void* x, const gmb_sage_weights
     // layer below on the way out: `other` becomes that layer's dZ; on layer
     // 0 (learnable embeddings) the input gradient goes into the table rows
     uint32_t* scan_state = reinterpret_cast<uint32_t*>(cnt + p.cnt_len + (embed ? l : l - 1) * p.scan_len);
-    e = gmb::launch_mean_backward(bk.sizes, bk.indptr, bk.indices, bk.cap_nnz, bk.fanout, dM,
-                                  l == 0 ? nullptr : h_in, d_in, other, bk.cap_dst, bk.cap_src, cnt, offs, pos,
+    const void* mask = l == 0 ? nullptr : (lo ? lo->hidden[l - 1] : static_cast<const void*>(h_in));
+    e = gmb::launch_mean_backward(bk.sizes, bk.indptr, bk.indices, bk.cap_nnz, bk.fanout, dM, mask, lo ? 1 : 0, d_in, other, bk.cap_dst, bk.cap_src, cnt, offs, pos,
                                   scan_state, csc, long_rows, l == 0 ? table : nullptr, bk.src_ids, num_nodes,
                                   emb_lr, beside_scan ? &defer : nullptr, &fold, s);
     if (e != hipSuccess) return hip_fail(e, "mean-backward launch");

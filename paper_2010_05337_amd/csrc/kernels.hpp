@@ -290,8 +290,9 @@ struct WgradArgs {
 // `defer` and `fold` when given, describes them instead, for later launches
 // to run as extra workgroups of their grids (launch_mean_backward: the
 // products beside the transpose scan, the reduction beside the fill).
-hipError_t launch_wgrad(const int32_t* sizes, const float* H, const float* M, int d_in, const float* dZ, int ldz,
-                        int d_out, int64_t cap_rows, float* partial, float* d_self, float* d_neigh,
+// bf16: H and M are bf16 (not with `defer`).
+hipError_t launch_wgrad(const int32_t* sizes, const void* H, const void* M, int bf16, int d_in, const float* dZ,
+                        int ldz, int d_out, int64_t cap_rows, float* partial, float* d_self, float* d_neigh,
                         float* d_bias, const float* loss_rows, int n_loss, float* loss, WgradArgs* defer,
                         ReduceArgs* fold, hipStream_t s);
 hipError_t launch_dgrad(const int32_t* sizes, const float* dZ, int ldz, int d_out, const float* ws,
@@ -307,8 +308,8 @@ int64_t csc_scan_tiles(int64_t cap_src);
 // With `defer` (from launch_wgrad) the transpose scan's grid also runs the
 // weight gradient's products, with `fold` the fill's grid its reduction.
 hipError_t launch_mean_backward(const int32_t* sizes, const int32_t* indptr, const int32_t* local,
-                                int64_t cap_nnz, int32_t fanout, const float* dM, const float* out, int d, float* dH,
-                                int64_t cap_dst, int64_t cap_src, int32_t* cnt, int32_t* off, int32_t* pos,
+                                int64_t cap_nnz, int32_t fanout, const float* dM, const void* out, int out_bf16, int d,
+                                float* dH, int64_t cap_dst, int64_t cap_src, int32_t* cnt, int32_t* off, int32_t* pos,
                                 uint32_t* scan_state, int2* csc, int32_t* long_rows, float* table, const int32_t* ids,
                                 int64_t num_nodes, float lr, const WgradArgs* defer, const ReduceArgs* fold,
                                 hipStream_t s);

@@ -312,11 +312,17 @@ __device__ __forceinline__ void wgrad_block(const int32_t* __restrict__ sizes, c
 constexpr int kWgradPartsDepth = GMB_WGRAD_PARTS_DEPTH;   // chunks in flight per wave
 constexpr int kWgradPartsWaves = GMB_WGRAD_PARTS_WAVES;   // waves per workgroup, two per SIMD at 8
 
+// TX = uint16_t: H and M are bf16 (layer 0 of a bf16 model).  Their values are
+// their own first parts and the other two are zero, so three part products
+// of the six remain and X is not cut; the sums are the same bit for bit as on
+// fp32 copies.
+template <typename TX>
 __global__ __launch_bounds__(64 * kWgradPartsWaves)
 __attribute__((amdgpu_waves_per_eu(kWgradPartsWaves / 4, kWgradPartsWaves / 4)))
-void k_wgrad_parts(const int32_t* __restrict__ sizes, const float* __restrict__ H, const float* __restrict__ M,
+void k_wgrad_parts(const int32_t* __restrict__ sizes, const TX* __restrict__ H, const TX* __restrict__ M,
                    int d_in, const float* __restrict__ dZ, int ldz, int ldp, float* __restrict__ partial) {
   using parts::bf16x8;
+  constexpr bool kLo = sizeof(TX) == 2;
   constexpr int W = kWgradPartsWaves;
   constexpr int kPad = 68;   // LDS row stride of the waves' tiles
   __shared__ __attribute__((aligned(16))) float red[W][64 * kPad];
@@ -331,12 +337,12 @@ void k_wgrad_parts(const int32_t* __restrict__ sizes, const float* __restrict__ 
   const int zc = from_m ? bz - TI : bz;
   const char* X = reinterpret_cast<const char*>(from_m ? M : H);   // uniform per workgroup
   const char* Zb = reinterpret_cast<const char*>(dZ);
-  const uint32_t xrow = static_cast<uint32_t>(d_in) * 4u, zrow = static_cast<uint32_t>(ldz) * 4u;
+  const uint32_t xrow = static_cast<uint32_t>(d_in * sizeof(TX)), zrow = static_cast<uint32_t>(ldz) * 4u;
   uint32_t xo[4], zo[4];
 #pragma unroll
   for (int b = 0; b < 4; ++b) {
     const int c = zc * 64 + 16 * b + li, o = by * 64 + 16 * b + li;
-    xo[b] = static_cast<uint32_t>(c < d_in ? c : 0) * 4u;
+    xo[b] = static_cast<uint32_t>((c < d_in ? c : 0) * sizeof(TX));
     zo[b] = static_cast<uint32_t>(o < ldz ? o : 0) * 4u;
   }
   const int gx = gridDim.x;
@@ -350,7 +356,7 @@ void k_wgrad_parts(const int32_t* __restrict__ sizes, const float* __restrict__ 
     for (int b = 0; b < 4; ++b) acc[a][b] = floatx4{0.f, 0.f, 0.f, 0.f};
   float dbs[4] = {0.f, 0.f, 0.f, 0.f};
 
-  auto load = [&](int k0, float (&xa)[4][8], float (&zb)[4][8]) {
+  auto load = [&](int k0, TX (&xa)[4][8], float (&zb)[4][8]) {
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
       const int row = k0 + 8 * g + e;
@@ -358,12 +364,12 @@ void k_wgrad_parts(const int32_t* __restrict__ sizes, const float* __restrict__ 
       const uint32_t xr = rc * xrow, zr = rc * zrow;
 #pragma unroll
       for (int b = 0; b < 4; ++b) {
-        xa[b][e] = *reinterpret_cast<const float*>(X + (xr + xo[b]));
+        xa[b][e] = *reinterpret_cast<const TX*>(X + (xr + xo[b]));
         zb[b][e] = *reinterpret_cast<const float*>(Zb + (zr + zo[b]));
       }
     }
   };
-  auto compute = [&](int k0, float (&xa)[4][8], float (&zb)[4][8]) {
+  auto compute = [&](int k0, TX (&xa)[4][8], float (&zb)[4][8]) {
     if (k0 + 32 > r1) {   // uniform: the range's last chunk of this wave
 #pragma unroll
       for (int e = 0; e < 8; ++e)
@@ -385,6 +391,18 @@ void k_wgrad_parts(const int32_t* __restrict__ sizes, const float* __restrict__ 
                     make_float4(zb[b][4], zb[b][5], zb[b][6], zb[b][7]), bp[b]);
 #pragma unroll
     for (int a = 0; a < 4; ++a) {
+      if constexpr (kLo) {
+        uint32_t w[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          w[i] = static_cast<uint32_t>(xa[a][2 * i]) | (static_cast<uint32_t>(xa[a][2 * i + 1]) << 16);
+        const bf16x8 x = __builtin_bit_cast(bf16x8, make_uint4(w[0], w[1], w[2], w[3]));
+#pragma unroll
+        for (int t = 2; t >= 0; --t)
+#pragma unroll
+          for (int b = 0; b < 4; ++b) acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x, bp[b][t], acc[a][b], 0, 0, 0);
+        continue;
+      }
       bf16x8 ap[3];
       parts::split8(make_float4(xa[a][0], xa[a][1], xa[a][2], xa[a][3]),
                     make_float4(xa[a][4], xa[a][5], xa[a][6], xa[a][7]), ap);
@@ -410,7 +428,8 @@ void k_wgrad_parts(const int32_t* __restrict__ sizes, const float* __restrict__ 
   constexpr int D = kWgradPartsDepth, STRIDE = 32 * W;
   int k0 = r0 + 32 * wave;
   const int nsteps = __builtin_amdgcn_readfirstlane(k0 < r1 ? (r1 - k0 + STRIDE - 1) / STRIDE : 0);
-  float xs[D][4][8], zs[D][4][8];
+  TX xs[D][4][8];
+  float zs[D][4][8];
   if (nsteps > 0) {
 #pragma unroll
     for (int b = 0; b + 1 < D; ++b) load(k0 + STRIDE * b, xs[b], zs[b]);
@@ -927,6 +946,15 @@ __global__ __launch_bounds__(256) void k_csc_fill(const int32_t* __restrict__ si
                      });
 }
 
+// Four values of the layer below's output (fp32, or a bf16 model's bf16; the
+// width is a multiple of 4).
+__device__ __forceinline__ float4 load_out4(const float* p) { return *reinterpret_cast<const float4*>(p); }
+__device__ __forceinline__ float4 load_out4(const uint16_t* p) {
+  const uint2 x = *reinterpret_cast<const uint2*>(p);
+  return make_float4(__uint_as_float(x.x << 16), __uint_as_float(x.x & 0xFFFF0000u), __uint_as_float(x.y << 16),
+                     __uint_as_float(x.y & 0xFFFF0000u));
+}
+
 // The sources with long transpose lists, one workgroup per row (the n_wg
 // workgroups that the row kernels append to their grids stride over the
 // list; wg is this one's index among them): the eight 32-lane groups take the entries
@@ -935,11 +963,11 @@ __global__ __launch_bounds__(256) void k_csc_fill(const int32_t* __restrict__ si
 // sums meet in LDS in a fixed order, then the row is finished as in
 // k_pull_mean (UPDATE = false: masked by the layer below's output, written
 // to dH) or k_pull_update (UPDATE = true: applied to the table row).
-template <bool UPDATE>
+template <bool UPDATE, typename TO>
 __device__ void pull_long_rows(int wg, int n_wg, const int32_t* __restrict__ sizes,
                                const uint32_t* __restrict__ n_long, const int32_t* __restrict__ long_rows,
                                const int32_t* __restrict__ off, const int2* __restrict__ csc, int64_t cap_nnz,
-                               const float* __restrict__ dM, const float* __restrict__ out, int d,
+                               const float* __restrict__ dM, const TO* __restrict__ out, int d,
                                float* __restrict__ dH, float* __restrict__ table, const int32_t* __restrict__ ids,
                                int64_t num_nodes, float lr) {
   constexpr int kGroups = 8, E = 4;
@@ -1008,7 +1036,7 @@ __device__ void pull_long_rows(int wg, int n_wg, const int32_t* __restrict__ siz
               *t = v;
             }
           } else {
-            const float4 o = *reinterpret_cast<const float4*>(out + at);
+            const float4 o = load_out4(out + at);
             acc.x = o.x > 0.f ? acc.x : 0.f;
             acc.y = o.y > 0.f ? acc.y : 0.f;
             acc.z = o.z > 0.f ? acc.z : 0.f;
@@ -1030,15 +1058,15 @@ __device__ void pull_long_rows(int wg, int n_wg, const int32_t* __restrict__ siz
 // of one mini-batch are distinct; mini-batches in flight together update
 // without locks, as Hogwild does); an id outside [0, num_nodes) skips the
 // row (only after a data error).
-template <int G>
+template <int G, typename TO>
 __global__ __launch_bounds__(256) void k_pull_mean(const int32_t* __restrict__ sizes,
                                                    const int32_t* __restrict__ off, const int2* __restrict__ csc,
                                                    int64_t cap_nnz, const float* __restrict__ dM,
-                                                   const float* __restrict__ out, int d, float* __restrict__ dH,
+                                                   const TO* __restrict__ out, int d, float* __restrict__ dH,
                                                    int row_blocks, const uint32_t* __restrict__ n_long,
                                                    const int32_t* __restrict__ long_rows) {
   if (static_cast<int>(blockIdx.x) >= row_blocks) {   // the long lists
-    pull_long_rows<false>(blockIdx.x - row_blocks, gridDim.x - row_blocks, sizes, n_long, long_rows, off, csc,
+    pull_long_rows<false, TO>(blockIdx.x - row_blocks, gridDim.x - row_blocks, sizes, n_long, long_rows, off, csc,
                           cap_nnz, dM, out, d, dH, nullptr, nullptr, 0, 0.f);
     return;
   }
@@ -1056,7 +1084,7 @@ __global__ __launch_bounds__(256) void k_pull_mean(const int32_t* __restrict__ s
   for (int c = lane; c < chunks; c += G) {
     const int64_t at = u * d + 4 * c;
     // the layer below's output does not depend on the gradient: read first
-    const float4 o = *reinterpret_cast<const float4*>(out + at);
+    const float4 o = load_out4(out + at);
     float4 acc = self ? *reinterpret_cast<const float4*>(dH + at) : make_float4(0.f, 0.f, 0.f, 0.f);
     // four entries per round of reads (the sum still runs in entry order)
     for (int32_t s = s0; s < s1; s += 4) {
@@ -1108,7 +1136,7 @@ __global__ __launch_bounds__(256) void k_pull_update(const int32_t* __restrict__
                                                      int row_blocks, const uint32_t* __restrict__ n_long,
                                                      const int32_t* __restrict__ long_rows) {
   if (static_cast<int>(blockIdx.x) >= row_blocks) {   // the long lists
-    pull_long_rows<true>(blockIdx.x - row_blocks, gridDim.x - row_blocks, sizes, n_long, long_rows, off, csc,
+    pull_long_rows<true, float>(blockIdx.x - row_blocks, gridDim.x - row_blocks, sizes, n_long, long_rows, off, csc,
                          cap_nnz, dM, nullptr, d, dH, table, ids, num_nodes, lr);
     return;
   }
@@ -1305,10 +1333,13 @@ int wgrad_parts(int64_t cap_rows, int d_in, int d_out) {
   return parts < 1 ? 1 : parts;
 }
 
-hipError_t launch_wgrad(const int32_t* sizes, const float* H, const float* M, int d_in, const float* dZ, int ldz,
-                        int d_out, int64_t cap_rows, float* partial, float* d_self, float* d_neigh,
+hipError_t launch_wgrad(const int32_t* sizes, const void* Hv, const void* Mv, int bf16, int d_in, const float* dZ,
+                        int ldz, int d_out, int64_t cap_rows, float* partial, float* d_self, float* d_neigh,
                         float* d_bias, const float* loss_rows, int n_loss, float* loss, WgradArgs* defer,
                         ReduceArgs* fold, hipStream_t s) {
+  if (bf16 && defer) return hipErrorInvalidValue;
+  const float* H = static_cast<const float*>(Hv);
+  const float* M = static_cast<const float*>(Mv);
   const int parts = wgrad_parts(cap_rows, d_in, d_out);
   const int ldp = wgrad_ldp(d_out);
   const dim3 grid(parts, (ldp + 63) / 64, 2 * ((d_in + 63) / 64));
@@ -1322,8 +1353,11 @@ hipError_t launch_wgrad(const int32_t* sizes, const float* H, const float* M, in
   if (defer) {
     *defer = WgradArgs{sizes, H, M, d_in, dZ, ldz, ldp, partial, parts, static_cast<int>(grid.y),
                        static_cast<int>(grid.z), vec ? 1 : 0};
+  } else if (bf16) {
+    hipLaunchKernelGGL(k_wgrad_parts<uint16_t>, grid, dim3(64 * kWgradPartsWaves), 0, s, sizes,
+                       static_cast<const uint16_t*>(Hv), static_cast<const uint16_t*>(Mv), d_in, dZ, ldz, ldp, partial);
   } else {
-    hipLaunchKernelGGL(k_wgrad_parts, grid, dim3(64 * kWgradPartsWaves), 0, s, sizes, H, M, d_in, dZ, ldz, ldp,
+    hipLaunchKernelGGL(k_wgrad_parts<float>, grid, dim3(64 * kWgradPartsWaves), 0, s, sizes, H, M, d_in, dZ, ldz, ldp,
                        partial);
   }
   if (fold)
@@ -1386,8 +1420,8 @@ int64_t csc_scan_tiles(int64_t cap_src) { return std::max<int64_t>(1, (cap_src +
 constexpr int kLongGrid = 512;   // workgroups appended for the long lists (grid-stride over them)
 
 hipError_t launch_mean_backward(const int32_t* sizes, const int32_t* indptr, const int32_t* local,
-                                int64_t cap_nnz, int32_t fanout, const float* dM, const float* out, int d, float* dH,
-                                int64_t cap_dst, int64_t cap_src, int32_t* cnt, int32_t* off, int32_t* pos,
+                                int64_t cap_nnz, int32_t fanout, const float* dM, const void* out, int out_bf16, int d,
+                                float* dH, int64_t cap_dst, int64_t cap_src, int32_t* cnt, int32_t* off, int32_t* pos,
                                 uint32_t* scan_state, int2* csc, int32_t* long_rows, float* table, const int32_t* ids,
                                 int64_t num_nodes, float lr, const WgradArgs* defer, const ReduceArgs* fold,
                                 hipStream_t s) {
@@ -1430,9 +1464,11 @@ hipError_t launch_mean_backward(const int32_t* sizes, const int32_t* indptr, con
   else if (chunks <= 16) G = 16;
   else if (chunks <= 32) G = 32;
   const unsigned rows = grid_of(std::max<int64_t>(cap_src, 1) * G, 1 << 30);
-#define GMB_PULL(GG)                                                                                     \
-  hipLaunchKernelGGL((k_pull_mean<GG>), dim3(rows + kLongGrid), dim3(256), 0, s, sizes, off, csc, cap_nnz, dM, \
-                     out, d, dH, static_cast<int>(rows), n_long, long_rows)
+#define GMB_PULL_T(GG, T)                                                                                      \
+  hipLaunchKernelGGL((k_pull_mean<GG, T>), dim3(rows + kLongGrid), dim3(256), 0, s, sizes, off, csc, cap_nnz, dM, \
+                     static_cast<const T*>(out), d, dH, static_cast<int>(rows), n_long, long_rows)
+#define GMB_PULL(GG) \
+  if (out_bf16) GMB_PULL_T(GG, uint16_t); else GMB_PULL_T(GG, float)
   switch (G) {
     case 4: GMB_PULL(4); break;
     case 8: GMB_PULL(8); break;
@@ -1441,6 +1477,7 @@ hipError_t launch_mean_backward(const int32_t* sizes, const int32_t* indptr, con
     default: GMB_PULL(64); break;
   }
 #undef GMB_PULL
+#undef GMB_PULL_T
   return hipGetLastError();
 }
 

@@ -60,7 +60,7 @@ hipError_t launch_xent(const float*, const int32_t*, int, int, int, float*, floa
 }
 int wgrad_ldp(int d_out) { return (d_out + 3) / 4 * 4; }
 int wgrad_parts(int64_t cap_rows, int, int) { return static_cast<int>(std::min<int64_t>(8, std::max<int64_t>(1, cap_rows / 64))); }
-hipError_t launch_wgrad(const int32_t*, const float*, const float*, int, const float*, int, int, int64_t, float*,
+hipError_t launch_wgrad(const int32_t*, const void*, const void*, int, int, const float*, int, int, int64_t, float*,
                         float*, float*, float*, const float*, int, float*, WgradArgs*, ReduceArgs*, hipStream_t) {
   return hipSuccess;
 }
@@ -70,7 +70,7 @@ hipError_t launch_dgrad(const int32_t*, const float*, int, int, const float*, co
 }
 int64_t csc_scan_tiles(int64_t cap_src) { return std::max<int64_t>(1, (cap_src + 1023) / 1024); }
 hipError_t launch_mean_backward(const int32_t*, const int32_t*, const int32_t*, int64_t, int32_t, const float*,
-                                const float*, int, float*, int64_t, int64_t, int32_t*, int32_t*, int32_t*, uint32_t*,
+                                const void*, int, int, float*, int64_t, int64_t, int32_t*, int32_t*, int32_t*, uint32_t*,
                                 int2*, int32_t*, float*, const int32_t*, int64_t, float, const WgradArgs*,
                                 const ReduceArgs*, hipStream_t) {
   return hipSuccess;

@@ -96,3 +96,61 @@ def test_rows_of_any_width(orc, dg, graph, dtype, d):
     assert torch.equal(fused, logits)
     assert torch.equal(x_dst[:1001].view(bits), want.view(bits))
     csr.check_status()
+
+
+@pytest.mark.parametrize("dims, rows", [([9, 5], 70), ([75, 41], 700), ([130, 47], 2000), ([1, 4], 33),
+                                        ([37, 16, 9], 129), ([128, 64, 10], 64)])
+def test_bf16_weight_gradient_widths(orc, dg, graph, dims, rows):
+    """Layer 0's weight gradient read from bf16 inputs and means, at widths
+    that four does not divide: the last layer's gradients (a one-layer model:
+    all of them, no ReLU in between) against the oracle's fp64 step within the
+    bf16 training tests' 2e-2; lower layers against the same backward run in
+    fp32 on the same values, where only the order of the transpose's sums may
+    differ (1e-4, the fp32 training tests' bound)."""
+    import ctypes
+    print(f"bf16 training widths {dims}, {rows} rows", flush=True)
+    fanouts = [4] * (len(dims) - 1)
+    feats = dg.features(graph.num_nodes, dims[0], 5, "bf16")
+    w = dg.sage_weights(dims, 6, "bf16")
+    seeds = dg.permutation(graph.num_nodes, 7)[:rows]
+    labels = dg.labels(graph.num_nodes, dims[-1], 9)[seeds]
+    y = torch.from_numpy(labels).cuda()
+    csr = csr_on_device(graph)
+    wt = to_torch_weights(w)
+    blocks = gmb.sample_blocks(csr, torch.from_numpy(seeds).cuda(), fanouts, 8)
+    x = gmb.gather_features(blocks, to_torch_feats(feats))
+    ws = gmb._aligned_bytes(gmb.forward_workspace_bytes(blocks, wt), x.device)[1]
+    logits = gmb.sage_forward(blocks, x, wt, workspace=ws)
+    grads, loss = gmb.sage_backward(blocks, x, wt, logits, y, ws)
+    ref = orc.sample_blocks(graph.indptr, graph.indices, seeds, fanouts, 8)
+    X = orc.widen(orc.gather(feats, ref[0].src), w.dtype)
+    _, _, (dws, dwn, dbs), _ = orc.sage_train_step(ref, X, *w.as_f64(), labels, 0.1)
+    for got, want in ((grads.d_self, dws), (grads.d_neigh, dwn), (grads.d_bias, dbs)):
+        err = np.abs(got[-1].cpu().numpy() - want[-1]).max() / np.abs(want[-1]).max()
+        assert err <= 2e-2, err
+    # the same values in fp32: x, the weights, and the forward workspace with
+    # its means and hidden outputs widened
+    w32 = wt.master()
+    ws32 = gmb._aligned_bytes(gmb.forward_workspace_bytes(blocks, w32), x.device)[1]
+    gmb.sage_forward(blocks, x.float(), w32, workspace=ws32)
+    sizes = blocks.sizes()
+
+    def copy(dst_off, src_off, rows_, cols):
+        src = ws[src_off:src_off + 2 * rows_ * cols].view(torch.bfloat16)
+        ws32[dst_off:dst_off + 4 * rows_ * cols].view(torch.float32).copy_(src.float())
+
+    at16 = at32 = 0
+    for l in range(len(dims) - 1):   # the means come first, one per layer, 256-byte aligned
+        cap = int(blocks.struct.blk[l].cap_dst)
+        copy(at32, at16, sizes[l][0], dims[l])
+        at16 += (2 * cap * dims[l] + 255) // 256 * 256
+        at32 += (4 * cap * dims[l] + 255) // 256 * 256
+    for l in range(len(dims) - 2):
+        off16 = gmb.lib().gmb_forward_hidden_offset(ctypes.byref(blocks.struct), ctypes.byref(wt.struct), l)
+        off32 = gmb.lib().gmb_forward_hidden_offset(ctypes.byref(blocks.struct), ctypes.byref(w32.struct), l)
+        copy(off32, off16, sizes[l][0], dims[l + 1])
+    grads32, _ = gmb.sage_backward(blocks, x.float(), w32, logits, y, ws32)
+    for got, want in ((grads.d_self, grads32.d_self), (grads.d_neigh, grads32.d_neigh), (grads.d_bias, grads32.d_bias)):
+        for a, b in zip(got, want):
+            assert float((a - b).abs().max()) <= 1e-4 * float(b.abs().max())
+    csr.check_status()
