@@ -878,20 +878,27 @@ __global__ __launch_bounds__(kRouteBlock) void k_route(RouteArgs a) {
 
 // Sampling and routing in one kernel, for fan-outs up to 64 (G lanes per
 // destination as in k_sample_table): router w loads its share of the
-// destinations (id, block row offset, CSR row) into LDS with two rounds of
-// independent reads (the previous hop's deferred local ids ride along),
-// samples them in rounds of kRouteBlock / G destinations (all rounds' draws
-// first, then all their neighbour reads in one batch), writes the sampled
-// ids and keeps them in LDS, and routes them with the destinations as
-// k_route does.
-constexpr int kSampleRounds = 8;   // span * G < 2 * (edges per tile) <= 8192 lanes
+// destinations (id, block row offset, CSR row; one per thread) into LDS with
+// two rounds of independent reads (the previous hop's deferred local ids ride
+// along), samples them in rounds of kRouteBlock / G destinations, each sampled
+// edge's CSR slot going to the edge's place in LDS, then reads all neighbours
+// in one batch, edge i by thread i mod kRouteBlock (coalesced stores), and
+// routes them and the destinations from its registers as k_route does.
+// What bounds it (256 routers of 153 destinations, fan-out 15: 16 us): the
+// draws' VALU work, 6 us (Philox's twenty 32 x 32 products at quarter rate and
+// floyd_resolve), launch and first reads 3.5, neighbour reads 1.2, the owner
+// histogram 2.8, the pairs' stores 2.5.  The rounds are a loop of one body;
+// unrolled, with the slots in registers, the kernel was 25 KB of code (with
+// k_owner's change below sample_blocks 71.4 -> 69.1 us).
+constexpr int kTileEdges = kScanBlock * 16;             // most edges of a router
+constexpr int kEdgeItems = kTileEdges / kRouteBlock;    // most edges per thread
 template <int G, bool WIDE>
 __global__ __launch_bounds__(kRouteBlock) void k_sample_route(CsrArgs ga, SampleArgs a, RouteArgs ra) {
   __shared__ int32_t s_v[kMaxSpan];
   __shared__ int32_t s_off[kMaxSpan + 1];
   __shared__ int32_t s_deg[kMaxSpan];
   __shared__ int64_t s_beg[kMaxSpan];
-  __shared__ int32_t s_key[kMaxRouteEntries];
+  __shared__ int64_t s_slot[kTileEdges];   // the edges' CSR slots
   __shared__ int32_t s_hist[kMaxOwners + 1];
   __shared__ int32_t s_wave[kRouteBlock / 64];
   __shared__ __attribute__((aligned(16))) uint32_t s_x[kRouteBlock];
@@ -941,48 +948,42 @@ __global__ __launch_bounds__(kRouteBlock) void k_sample_route(CsrArgs ga, Sample
   r.e0 = s_off[0];
   r.e1 = off_end;
   const int32_t E = r.e1 - r.e0;
-  if (tid < K) s_key[E + tid] = v;
   // draws: lane task q = tid + k * kRouteBlock is lane q % G of destination q / G
   const int lane = tid & (G - 1);
-  int32_t pos[kSampleRounds];
-  int64_t slot[kSampleRounds];
-#pragma unroll
-  for (int k = 0; k < kSampleRounds; ++k) {
-    pos[k] = -1;
-    slot[k] = 0;
-    const int32_t t = (tid + k * kRouteBlock) / G;
-    if (k * kRouteBlock >= K * G || t >= K) continue;   // the first test is uniform
+#pragma unroll 1
+  for (int t = tid / G; t - tid / G < K; t += kRouteBlock / G) {   // uniform
+    if (t >= K) continue;
     int32_t place;
-    sample_slot<G>(s_deg[t], a.fanout, s_v[t], a.layer, a.k0, a.k1, lane, &s_x[tid - lane], place, slot[k]);
-    if (place >= 0) {
-      pos[k] = s_off[t] + place;
-      slot[k] += s_beg[t];
-    }
+    int64_t slot;
+    sample_slot<G>(s_deg[t], a.fanout, s_v[t], a.layer, a.k0, a.k1, lane, &s_x[tid - lane], place, slot);
+    if (place >= 0) s_slot[s_off[t] + place - r.e0] = s_beg[t] + slot;
   }
-  int32_t u[kSampleRounds];
-#pragma unroll
-  for (int k = 0; k < kSampleRounds; ++k) u[k] = g.indices[pos[k] >= 0 ? slot[k] : 0];
-#pragma unroll
-  for (int k = 0; k < kSampleRounds; ++k) {
-    if (pos[k] < 0) continue;
-    a.nbr[pos[k]] = u[k];
-    s_key[pos[k] - r.e0] = u[k];
-    if (!valid_vertex(u[k], g.num_nodes)) raise_status(a.status, GMB_STATUS_ERANGE);
-  }
-  // routing (see k_route), the keys from LDS
-  const int32_t M = E + K;
   __syncthreads();
-  int32_t key[kRouteItems];
-  uint32_t bucket[kRouteItems];
-  int32_t rank[kRouteItems];
+  // thread's items: the edges tid + k * kRouteBlock and destination tid
+  constexpr int kItems = kEdgeItems + 1;
+  int32_t key[kItems];
+  bool live[kItems];
 #pragma unroll
-  for (int k = 0; k < kRouteItems; ++k) {
-    const int32_t i = tid + k * kRouteBlock;
-    key[k] = i < M ? s_key[i] : -1;
+  for (int k = 0; k < kEdgeItems; ++k) {
+    live[k] = tid + k * kRouteBlock < E;
+    key[k] = g.indices[live[k] ? s_slot[tid + k * kRouteBlock] : 0];
+  }
+  live[kEdgeItems] = tid < K;
+  key[kEdgeItems] = v;
+#pragma unroll
+  for (int k = 0; k < kEdgeItems; ++k) {
+    if (!live[k]) continue;
+    a.nbr[r.e0 + tid + k * kRouteBlock] = key[k];
+    if (!valid_vertex(key[k], g.num_nodes)) raise_status(a.status, GMB_STATUS_ERANGE);
+  }
+  uint32_t bucket[kItems];
+  int32_t rank[kItems];
+#pragma unroll
+  for (int k = 0; k < kItems; ++k) {
     const bool ok = valid_vertex(key[k], ra.num_nodes);
     bucket[k] = ok ? owner_of(static_cast<uint32_t>(key[k]), P) : 0u;
     if (!ok) key[k] = -1;
-    rank[k] = i < M ? atomicAdd(&s_hist[bucket[k]], 1) : 0;
+    if (live[k]) rank[k] = atomicAdd(&s_hist[bucket[k]], 1);
   }
   __syncthreads();
   block_scan_inplace<kRouteBlock>(s_hist, P + 1, s_wave);
@@ -991,10 +992,10 @@ __global__ __launch_bounds__(kRouteBlock) void k_sample_route(CsrArgs ga, Sample
     ra.off[static_cast<int64_t>(b) * ra.routers + w] = static_cast<uint16_t>(s_hist[b]);
   if (tid == 0) ra.rs[w] = static_cast<int32_t>(region);
 #pragma unroll
-  for (int k = 0; k < kRouteItems; ++k) {
-    const int32_t i = tid + k * kRouteBlock;
-    if (i >= M) continue;
-    const uint32_t val = i < E ? (kEdgeTag | static_cast<uint32_t>(r.e0 + i)) : static_cast<uint32_t>(r.p0 + (i - E));
+  for (int k = 0; k < kItems; ++k) {
+    if (!live[k]) continue;
+    const uint32_t val = k < kEdgeItems ? (kEdgeTag | static_cast<uint32_t>(r.e0 + tid + k * kRouteBlock))
+                                        : static_cast<uint32_t>(r.p0 + tid);
     ra.pairs[region + s_hist[bucket[k]] + rank[k]] = make_uint2(static_cast<uint32_t>(key[k]), val);
   }
 }
@@ -1010,10 +1011,11 @@ __global__ __launch_bounds__(kRouteBlock) void k_sample_route(CsrArgs ga, Sample
 // group, so a lane's first pairs cost two rounds of reads (the segment's
 // offsets, its pair) and stay in registers for the answers; a segment's
 // further pairs, and the segments past kOwnerSegs per group, are read again
-// (from the L2).  11.1 us on 256 owners of 2.3k pairs from 256 routers;
-// finding every pair's segment by a scan of the segment lengths and a binary
-// search in LDS took 12.3 us, and an LDS copy of the pairs that this needs no
-// more.
+// (from the L2).  (Finding every pair's segment by a scan of the segment
+// lengths and a binary search in LDS: 12.3 us on 256 owners of 2.3k pairs from
+// 256 routers, this 11.1.)  Key and value share a 64-bit slot, so a new key
+// costs one LDS atomic instead of a read and two, and a lane keeps its pairs'
+// slots for the answers instead of probing again: 10.0 us.
 // If the table overflows (more distinct keys than slots), the owner redoes
 // its pairs through the per-vertex table of the sampler state: atomicMin, a
 // barrier, the read-back, and the slots reset; only this owner ever touches
@@ -1021,7 +1023,8 @@ __global__ __launch_bounds__(kRouteBlock) void k_sample_route(CsrArgs ga, Sample
 constexpr int kOwnerBlock = 1024;
 constexpr int kOwnerSegs = 4;
 constexpr int32_t kFirstOccurrence = INT32_MIN;
-constexpr int32_t kEmptyKey = INT32_MIN;
+constexpr unsigned long long kEmptySlot = ~0ull;   // (no key has its top bit set)
+constexpr uint32_t kNoSlot = ~0u;
 
 __device__ __forceinline__ int32_t owner_answer(uint32_t best, uint32_t val) {
   if (best < kEdgeTag) return static_cast<int32_t>(best);
@@ -1034,11 +1037,11 @@ __device__ __forceinline__ int32_t owner_answer(uint32_t best, uint32_t val) {
 struct OwnerSegs {
   int32_t start[kOwnerSegs], len[kOwnerSegs];
   uint2 pr[kOwnerSegs];
+  uint32_t slot[kOwnerSegs];   // the table slot of this lane's first pair, once inserted
 };
 
 __global__ __launch_bounds__(kOwnerBlock) void k_owner(OwnerArgs a) {
-  __shared__ __attribute__((aligned(16))) int32_t s_key[kOwnerSlots];
-  __shared__ __attribute__((aligned(16))) uint32_t s_val[kOwnerSlots];
+  __shared__ __attribute__((aligned(16))) unsigned long long s_slot[kOwnerSlots];   // key << 32 | value
   __shared__ int s_overflow;
   const int b = blockIdx.x;
   const int W = a.routers;
@@ -1070,12 +1073,16 @@ __global__ __launch_bounds__(kOwnerBlock) void k_owner(OwnerArgs a) {
     for (int k = 0; k < kOwnerSegs; ++k)
       if (lane >= sg.len[k]) sg.pr[k] = make_uint2(0xFFFFFFFFu, 0u);
   };
-  // every pair of the segments: f(position, pair)
-  auto for_pairs = [&](const OwnerSegs& sg, auto&& f) {
+  // every pair of the segments: f(position, pair, its table slot (kNoSlot
+  // where it is not kept))
+  auto for_pairs = [&](OwnerSegs& sg, auto&& f) {
 #pragma unroll
     for (int k = 0; k < kOwnerSegs; ++k) {
-      if (lane < sg.len[k]) f(sg.start[k] + lane, sg.pr[k]);
-      for (int32_t i = lane + lanes; i < sg.len[k]; i += lanes) f(sg.start[k] + i, a.pairs[sg.start[k] + i]);
+      if (lane < sg.len[k]) f(sg.start[k] + lane, sg.pr[k], sg.slot[k]);
+      for (int32_t i = lane + lanes; i < sg.len[k]; i += lanes) {
+        uint32_t none = kNoSlot;
+        f(sg.start[k] + i, a.pairs[sg.start[k] + i], none);
+      }
     }
   };
   const int step = groups * kOwnerSegs;
@@ -1087,29 +1094,27 @@ __global__ __launch_bounds__(kOwnerBlock) void k_owner(OwnerArgs a) {
       OwnerSegs sg;
       load_segs(w0, sg);
       load_pairs(sg);
+#pragma unroll
+      for (int k = 0; k < kOwnerSegs; ++k) sg.slot[k] = kNoSlot;
       for_pairs(sg, f);
     }
   };
   load_segs(0, first);
-  for (int i = threadIdx.x; i < C / 4; i += kOwnerBlock) {   // C >= 64
-    reinterpret_cast<int4*>(s_key)[i] = make_int4(kEmptyKey, kEmptyKey, kEmptyKey, kEmptyKey);
-    reinterpret_cast<uint4*>(s_val)[i] = make_uint4(kEmpty, kEmpty, kEmpty, kEmpty);
-  }
+  for (int i = threadIdx.x; i < C / 2; i += kOwnerBlock)   // C >= 64
+    reinterpret_cast<uint4*>(s_slot)[i] = make_uint4(~0u, ~0u, ~0u, ~0u);
   if (threadIdx.x == 0) s_overflow = 0;
   load_pairs(first);
   __syncthreads();
-  for_all([&](int32_t, const uint2& pr) {
-    const int32_t key = static_cast<int32_t>(pr.x);
-    if (key < 0) return;
+  for_all([&](int32_t, const uint2& pr, uint32_t& slot) {
+    if (static_cast<int32_t>(pr.x) < 0) return;
+    const unsigned long long mine = (static_cast<unsigned long long>(pr.x) << 32) | pr.y;
     uint32_t h = slot_of(pr.x, shift);
     for (int probes = 0;; ++probes) {
-      int32_t cur = s_key[h];
-      if (cur == kEmptyKey) {
-        cur = atomicCAS(&s_key[h], kEmptyKey, key);
-        if (cur == kEmptyKey) cur = key;
-      }
-      if (cur == key) {
-        const uint32_t old = atomicMin(&s_val[h], pr.y);
+      // a new key takes an empty slot with its value in one step
+      const unsigned long long cur = atomicCAS(&s_slot[h], kEmptySlot, mine);
+      if (cur == kEmptySlot) break;
+      if (static_cast<uint32_t>(cur >> 32) == pr.x) {
+        const uint32_t old = static_cast<uint32_t>(atomicMin(&s_slot[h], mine));
         if (pr.y < kEdgeTag && old < kEdgeTag && old != pr.y) raise_status(a.status, GMB_STATUS_EDUP);
         break;
       }
@@ -1119,34 +1124,35 @@ __global__ __launch_bounds__(kOwnerBlock) void k_owner(OwnerArgs a) {
       }
       h = (h + 1) & (C - 1);
     }
+    slot = h;
   });
   __syncthreads();
   if (!s_overflow) {
-    for_all([&](int32_t at, const uint2& pr) {
+    for_all([&](int32_t at, const uint2& pr, uint32_t& slot) {
       if (!(pr.y & kEdgeTag)) return;
       int32_t ans = 0;   // an id outside the graph: local id 0
       if (static_cast<int32_t>(pr.x) >= 0) {
-        uint32_t h = slot_of(pr.x, shift);
-        for (int probes = 0; probes < C; ++probes, h = (h + 1) & (C - 1)) {
-          if (s_key[h] == static_cast<int32_t>(pr.x)) {
-            ans = owner_answer(s_val[h], pr.y);
-            break;
-          }
+        uint32_t h = slot;
+        if (h == kNoSlot) {   // not kept: find it again
+          h = slot_of(pr.x, shift);
+          for (int probes = 0; probes < C && static_cast<uint32_t>(s_slot[h] >> 32) != pr.x; ++probes)
+            h = (h + 1) & (C - 1);
         }
+        ans = owner_answer(static_cast<uint32_t>(s_slot[h]), pr.y);
       }
       a.res[at] = ans;
     });
     return;
   }
   // overflow: the same through the state's per-vertex table
-  for_all([&](int32_t, const uint2& pr) {
+  for_all([&](int32_t, const uint2& pr, uint32_t&) {
     if (static_cast<int32_t>(pr.x) < 0) return;
     const uint32_t old = atomicMin(&a.table[pr.x], pr.y);
     if (pr.y < kEdgeTag && old < kEdgeTag && old != pr.y) raise_status(a.status, GMB_STATUS_EDUP);
   });
   __threadfence();
   __syncthreads();
-  for_all([&](int32_t at, const uint2& pr) {
+  for_all([&](int32_t at, const uint2& pr, uint32_t&) {
     if (!(pr.y & kEdgeTag)) return;
     int32_t ans = 0;
     if (static_cast<int32_t>(pr.x) >= 0)
@@ -1155,7 +1161,7 @@ __global__ __launch_bounds__(kOwnerBlock) void k_owner(OwnerArgs a) {
   });
   __threadfence();
   __syncthreads();
-  for_all([&](int32_t, const uint2& pr) {
+  for_all([&](int32_t, const uint2& pr, uint32_t&) {
     if (static_cast<int32_t>(pr.x) >= 0) a.table[pr.x] = kEmpty;
   });
 }
