@@ -742,7 +742,7 @@ namespace {
 struct BackwardPlan {
   int ldz[GMB_MAX_LAYERS];   // row stride of dZ of layer l (floats, multiple of 4)
   size_t off_a, off_b, off_dm, off_part, off_lossrows;
-  size_t off_cnt, off_off, off_pos, off_csc, off_long;   // the transpose of a block
+  size_t off_cnt, off_off, off_pos, off_place, off_csc, off_long;   // the transpose of a block
   int64_t cnt_len;                             // ints of the edge counters
   int64_t scan_len;                            // ints of one layer's scan state
   int64_t clear_len;                           // ints cleared at the start (counters + scan states)
@@ -758,6 +758,11 @@ struct BackwardPlan {
 // also runs layer 0's input gradient and its transpose (the rows it needs:
 // layer 0's destinations for the self part and the mean's gradient).
 int plan_backward_f32(const gmb_blocks* b, const gmb_sage_weights* w, BackwardPlan* plan, bool embed);
+
+// Blocks of more edges (by capacity) keep each edge's place from the
+// transpose's count; smaller ones take cursors in the fill (sage_bwd.hip has
+// both sides' times at 990k and 60k edges of capacity).
+constexpr int64_t kPlaceNnz = 262144;
 
 // The fp32 weights struct of a bf16 model's training step: the same dims
 // and biases, the upper layers' matrices at the fp32 copies of the plan in
@@ -846,6 +851,8 @@ int plan_backward_f32(const gmb_blocks* b, const gmb_sage_weights* w, BackwardPl
   off = align_up(off + 4 * (src + 1));
   p.off_pos = off;
   off = align_up(off + 4 * src);
+  p.off_place = off;
+  if (nnz > kPlaceNnz) off = align_up(off + 4 * nnz);
   p.off_csc = off;
   off = align_up(off + 8 * nnz);
   p.off_long = off;
@@ -996,18 +1003,19 @@ int run_backward(const gmb_blocks* blocks, const void* x, const gmb_sage_weights
                           below ? &fold : nullptr, s);
     if (e != hipSuccess) return hip_fail(e, "weight-gradient launch");
     if (!below) break;
+    int32_t* place = bk.cap_nnz > kPlaceNnz ? reinterpret_cast<int32_t*>(base + p.off_place) : nullptr;
     // dZ [W_self; W_neigh]^T: dH_self into `other`, dM; the block's
     // in-edge counts per source on the way
     e = gmb::launch_dgrad(bk.sizes, cur, p.ldz[l], d_out, static_cast<const float*>(weights->w_self[l]),
-                          static_cast<const float*>(weights->w_neigh[l]), d_in, other, dM, bk.cap_dst, bk.indptr,
-                          bk.indices, bk.cap_nnz, bk.fanout, cnt, s);
+                          static_cast<const float*>(weights->w_neigh[l]), d_in, other, dM, bk.cap_dst,
+                          bk.indices, bk.cap_nnz, cnt, place, s);
     if (e != hipSuccess) return hip_fail(e, "input-gradient launch");
     // the mean's backward through the block's transpose, the ReLU of the
     // layer below on the way out: `other` becomes that layer's dZ; on layer
     // 0 (learnable embeddings) the input gradient goes into the table rows
     uint32_t* scan_state = reinterpret_cast<uint32_t*>(cnt + p.cnt_len + (embed ? l : l - 1) * p.scan_len);
     const void* mask = l == 0 ? nullptr : (lo ? lo->hidden[l - 1] : static_cast<const void*>(h_in));
-    e = gmb::launch_mean_backward(bk.sizes, bk.indptr, bk.indices, bk.cap_nnz, bk.fanout, dM, mask, lo ? 1 : 0, d_in, other, bk.cap_dst, bk.cap_src, cnt, offs, pos,
+    e = gmb::launch_mean_backward(bk.sizes, bk.indptr, bk.indices, bk.cap_nnz, bk.fanout, dM, mask, lo ? 1 : 0, d_in, other, bk.cap_dst, bk.cap_src, cnt, offs, pos, place,
                                   scan_state, csc, long_rows, l == 0 ? table : nullptr, bk.src_ids, num_nodes,
                                   emb_lr, beside_scan ? &defer : nullptr, &fold, s);
     if (e != hipSuccess) return hip_fail(e, "mean-backward launch");

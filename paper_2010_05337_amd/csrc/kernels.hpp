@@ -295,10 +295,12 @@ hipError_t launch_wgrad(const int32_t* sizes, const void* H, const void* M, int 
                         int ldz, int d_out, int64_t cap_rows, float* partial, float* d_self, float* d_neigh,
                         float* d_bias, const float* loss_rows, int n_loss, float* loss, WgradArgs* defer,
                         ReduceArgs* fold, hipStream_t s);
+// Also counts the block's edges per source into cnt (zero before) and, with
+// `place` [cap_nnz], writes each edge's number among its source's there (the
+// mean backward then takes no cursors).
 hipError_t launch_dgrad(const int32_t* sizes, const float* dZ, int ldz, int d_out, const float* ws,
                         const float* wn, int d_in, float* dH, float* dM, int64_t cap_rows,
-                        const int32_t* indptr, const int32_t* local, int64_t cap_nnz, int32_t fanout, int32_t* cnt,
-                        hipStream_t s);
+                        const int32_t* local, int64_t cap_nnz, int32_t* cnt, int32_t* place, hipStream_t s);
 // look-back tiles of the transpose scan over cap_src sources; its state
 // (the tile tickets, the long-row count, then 2 words per tile) must start
 // zeroed; long_rows holds cap_src ints
@@ -309,7 +311,8 @@ int64_t csc_scan_tiles(int64_t cap_src);
 // weight gradient's products, with `fold` the fill's grid its reduction.
 hipError_t launch_mean_backward(const int32_t* sizes, const int32_t* indptr, const int32_t* local,
                                 int64_t cap_nnz, int32_t fanout, const float* dM, const void* out, int out_bf16, int d,
-                                float* dH, int64_t cap_dst, int64_t cap_src, int32_t* cnt, int32_t* off, int32_t* pos,
+                                float* dH, int64_t cap_dst, int64_t cap_src, int32_t* cnt, int32_t* off,
+                                int32_t* pos, const int32_t* place,
                                 uint32_t* scan_state, int2* csc, int32_t* long_rows, float* table, const int32_t* ids,
                                 int64_t num_nodes, float lr, const WgradArgs* defer, const ReduceArgs* fold,
                                 hipStream_t s);

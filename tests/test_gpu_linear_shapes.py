@@ -154,3 +154,35 @@ def test_bf16_weight_gradient_widths(orc, dg, graph, dims, rows):
         for a, b in zip(got, want):
             assert float((a - b).abs().max()) <= 1e-4 * float(b.abs().max())
     csr.check_status()
+
+
+@pytest.mark.parametrize("rows", [16384, 16385])
+def test_embedding_update_at_the_place_threshold(orc, dg, graph, rows):
+    """The transpose of a block of 2^18 edges of capacity takes cursors in its
+    fill, of more the places from the count: every updated embedding row and
+    the untouched ones against the oracle's fp64 step (a one-layer model, no
+    ReLU), within 1e-4 of the largest gradient (fp32 sums of a source's few
+    hundred terms) plus the update's rounding."""
+    print(f"{rows} rows", flush=True)
+    dims, fanouts, lr = [12, 5], [16], 0.5
+    table_np = dg.features(graph.num_nodes, dims[0], 5, "f32")
+    table = to_torch_feats(table_np)
+    w = dg.sage_weights(dims, 6)
+    seeds = dg.permutation(graph.num_nodes, 7)[:rows]
+    labels = dg.labels(graph.num_nodes, dims[-1], 9)[seeds]
+    csr = csr_on_device(graph)
+    wt = to_torch_weights(w)
+    blocks = gmb.sample_blocks(csr, torch.from_numpy(seeds).cuda(), fanouts, 8)
+    ws = gmb._aligned_bytes(gmb.forward_workspace_bytes(blocks, wt), table.device)[1]
+    logits, x_dst = gmb.sage_forward_fused(blocks, table, wt, workspace=ws)
+    gmb.sage_backward(blocks, x_dst, wt, logits, torch.from_numpy(labels).cuda(), ws, embedding=table, emb_lr=lr)
+    ref = orc.sample_blocks(graph.indptr, graph.indices, seeds, fanouts, 8)
+    ws_, wn_, bs_ = w.as_f64()
+    _, _, dX, _, ref_table = orc.sage_train_step_embed(ref, table_np.astype(np.float64), ws_, wn_, bs_, labels, 0.1, lr)
+    got = table.cpu().numpy()
+    bound = lr * 1e-4 * np.abs(dX).max() + 2.0 ** -23 * np.abs(table_np).max()
+    assert np.abs(got - ref_table).max() <= bound
+    rest = np.ones(graph.num_nodes, bool)
+    rest[ref[0].src] = False
+    assert np.array_equal(got[rest], table_np[rest])
+    csr.check_status()
