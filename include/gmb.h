@@ -331,11 +331,12 @@ size_t gmb_backward_workspace_bytes(const gmb_blocks* blocks, const gmb_sage_wei
  * (dZ W_neigh^T)[v] / k_v of the mean.
  *   blocks, x, weights  as given to the gmb_sage_forward call that produced
  *                       `logits`, fp32 or bf16.  A bf16 model's backward
- *                       first widens block 0's destination rows of x, every
- *                       layer's kept mean and hidden output and the matrices
- *                       to fp32 (inside `ws`), then runs the fp32 backward
- *                       on them: fp32 products, fp32 gradients (update
- *                       with gmb_sgd_update_bf16).
+ *                       first widens the upper layers' rows (each layer
+ *                       l >= 1: its destination rows and its kept mean) and
+ *                       the matrices to fp32 (inside `ws`); layer 0's rows
+ *                       and mean and every ReLU mask are read as bf16, a
+ *                       value that fp32 holds exactly.  fp32 products, fp32
+ *                       gradients (update with gmb_sgd_update_bf16).
  *   logits   device fp32 [num_seeds, dims[L]] from that call.
  *   labels   device int32 [num_seeds], the class of each seed in
  *            [0, dims[L]) (a label outside it is a data error: that row's
