@@ -246,7 +246,7 @@ def summarize_profile(args):
         steps, cur = [], None
         for r in window:
             name = r["Kernel_Name"].replace("gmb::(anonymous namespace)::", "").replace("void ", "").split("(")[0]
-            if name.startswith("k_seed_scan"):
+            if name.startswith(("k_seed_scan", "k_seed_sample")):   # a step's first kernel
                 cur = []
                 steps.append(cur)
             if cur is not None:
