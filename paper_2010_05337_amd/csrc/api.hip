@@ -179,7 +179,7 @@ int plan_sampling(int32_t num_seeds, const int32_t* fanouts, int32_t num_layers,
     }
     hp.tiles_word = zero_words;
     zero_words += hp.tile_stride * (num_layers - h);
-    zero_words = (zero_words + 15) / 16 * 16;   // the tickets on lines of their own
+    zero_words = (zero_words + 15) / 16 * 16;   // the ticket on a line of its own
     hp.ticket_word = zero_words;
     zero_words += gmb::kScanTicketWords / 2;
     cap_dst = hp.cap_src;

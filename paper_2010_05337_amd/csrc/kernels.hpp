@@ -34,8 +34,8 @@ struct HopArgs {
   int layer;
 };
 
-// 32-bit words of one scan's tile tickets (scan.hpp), start zeroed
-constexpr int kScanTicketWords = 256;
+// 32-bit words of one scan's tile ticket (scan.hpp), start zeroed
+constexpr int kScanTicketWords = 32;
 constexpr int kScanBlock = 256;
 // Items per thread of a relabel tile (kScanBlock threads): 2, 4, 8 or 16.
 // Small hops take small tiles so that their random reads spread over many
@@ -302,7 +302,7 @@ hipError_t launch_dgrad(const int32_t* sizes, const float* dZ, int ldz, int d_ou
                         const float* wn, int d_in, float* dH, float* dM, int64_t cap_rows,
                         const int32_t* local, int64_t cap_nnz, int32_t* cnt, int32_t* place, hipStream_t s);
 // look-back tiles of the transpose scan over cap_src sources; its state
-// (the tile tickets, the long-row count, then 2 words per tile) must start
+// (the tile ticket, the long-row count, then 2 words per tile) must start
 // zeroed; long_rows holds cap_src ints
 int64_t csc_scan_tiles(int64_t cap_src);
 // With table != NULL the pull applies table[ids[u]] -= lr * g instead of

@@ -842,9 +842,9 @@ bool dgrad_parts_for(const int32_t* sizes, const parts::DgradOp& op, int64_t cap
 // fill's cursors, where it takes any), cnt cleared for the next layer, and the
 // sources
 // with more than kLongList entries listed in long_rows[0 .. *n_long).  Tiles of 1024
-// counts (four per thread), numbered by an atomic ticket, joined by the
-// decoupled look-back (both the ticket and the look-back words start at 0).
-// If the look-back's bounded wait runs out (it does not when every tile
+// counts (four per thread), numbered by an atomic ticket, joined by
+// tile_prefix (both the ticket and the tiles' words start at 0).
+// If its bounded wait runs out (it does not when every tile
 // runs), the offsets come out wrong but the fill and the pull stay in
 // bounds.
 // Counts per scan workgroup (256 threads, kScanTile / 1024 int4 each):
@@ -1470,7 +1470,7 @@ hipError_t launch_mean_backward(const int32_t* sizes, const int32_t* indptr, con
                                 int64_t num_nodes, float lr, const WgradArgs* defer, const ReduceArgs* fold,
                                 hipStream_t s) {
   const EdgeView ev{indptr, local, place, cap_nnz, fanout};
-  // scan_state: the tile tickets, the long-row count, a pad word, then the
+  // scan_state: the tile ticket, the long-row count, a pad word, then the
   // look-back words
   uint32_t* n_long = scan_state + kTicketWords;
   int32_t* cursors = place ? nullptr : pos;

@@ -8,12 +8,12 @@
 // "Single-pass parallel prefix scan with decoupled look-back", NVIDIA
 // technical report NVR-2016-002): every tile publishes its aggregate at
 // once, then walks back over its predecessors until it meets one that has
-// published an inclusive prefix.  Tiles are numbered by tickets
-// (claim_tile), so that a tile only ever waits on tiles that run or are next
-// to start, and every tile publishes its aggregate before it waits: every
-// wait ends.  The wait is still bounded (kLookbackSpins
-// sleeps); a tile that runs out reports it, publishes a wrong prefix (so
-// its successors still finish) and goes on.
+// published an inclusive prefix.  Tiles are numbered in the order in which
+// workgroups start (claim_tile), so a tile only ever waits on tiles that are
+// already running, and every tile publishes its aggregate before it waits:
+// every wait ends.  The wait is still bounded (kLookbackSpins sleeps); a tile
+// that runs out reports it, publishes a wrong prefix (so its successors still
+// finish) and goes on.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -79,7 +79,8 @@ __device__ __forceinline__ void block_exclusive_scan_multi(const int32_t (&x)[NV
 // ran out.
 template <int NV>
 __device__ bool tile_lookback_multi(uint64_t* tiles, int64_t stride, int tile,
-                                    const int32_t (&aggregate)[NV], int32_t (&exclusive)[NV]) {
+                                    const int32_t (&aggregate)[NV], int32_t (&exclusive)[NV],
+                                    int max_spins = kLookbackSpins) {
   const int lane = threadIdx.x & 63;
 #pragma unroll
   for (int a = 0; a < NV; ++a) exclusive[a] = 0;
@@ -114,7 +115,7 @@ __device__ bool tile_lookback_multi(uint64_t* tiles, int64_t stride, int tile,
 #pragma unroll
       for (int a = 0; a < NV; ++a) pending |= !done[a] && (w[a] >> 62) == 0;
       if (!__any(pending)) break;
-      if (++spins > kLookbackSpins) {
+      if (++spins > max_spins) {
         ok = false;
         break;
       }
@@ -165,7 +166,8 @@ __device__ bool tile_lookback_multi(uint64_t* tiles, int64_t stride, int tile,
 constexpr int kFlatTiles = 1024;
 template <int BLOCK, int NV>
 __device__ __forceinline__ bool tile_prefix(uint64_t* tiles, int64_t stride, int tile, int num_tiles,
-                                            const int32_t (&aggregate)[NV], int32_t (&exclusive)[NV], int32_t* smem) {
+                                            const int32_t (&aggregate)[NV], int32_t (&exclusive)[NV], int32_t* smem,
+                                            int max_spins = kLookbackSpins) {
   constexpr int W = BLOCK / 64;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   bool ok = true;
@@ -188,7 +190,7 @@ __device__ __forceinline__ bool tile_prefix(uint64_t* tiles, int64_t stride, int
           w[a] = __hip_atomic_load(&tiles[a * stride + t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
         for (int a = 0; a < NV; ++a) pending |= w[a] == 0;
-        if (!pending || ++spins > kLookbackSpins) {
+        if (!pending || ++spins > max_spins) {
           ok &= !pending;
 #pragma unroll
           for (int a = 0; a < NV; ++a) sum[a] += static_cast<int32_t>(static_cast<uint32_t>(w[a]));
@@ -205,7 +207,7 @@ __device__ __forceinline__ bool tile_prefix(uint64_t* tiles, int64_t stride, int
   } else {
 #pragma unroll
     for (int a = 0; a < NV; ++a) sum[a] = 0;
-    if (wave == 0) ok = tile_lookback_multi<NV>(tiles, stride, tile, aggregate, sum);
+    if (wave == 0) ok = tile_lookback_multi<NV>(tiles, stride, tile, aggregate, sum, max_spins);
   }
   if (lane == 0) {
 #pragma unroll
@@ -222,29 +224,19 @@ __device__ __forceinline__ bool tile_prefix(uint64_t* tiles, int64_t stride, int
 }
 
 // Claims the next tile number for this workgroup (thread 0 takes a ticket,
-// the block reads it from LDS).  Tickets on one counter are served one after
-// another, about 13 ns each, so a scan's last tile started microseconds
-// after its first (256 tiles 3.3 us); kTicketShards counters on lines of
-// their own serve the workgroups b = s mod kTicketShards: shard s's k-th ticket
-// is tile kTicketShards k + s, so the tiles of the first n workgroups are 0
-// .. n - 1 as before.
-//
-// Every wait still ends: let T, in shard s, be the smallest unfinished tile.
-// If it runs, all its predecessors have finished, so it finishes.  If it has
-// not started, the workgroups of shard s that have are tiles below T (a shard
-// gives its tickets in the order in which they are asked for), so they have
-// finished and hold nothing; workgroups go round robin over the 8 XCDs, so
-// shard s has an XCD to itself and its next workgroup, which becomes T, is not
-// kept out by waiting ones of other shards.  Where workgroups start in order
-// (on one XCD, too), tile numbers are workgroup numbers and the same holds.
-constexpr int kTicketShards = 8;
-constexpr int kTicketStride = 32;   // uint32 words between the shards' counters
-constexpr int kTicketWords = kTicketShards * kTicketStride;
-__device__ __forceinline__ int claim_tile(uint32_t* counters, int* s_tile) {
-  if (threadIdx.x == 0) {
-    const uint32_t shard = blockIdx.x % kTicketShards;
-    *s_tile = static_cast<int>(atomicAdd(&counters[shard * kTicketStride], 1u) * kTicketShards + shard);
-  }
+// the block reads it from LDS).  One counter for the whole scan, so tiles are
+// numbered in the order in which workgroups ask, whichever they are: all
+// predecessors of a tile have started, hold their CU until they end, and
+// publish before they wait.  That holds whatever else runs on the GPU.  Several
+// scans share it (mini-batches in flight on several streams), and one scan's
+// waiting workgroups can fill CUs that another's unstarted ones need: a scheme
+// that fixes the numbers by workgroup index, or by counters for classes of
+// indices, can then wait for a tile that never starts.  It costs time:
+// tickets on one word are served one after another, about 13 ns each (a scan
+// of 256 tiles 3.3 us).
+constexpr int kTicketWords = 32;   // uint32 words: the counter on a line of its own
+__device__ __forceinline__ int claim_tile(uint32_t* counter, int* s_tile) {
+  if (threadIdx.x == 0) *s_tile = static_cast<int>(atomicAdd(counter, 1u));
   __syncthreads();
   return *s_tile;
 }
