@@ -263,7 +263,11 @@ int run_sampling(const gmb_csr* csr, const int32_t* seeds, int32_t num_seeds, in
   uint32_t* status = static_cast<uint32_t*>(state);
   uint32_t* table = reinterpret_cast<uint32_t*>(static_cast<char*>(state) + kStateHeader);
 
-  gmb::CsrArgs g{csr->indptr, csr->indices, csr->num_nodes, csr->indptr_bits == 64 ? 1 : 0};
+  // a graph without edges may come without an indices array; k_sample_route
+  // reads indices[0] for lanes that hold no edge (and drops it), so it gets an
+  // address that is readable: the row offsets, at least two words
+  const int32_t* indices = csr->num_edges > 0 ? csr->indices : static_cast<const int32_t*>(csr->indptr);
+  gmb::CsrArgs g{csr->indptr, indices, csr->num_nodes, csr->indptr_bits == 64 ? 1 : 0};
   gmb::HopArgs hops[GMB_MAX_LAYERS];
   gmb_blocks res{};
   res.num_layers = num_layers;

@@ -102,6 +102,20 @@ static void run_shape(int32_t B, std::vector<int32_t> fanouts, int64_t N, std::v
   CHECK(rc == 0 || rc == GMB_EDEVICE || rc == GMB_ENOSPC);
 }
 
+// A graph without edges needs no indices array; every kernel gets an address
+// that it may read.
+static void run_edgeless(int32_t B, std::vector<int32_t> fanouts, int64_t N) {
+  const int L = static_cast<int>(fanouts.size());
+  const size_t ws = gmb_sample_workspace_bytes(B, fanouts.data(), L, N);
+  const size_t sb = gmb_sampler_state_bytes(N);
+  gmb_blocks out{};
+  for (const void* indices : {static_cast<const void*>(nullptr), static_cast<const void*>(fake(2))}) {
+    gmb_csr csr{N, 0, fake(1), 32, 0, static_cast<const int32_t*>(indices)};
+    CHECK(gmb_sample_blocks(&csr, static_cast<const int32_t*>(fake(4)), B, fanouts.data(), L, 1, fake(3), sb, fake(5),
+                            ws, &out, nullptr) == 0);
+  }
+}
+
 int main() {
   setenv("GMB_VALIDATE", "1", 1);   // the sampling calls also enqueue the block check
   run_shape(1000, {15, 10, 5}, 2449029, {100, 256, 256, 47}, false);
@@ -113,6 +127,9 @@ int main() {
   run_shape(50, {6, 30}, 3000, {16, 12, 8}, false);
   run_shape(7, {1, 1, 1, 1, 1, 1, 1, 1}, 100, {4, 4, 4, 4, 4, 4, 4, 4, 4}, false);
   run_shape(3, {4096}, 1 << 20, {8, 4}, false);
+  run_edgeless(1000, {15, 10, 5}, 2449029);   // the last hop by owners
+  run_edgeless(40, {5}, 128);
+  run_edgeless(300, {70}, 3000);
   // argument errors
   std::vector<int32_t> f = {5, 0};
   CHECK(gmb_sample_workspace_bytes(10, f.data(), 2, 100) == 0);

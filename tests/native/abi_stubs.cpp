@@ -12,32 +12,39 @@
 
 namespace gmb {
 
+namespace {
+// the samplers read indices[0] for lanes without an edge: never NULL
+hipError_t readable(const CsrArgs& g) { return g.indptr && g.indices ? hipSuccess : hipErrorInvalidValue; }
+}  // namespace
+
 hipError_t launch_state_init(uint32_t*, uint32_t*, int64_t, hipStream_t) { return hipSuccess; }
-hipError_t launch_seed_scan(const SeedArgs&, int, const CsrArgs&, hipStream_t) { return hipSuccess; }
+hipError_t launch_seed_scan(const SeedArgs&, int, const CsrArgs& g, hipStream_t) { return readable(g); }
 bool seed_sample_fits(int32_t num_seeds, int num_values, int fanout) {
   return num_seeds >= 1 && num_seeds <= 8192 && num_values <= 3 && fanout <= 64;
 }
-hipError_t launch_seed_sample(const SeedArgs&, int, const CsrArgs&, int32_t*, uint32_t*, uint32_t*, int, uint32_t,
+hipError_t launch_seed_sample(const SeedArgs&, int, const CsrArgs& g, int32_t*, uint32_t*, uint32_t*, int, uint32_t,
                               uint32_t, hipStream_t) {
-  return hipSuccess;
+  return readable(g);
 }
-hipError_t launch_sample_table(const CsrArgs&, const int32_t*, const HopArgs&, uint32_t*, uint32_t*, uint32_t,
+hipError_t launch_sample_table(const CsrArgs& g, const int32_t*, const HopArgs&, uint32_t*, uint32_t*, uint32_t,
                                uint32_t, int, const DeferredArgs&, hipStream_t) {
-  return hipSuccess;
+  return readable(g);
 }
-hipError_t launch_assign(const AssignArgs&, int, const CsrArgs&, int64_t, int, int32_t*, uint32_t*, uint32_t*,
+hipError_t launch_assign(const AssignArgs&, int, const CsrArgs& g, int64_t, int, int32_t*, uint32_t*, uint32_t*,
                          hipStream_t) {
-  return hipSuccess;
+  return readable(g);
 }
-hipError_t launch_sample(const CsrArgs&, const int32_t*, const HopArgs&, uint32_t*, uint32_t, uint32_t, int,
+hipError_t launch_sample(const CsrArgs& g, const int32_t*, const HopArgs&, uint32_t*, uint32_t, uint32_t, int,
                          const DeferredArgs&, hipStream_t) {
-  return hipSuccess;
+  return readable(g);
 }
 hipError_t launch_route(const RouteArgs&, hipStream_t) { return hipSuccess; }
-hipError_t launch_sample_route(const CsrArgs&, const SampleArgs&, const RouteArgs&, hipStream_t) { return hipSuccess; }
+hipError_t launch_sample_route(const CsrArgs& g, const SampleArgs&, const RouteArgs&, hipStream_t) {
+  return readable(g);
+}
 hipError_t launch_owner(const OwnerArgs&, hipStream_t) { return hipSuccess; }
-hipError_t launch_rank(const RankArgs&, int, const CsrArgs&, int, int, int32_t*, uint32_t*, hipStream_t) {
-  return hipSuccess;
+hipError_t launch_rank(const RankArgs&, int, const CsrArgs& g, int, int, int32_t*, uint32_t*, hipStream_t) {
+  return readable(g);
 }
 hipError_t launch_validate(const ValidateArgs&, int64_t, uint32_t*, hipStream_t) { return hipSuccess; }
 hipError_t launch_fix(const DeferredArgs&, const int32_t*, const int32_t*, int64_t, uint32_t*, int64_t, hipStream_t) {

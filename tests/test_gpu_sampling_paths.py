@@ -75,3 +75,21 @@ def test_seed_scan_with_the_first_hop(orc, dg, graph, fanouts, num_seeds):
         with pytest.raises(gmb.GmbError) as e:
             csr.check_status()
         assert e.value.code == -4
+
+
+@pytest.mark.parametrize("wide", [False, True])
+@pytest.mark.parametrize("fanouts, num_seeds, num_nodes", [([15, 10, 5], 1000, 20_000), ([20], 14_000, 20_000),
+                                                           ([70], 300, 500), ([5, 5], 40, 128), ([3], 1, 1)])
+def test_graph_without_edges(orc, dg, fanouts, num_seeds, num_nodes, wide):
+    """No edges and so no indices array: every hop finds nothing, through the
+    owners (edge capacities above 2^18), the table and the wide fan-outs."""
+    print(f"no edges: fanouts {fanouts}, {num_seeds} seeds, wide {wide}", flush=True)
+
+    class G:
+        indptr, indices = np.zeros(num_nodes + 1, np.int64), np.zeros(0, np.int32)
+    csr = csr_on_device(G, wide)
+    seeds = dg.permutation(num_nodes, 4)[:num_seeds]
+    _, host = gpu_blocks(csr, seeds, fanouts, 3)
+    assert_blocks_equal(host, orc.sample_blocks(G.indptr, G.indices, seeds, fanouts, 3))
+    csr.check_status()
+    assert bool((csr.state[256:256 + 4 * num_nodes].view(torch.int32) == -1).all())
