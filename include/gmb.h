@@ -359,8 +359,9 @@ size_t gmb_backward_workspace_bytes(const gmb_blocks* blocks, const gmb_sage_wei
  * differ in their last bits.  The transpose's offsets come from a
  * single-pass scan whose tiles wait for their predecessors in a bounded
  * loop (about 4M short sleeps); only a GPU that stalls a running tile for
- * that long makes a wait give up, and then the input gradients of that
- * call are wrong (the call reports no status for it). */
+ * that long makes a wait give up.  The input gradients of that layer are
+ * unknown then: the weight gradients of the layers below it are NaN, and so
+ * is the loss (with loss NULL: the first entry of d_bias[0]). */
 int gmb_sage_backward(const gmb_blocks* blocks, const void* x, const gmb_sage_weights* weights,
                       const float* logits, const int32_t* labels, const void* fwd_ws, size_t fwd_ws_bytes,
                       const gmb_sage_grads* grads, float* loss, void* ws, size_t ws_bytes, void* stream);
@@ -391,6 +392,8 @@ size_t gmb_backward_embedding_workspace_bytes(const gmb_blocks* blocks, const gm
  * calls in flight together on several streams update the shared table
  * without locks (asynchronous SGD as in Hogwild, as the paper updates its
  * embeddings), and a gather running meanwhile may see old or new rows.
+ * If a wait of block 0's transpose gives up (see gmb_sage_backward), no row
+ * changes and the loss is NaN (with loss NULL: the first entry of d_bias[0]).
  * An empty batch changes no row (the gradients and the loss as for
  * gmb_sage_backward). */
 int gmb_sage_backward_embedding(const gmb_blocks* blocks, const void* x, const gmb_sage_weights* weights,

@@ -1021,7 +1021,7 @@ int run_backward(const gmb_blocks* blocks, const void* x, const gmb_sage_weights
     const void* mask = l == 0 ? nullptr : (lo ? lo->hidden[l - 1] : static_cast<const void*>(h_in));
     e = gmb::launch_mean_backward(bk.sizes, bk.indptr, bk.indices, bk.cap_nnz, bk.fanout, dM, mask, lo ? 1 : 0, d_in, other, bk.cap_dst, bk.cap_src, cnt, offs, pos, place,
                                   scan_state, csc, long_rows, l == 0 ? table : nullptr, bk.src_ids, num_nodes,
-                                  emb_lr, beside_scan ? &defer : nullptr, &fold, s);
+                                  emb_lr, beside_scan ? &defer : nullptr, &fold, loss ? loss : grads->d_bias[0], s);
     if (e != hipSuccess) return hip_fail(e, "mean-backward launch");
     std::swap(cur, other);
   }

@@ -302,20 +302,22 @@ hipError_t launch_dgrad(const int32_t* sizes, const float* dZ, int ldz, int d_ou
                         const float* wn, int d_in, float* dH, float* dM, int64_t cap_rows,
                         const int32_t* local, int64_t cap_nnz, int32_t* cnt, int32_t* place, hipStream_t s);
 // look-back tiles of the transpose scan over cap_src sources; its state
-// (the tile ticket, the long-row count, then 2 words per tile) must start
-// zeroed; long_rows holds cap_src ints
+// (the tile ticket, the long-row count, the word that a wait which ran out
+// sets, then 2 words per tile) must start zeroed; long_rows holds cap_src ints
 int64_t csc_scan_tiles(int64_t cap_src);
 // With table != NULL the pull applies table[ids[u]] -= lr * g instead of
 // writing the masked gradient into dH (out unused).
 // With `defer` (from launch_wgrad) the transpose scan's grid also runs the
 // weight gradient's products, with `fold` the fill's grid its reduction.
+// If a wait of the scan runs out (max_spins sleeps; 0: kLookbackSpins), every row of dH becomes NaN (a table stays as it is), and so does
+// *report.
 hipError_t launch_mean_backward(const int32_t* sizes, const int32_t* indptr, const int32_t* local,
                                 int64_t cap_nnz, int32_t fanout, const float* dM, const void* out, int out_bf16, int d,
                                 float* dH, int64_t cap_dst, int64_t cap_src, int32_t* cnt, int32_t* off,
                                 int32_t* pos, const int32_t* place,
                                 uint32_t* scan_state, int2* csc, int32_t* long_rows, float* table, const int32_t* ids,
                                 int64_t num_nodes, float lr, const WgradArgs* defer, const ReduceArgs* fold,
-                                hipStream_t s);
+                                float* report, hipStream_t s, int max_spins = 0);
 hipError_t launch_sgd(const SgdArgs& a, float lr, hipStream_t s);
 hipError_t launch_widen(const WidenArgs& a, hipStream_t s);
 // every array of `a` (w[t], n[t]; g unused) and *scalar (if not NULL) to 0

@@ -844,9 +844,9 @@ bool dgrad_parts_for(const int32_t* sizes, const parts::DgradOp& op, int64_t cap
 // with more than kLongList entries listed in long_rows[0 .. *n_long).  Tiles of 1024
 // counts (four per thread), numbered by an atomic ticket, joined by
 // tile_prefix (both the ticket and the tiles' words start at 0).
-// If its bounded wait runs out (it does not when every tile
-// runs), the offsets come out wrong but the fill and the pull stay in
-// bounds.
+// If its bounded wait (max_spins) runs out (it does not when every tile
+// runs), the offsets come out wrong, n_long[1] is set, and the fill and the
+// pull stay in bounds; the pull then reports it (kUnknown below).
 // Counts per scan workgroup (256 threads, kScanTile / 1024 int4 each):
 // 4096 measured no faster than 1024 on the 342k sources of a products2m
 // block's bottom layer (13 against 14 us; the hidden layer's fused scan 1 us
@@ -881,7 +881,8 @@ template <int WG>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(wg_occupancy(WG), wg_occupancy(WG))))
 void k_csc_scan(const int32_t* __restrict__ sizes, int32_t* __restrict__ cnt, int32_t* __restrict__ off,
                 int32_t* __restrict__ pos, uint32_t* __restrict__ ticket, uint64_t* __restrict__ words,
-                uint32_t* __restrict__ n_long, int32_t* __restrict__ long_rows, int scan_blocks, WgradArgs wg) {
+                uint32_t* __restrict__ n_long, int32_t* __restrict__ long_rows, int scan_blocks, int max_spins,
+                WgradArgs wg) {
   if constexpr (WG != 0) {
     if (static_cast<int>(blockIdx.x) >= scan_blocks) {
       const int w = blockIdx.x - scan_blocks;
@@ -928,7 +929,8 @@ void k_csc_scan(const int32_t* __restrict__ sizes, int32_t* __restrict__ cnt, in
   int32_t excl[1], total[1];
   block_exclusive_scan_multi<256, 1>(x, excl, total, smem);
   int32_t before[1];
-  tile_prefix<256, 1>(words, 0, tile, ntiles, total, before, smem);
+  if (!tile_prefix<256, 1>(words, 0, tile, ntiles, total, before, smem, max_spins) && threadIdx.x == 0)
+    atomicOr(n_long + 1, 1u);
   int32_t o = before[0] + excl[0];
 #pragma unroll
   for (int v = 0; v < kScanVec; ++v) {
@@ -1000,6 +1002,11 @@ __device__ __forceinline__ float4 load_out4(const uint16_t* p) {
                      __uint_as_float(x.y & 0xFFFF0000u));
 }
 
+// What the pull writes when the transpose's scan gave up (n_long[1]): NaN as
+// the gradient of every row (no row is updated on a table), and in `report`.
+// The flag is read with the first loads and used at the stores.
+constexpr float kUnknown = __builtin_nanf("");
+
 // The sources with long transpose lists, one workgroup per row (the n_wg
 // workgroups that the row kernels append to their grids stride over the
 // list; wg is this one's index among them): the eight 32-lane groups take the entries
@@ -1020,6 +1027,7 @@ __device__ void pull_long_rows(int wg, int n_wg, const int32_t* __restrict__ siz
   const int32_t n_dst = load_size(&sizes[kNDst]);
   const int32_t n_src = load_size(&sizes[kNSrc]);
   const int32_t nl = static_cast<int32_t>(__hip_atomic_load(n_long, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+  if (n_long[1]) return;   // the row kernel writes every row
   const int grp = threadIdx.x >> 5, lane = threadIdx.x & 31;
   const int chunks = d / 4;
   for (int32_t li = wg; li < nl; li += n_wg) {
@@ -1109,7 +1117,8 @@ __global__ __launch_bounds__(256) void k_pull_mean(const int32_t* __restrict__ s
                                                    int64_t cap_nnz, const float* __restrict__ dM,
                                                    const TO* __restrict__ out, int d, float* __restrict__ dH,
                                                    int row_blocks, const uint32_t* __restrict__ n_long,
-                                                   const int32_t* __restrict__ long_rows) {
+                                                   const int32_t* __restrict__ long_rows,
+                                                   float* __restrict__ report) {
   if (static_cast<int>(blockIdx.x) >= row_blocks) {   // the long lists
     pull_long_rows<false, TO>(blockIdx.x - row_blocks, gridDim.x - row_blocks, sizes, n_long, long_rows, off, csc,
                           cap_nnz, dM, out, d, dH, nullptr, nullptr, 0, 0.f);
@@ -1117,13 +1126,15 @@ __global__ __launch_bounds__(256) void k_pull_mean(const int32_t* __restrict__ s
   }
   const int32_t n_dst = load_size(&sizes[kNDst]);
   const int32_t n_src = load_size(&sizes[kNSrc]);
+  const bool unknown = n_long[1] != 0;
   const int64_t u = (static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x) / G;
   const int lane = threadIdx.x & (G - 1);
   if (u >= n_src) return;
   int32_t s0 = off[u], s1 = off[u + 1];
-  if (s1 - s0 > kLongList) return;   // a long list: the appended workgroups take it
+  if (s1 - s0 > kLongList && !unknown) return;   // a long list: the appended workgroups take it
+  if (unknown && u == 0 && lane == 0) *report = kUnknown;
   s0 = s0 < 0 ? 0 : s0;
-  s1 = s1 > cap_nnz ? static_cast<int32_t>(cap_nnz) : s1;
+  s1 = unknown ? s0 : (s1 > cap_nnz ? static_cast<int32_t>(cap_nnz) : s1);
   const bool self = u < n_dst;
   const int chunks = d / 4;
   for (int c = lane; c < chunks; c += G) {
@@ -1155,6 +1166,7 @@ __global__ __launch_bounds__(256) void k_pull_mean(const int32_t* __restrict__ s
     acc.y = o.y > 0.f ? acc.y : 0.f;
     acc.z = o.z > 0.f ? acc.z : 0.f;
     acc.w = o.w > 0.f ? acc.w : 0.f;
+    if (unknown) acc = make_float4(kUnknown, kUnknown, kUnknown, kUnknown);
     *reinterpret_cast<float4*>(dH + at) = acc;
   }
 }
@@ -1179,7 +1191,8 @@ __global__ __launch_bounds__(256) void k_pull_update(const int32_t* __restrict__
                                                      int d, float* __restrict__ table,
                                                      const int32_t* __restrict__ ids, int64_t num_nodes, float lr,
                                                      int row_blocks, const uint32_t* __restrict__ n_long,
-                                                     const int32_t* __restrict__ long_rows) {
+                                                     const int32_t* __restrict__ long_rows,
+                                                     float* __restrict__ report) {
   if (static_cast<int>(blockIdx.x) >= row_blocks) {   // the long lists
     pull_long_rows<true, float>(blockIdx.x - row_blocks, gridDim.x - row_blocks, sizes, n_long, long_rows, off, csc,
                          cap_nnz, dM, nullptr, d, dH, table, ids, num_nodes, lr);
@@ -1187,10 +1200,12 @@ __global__ __launch_bounds__(256) void k_pull_update(const int32_t* __restrict__
   }
   const int32_t n_dst = load_size(&sizes[kNDst]);
   const int32_t n_src = load_size(&sizes[kNSrc]);
+  const bool unknown = n_long[1] != 0;
   const int64_t group = (static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x) / G;
   const int lane = threadIdx.x & (G - 1);
   const int64_t u0 = group * R;
   if (u0 >= n_src) return;
+  if (unknown && group == 0 && lane == 0) *report = kUnknown;
   // first reads: the rows' offsets and table ids
   int32_t s0[R], cnt[R], trow[R];
   bool live[R], self[R];
@@ -1204,8 +1219,8 @@ __global__ __launch_bounds__(256) void k_pull_update(const int32_t* __restrict__
     a = a < 0 ? 0 : a;
     b = b > cap_nnz ? static_cast<int32_t>(cap_nnz) : b;
     s0[r] = a;
-    cnt[r] = b > a && !long_list ? b - a : 0;
-    live[r] = u < n_src && id >= 0 && id < num_nodes && !long_list;
+    cnt[r] = b > a && !long_list && !unknown ? b - a : 0;
+    live[r] = u < n_src && id >= 0 && id < num_nodes && !long_list && !unknown;
     trow[r] = live[r] ? id : 0;
     self[r] = u < n_dst;
   }
@@ -1468,10 +1483,11 @@ hipError_t launch_mean_backward(const int32_t* sizes, const int32_t* indptr, con
                                 int32_t* pos, const int32_t* place,
                                 uint32_t* scan_state, int2* csc, int32_t* long_rows, float* table, const int32_t* ids,
                                 int64_t num_nodes, float lr, const WgradArgs* defer, const ReduceArgs* fold,
-                                hipStream_t s) {
+                                float* report, hipStream_t s, int max_spins) {
   const EdgeView ev{indptr, local, place, cap_nnz, fanout};
-  // scan_state: the tile ticket, the long-row count, a pad word, then the
-  // look-back words
+  if (max_spins <= 0) max_spins = kLookbackSpins;
+  // scan_state: the tile ticket, the long-row count, a word for a wait that
+  // ran out, then the look-back words
   uint32_t* n_long = scan_state + kTicketWords;
   int32_t* cursors = place ? nullptr : pos;
   const int scan_blocks = static_cast<int>(csc_scan_tiles(cap_src));
@@ -1481,13 +1497,13 @@ hipError_t launch_mean_backward(const int32_t* sizes, const int32_t* indptr, con
   uint64_t* words = reinterpret_cast<uint64_t*>(n_long + 2);
   if (!defer)
     hipLaunchKernelGGL(k_csc_scan<0>, scan_grid, dim3(256), 0, s, sizes, cnt, off, cursors, scan_state, words,
-                       n_long, long_rows, scan_blocks, no_wg);
+                       n_long, long_rows, scan_blocks, max_spins, no_wg);
   else if (defer->vec)
     hipLaunchKernelGGL(k_csc_scan<1>, scan_grid, dim3(256), 0, s, sizes, cnt, off, cursors, scan_state, words,
-                       n_long, long_rows, scan_blocks, *defer);
+                       n_long, long_rows, scan_blocks, max_spins, *defer);
   else
     hipLaunchKernelGGL(k_csc_scan<2>, scan_grid, dim3(256), 0, s, sizes, cnt, off, cursors, scan_state, words,
-                       n_long, long_rows, scan_blocks, *defer);
+                       n_long, long_rows, scan_blocks, max_spins, *defer);
   const int64_t slots = std::max<int64_t>(cap_dst, 1) * std::max(fanout, 1);
   const int fill_blocks = static_cast<int>(grid_of(slots, 1 << 16));
   const ReduceArgs no_red{};
@@ -1500,7 +1516,7 @@ hipError_t launch_mean_backward(const int32_t* sizes, const int32_t* indptr, con
     const unsigned rows = grid_of((std::max<int64_t>(cap_src, 1) + kR - 1) / kR * kG, 1 << 30);
     hipLaunchKernelGGL((k_pull_update<kG, kR, kE>), dim3(rows + kLongGrid), dim3(256), 0, s, sizes, off, csc,
                        cap_nnz, dM, dH, d, table, ids, num_nodes, lr, static_cast<int>(rows), n_long,
-                       long_rows);
+                       long_rows, report);
     return hipGetLastError();
   }
   int G = 64;
@@ -1511,7 +1527,7 @@ hipError_t launch_mean_backward(const int32_t* sizes, const int32_t* indptr, con
   const unsigned rows = grid_of(std::max<int64_t>(cap_src, 1) * G, 1 << 30);
 #define GMB_PULL_T(GG, T)                                                                                      \
   hipLaunchKernelGGL((k_pull_mean<GG, T>), dim3(rows + kLongGrid), dim3(256), 0, s, sizes, off, csc, cap_nnz, dM, \
-                     static_cast<const T*>(out), d, dH, static_cast<int>(rows), n_long, long_rows)
+                     static_cast<const T*>(out), d, dH, static_cast<int>(rows), n_long, long_rows, report)
 #define GMB_PULL(GG) \
   if (out_bf16) GMB_PULL_T(GG, uint16_t); else GMB_PULL_T(GG, float)
   switch (G) {

@@ -77,11 +77,10 @@ hipError_t launch_dgrad(const int32_t*, const float*, int, int, const float*, co
 }
 int64_t csc_scan_tiles(int64_t cap_src) { return std::max<int64_t>(1, (cap_src + 1023) / 1024); }
 hipError_t launch_mean_backward(const int32_t*, const int32_t*, const int32_t*, int64_t, int32_t, const float*,
-                                const void*, int, int, float*, int64_t, int64_t, int32_t*, int32_t*, int32_t*, const int32_t*,
-                                uint32_t*,
-                                int2*, int32_t*, float*, const int32_t*, int64_t, float, const WgradArgs*,
-                                const ReduceArgs*, hipStream_t) {
-  return hipSuccess;
+                                const void*, int, int, float*, int64_t, int64_t, int32_t*, int32_t*, int32_t*,
+                                const int32_t*, uint32_t*, int2*, int32_t*, float*, const int32_t*, int64_t, float,
+                                const WgradArgs*, const ReduceArgs*, float* report, hipStream_t, int) {
+  return report ? hipSuccess : hipErrorInvalidValue;
 }
 hipError_t launch_sgd(const SgdArgs&, float, hipStream_t) { return hipSuccess; }
 hipError_t launch_widen(const WidenArgs&, hipStream_t) { return hipSuccess; }
