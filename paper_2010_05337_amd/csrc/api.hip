@@ -1012,7 +1012,7 @@ int run_backward(const gmb_blocks* blocks, const void* x, const gmb_sage_weights
     // in-edge counts per source on the way
     e = gmb::launch_dgrad(bk.sizes, cur, p.ldz[l], d_out, static_cast<const float*>(weights->w_self[l]),
                           static_cast<const float*>(weights->w_neigh[l]), d_in, other, dM, bk.cap_dst,
-                          bk.indices, bk.cap_nnz, cnt, place, s);
+                          bk.indptr, bk.indices, bk.cap_nnz, cnt, place, s);
     if (e != hipSuccess) return hip_fail(e, "input-gradient launch");
     // the mean's backward through the block's transpose, the ReLU of the
     // layer below on the way out: `other` becomes that layer's dZ; on layer

@@ -300,7 +300,8 @@ hipError_t launch_wgrad(const int32_t* sizes, const void* H, const void* M, int 
 // mean backward then takes no cursors).
 hipError_t launch_dgrad(const int32_t* sizes, const float* dZ, int ldz, int d_out, const float* ws,
                         const float* wn, int d_in, float* dH, float* dM, int64_t cap_rows,
-                        const int32_t* local, int64_t cap_nnz, int32_t* cnt, int32_t* place, hipStream_t s);
+                        const int32_t* indptr, const int32_t* local, int64_t cap_nnz, int32_t* cnt, int32_t* place,
+                        hipStream_t s);
 // look-back tiles of the transpose scan over cap_src sources; its state
 // (the tile ticket, the long-row count, the word that a wait which ran out
 // sets, then 2 words per tile) must start zeroed; long_rows holds cap_src ints

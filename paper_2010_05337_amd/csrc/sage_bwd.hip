@@ -555,9 +555,10 @@ __global__ __launch_bounds__(256) void k_wgrad_reduce(ReduceArgs r) { wgrad_redu
 
 // ---- input gradient -------------------------------------------------------
 
-// The transpose's edge count, an edge per thread and step of the grid.  With
-// `place` (blocks of many edges) a thread takes four edges per step (one
-// 16-byte read, four atomics in flight) and every edge keeps the number of edges counted before it for its source, to
+// The transpose's edge count, an edge per thread and step of the grid, over
+// the edges of the row offsets.  With `place` (blocks of many edges) a thread
+// takes four edges per step (one 16-byte read, four atomics in flight) and
+// every edge keeps the number of edges counted before it for its source, to
 // which the fill adds the source's offset, instead of taking a second round of
 // atomics on cursors: 547k edges, fill 17.3 -> 10.8 us and the scan, which has
 // no cursors to write, 14.0 -> 11.0.  Without it nothing waits for the atomics'
@@ -565,22 +566,28 @@ __global__ __launch_bounds__(256) void k_wgrad_reduce(ReduceArgs r) { wgrad_redu
 // of the 3-layer model 126 against 128 us).  Sources outside [0, n_src) are
 // skipped (only after a data error).
 struct CountArgs {
+  const int32_t* indptr;
   const int32_t* local;
   int64_t cap_nnz;
   int32_t* cnt;
   int32_t* place;   // [cap_nnz] or NULL
 };
-__device__ __forceinline__ void count_edges(const CountArgs& a, int32_t nnz, int32_t n_src, int64_t tid,
+__device__ __forceinline__ int32_t clamp_edge(int32_t e, int64_t cap_nnz) {
+  return e < 0 ? 0 : (e > cap_nnz ? static_cast<int32_t>(cap_nnz) : e);
+}
+
+__device__ __forceinline__ void count_edges(const CountArgs& a, int32_t n_dst, int32_t n_src, int64_t tid,
                                             int64_t threads) {
-  const int64_t n = nnz < a.cap_nnz ? nnz : a.cap_nnz;
+  const int32_t first = clamp_edge(a.indptr[0], a.cap_nnz);
+  const int64_t n = clamp_edge(a.indptr[n_dst], a.cap_nnz);
   if (!a.place) {   // uniform
-    for (int64_t e = tid; e < n; e += threads) {
+    for (int64_t e = first + tid; e < n; e += threads) {
       const int32_t u = a.local[e];
       if (u >= 0 && u < n_src) atomicAdd(&a.cnt[u], 1);
     }
     return;
   }
-  for (int64_t e0 = 4 * tid; e0 < n; e0 += 4 * threads) {
+  for (int64_t e0 = first + 4 * tid; e0 < n; e0 += 4 * threads) {
     int32_t u[4], at[4];
     if (e0 + 4 <= n) {
       __builtin_memcpy(u, a.local + e0, 16);
@@ -600,9 +607,10 @@ __device__ __forceinline__ void count_edges(const CountArgs& a, int32_t nnz, int
   }
 }
 
-// The block's edges as slots (v, j), j < fanout (a sampled row holds at
-// most fanout edges): slot (v, j) is edge indptr[v] + j if that is below
-// indptr[v+1] and cap_nnz.
+// The block's edges as slots (v, j), j < fanout: slot (v, j) holds the edges
+// indptr[v] + j, + fanout, ... below indptr[v+1] and cap_nnz.  A sampled row
+// holds at most fanout edges, so one; a row of a caller's own block may hold
+// more.  Rising row offsets give the edges of the count, each once.
 struct EdgeView {
   const int32_t* indptr;
   const int32_t* local;
@@ -614,26 +622,25 @@ struct EdgeView {
 __device__ __forceinline__ void edge_range(const EdgeView& ev, int64_t v, int32_t& b, int32_t& e) {
   b = ev.indptr[v];
   e = ev.indptr[v + 1];
-  b = b < 0 ? 0 : (b > ev.cap_nnz ? static_cast<int32_t>(ev.cap_nnz) : b);
-  e = e < b ? b : (e > ev.cap_nnz ? static_cast<int32_t>(ev.cap_nnz) : e);
+  b = clamp_edge(b, ev.cap_nnz);
+  e = e < b ? b : clamp_edge(e, ev.cap_nnz);
 }
 
-// Calls f(v, e, k_v) for every slot of the block that holds an edge e, slot
-// t = v * fanout + j over a grid-stride loop starting at t0.
+// Calls f(v, e, k_v) for every edge e of every slot t = v * fanout + j over a
+// grid-stride loop starting at t0.
 template <typename F>
 __device__ __forceinline__ void for_each_edge_slot(const EdgeView& ev, int32_t n_dst, int64_t t0, int64_t stride,
                                                    F&& f) {
-  if (ev.fanout < 1) return;
-  const int64_t total = static_cast<int64_t>(n_dst) * ev.fanout;
+  const int32_t fanout = ev.fanout < 1 ? 1 : ev.fanout;
+  const int64_t total = static_cast<int64_t>(n_dst) * fanout;
   for (int64_t t = t0; t < total; t += stride) {
     // (the slots number below 2^31 in every sampled block: a 32-bit division)
-    const int64_t v = total <= INT32_MAX ? static_cast<int64_t>(static_cast<uint32_t>(t) / static_cast<uint32_t>(ev.fanout))
-                                         : t / ev.fanout;
-    const int32_t j = static_cast<int32_t>(t - v * ev.fanout);
+    const int64_t v = total <= INT32_MAX ? static_cast<int64_t>(static_cast<uint32_t>(t) / static_cast<uint32_t>(fanout))
+                                         : t / fanout;
+    const int32_t j = static_cast<int32_t>(t - v * fanout);
     int32_t b, e;
     edge_range(ev, v, b, e);
-    if (b + j >= e) continue;
-    f(v, b + j, e - b);
+    for (int64_t at = static_cast<int64_t>(b) + j; at < e; at += fanout) f(v, static_cast<int32_t>(at), e - b);
   }
 }
 
@@ -780,7 +787,7 @@ __global__ __launch_bounds__(256) void k_dgrad(const int32_t* __restrict__ sizes
   }
   // the block's in-edge count per source, for the transpose (the next
   // kernel on the stream reads it)
-  count_edges(count, load_size(&sizes[kNnz]), load_size(&sizes[kNSrc]),
+  count_edges(count, M, load_size(&sizes[kNSrc]),
               (static_cast<int64_t>(blockIdx.y) * gridDim.x + blockIdx.x) * blockDim.x + threadIdx.x,
               static_cast<int64_t>(gridDim.x) * gridDim.y * blockDim.x);
 }
@@ -795,7 +802,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
 void k_dgrad_parts(const int32_t* __restrict__ sizes, parts::DgradOp op, CountArgs count) {
   const int32_t M = load_size(&sizes[kNDst]);
   parts::parts_gemm<parts::DgradOp, NCH, J, R, SPLIT, WAVES>(op, M);
-  count_edges(count, load_size(&sizes[kNnz]), load_size(&sizes[kNSrc]),
+  count_edges(count, M, load_size(&sizes[kNSrc]),
               (static_cast<int64_t>(blockIdx.y) * gridDim.x + blockIdx.x) * blockDim.x + threadIdx.x,
               static_cast<int64_t>(gridDim.x) * gridDim.y * blockDim.x);
 }
@@ -1429,8 +1436,9 @@ hipError_t launch_wgrad(const int32_t* sizes, const void* Hv, const void* Mv, in
 
 hipError_t launch_dgrad(const int32_t* sizes, const float* dZ, int ldz, int d_out, const float* ws,
                         const float* wn, int d_in, float* dH, float* dM, int64_t cap_rows,
-                        const int32_t* local, int64_t cap_nnz, int32_t* cnt, int32_t* place, hipStream_t s) {
-  const CountArgs count{local, cap_nnz, cnt, place};
+                        const int32_t* indptr, const int32_t* local, int64_t cap_nnz, int32_t* cnt, int32_t* place,
+                        hipStream_t s) {
+  const CountArgs count{indptr, local, cap_nnz, cnt, place};
   const uintptr_t align = reinterpret_cast<uintptr_t>(dZ) | reinterpret_cast<uintptr_t>(ws) |
                           reinterpret_cast<uintptr_t>(wn);
   const int nch32 = (d_out + 31) / 32;

@@ -72,7 +72,7 @@ hipError_t launch_wgrad(const int32_t*, const void*, const void*, int, int, cons
   return hipSuccess;
 }
 hipError_t launch_dgrad(const int32_t*, const float*, int, int, const float*, const float*, int, float*, float*,
-                        int64_t, const int32_t*, int64_t, int32_t*, int32_t*, hipStream_t) {
+                        int64_t, const int32_t*, const int32_t*, int64_t, int32_t*, int32_t*, hipStream_t) {
   return hipSuccess;
 }
 int64_t csc_scan_tiles(int64_t cap_src) { return std::max<int64_t>(1, (cap_src + 1023) / 1024); }
