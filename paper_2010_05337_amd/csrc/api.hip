@@ -82,12 +82,10 @@ constexpr int kTotalsWords = GMB_MAX_LAYERS;
 
 // The owners' LDS table size: kOwnerSlots, or a smaller power of two from
 // the environment variable GMB_OWNER_TABLE_SLOTS (64 .. kOwnerSlots), a test
-// hook that makes owners overflow into the state table so that path runs on
-// small inputs.  While it is set the last hop dedups by owners whatever its
-// size.
-const char* owner_hook() { return std::getenv("GMB_OWNER_TABLE_SLOTS"); }
+// hook that makes owners overflow into the state table.  It changes nothing
+// else: the plan does not look at it.
 int32_t owner_slots() {
-  const char* v = owner_hook();
+  const char* v = std::getenv("GMB_OWNER_TABLE_SLOTS");
   if (!v) return gmb::kOwnerSlots;
   const long x = std::strtol(v, nullptr, 10);
   int32_t slots = 64;
@@ -103,7 +101,6 @@ int32_t owner_slots() {
 // 57.7, 507 k 65.7 / 62.6, 990 k 87.8 / 75.5 us; the line is drawn below the
 // crossing, since a larger graph's table spreads over more lines.
 constexpr int64_t kTableLastNnz = 262144;
-
 
 // Fills the plan; returns GMB_OK or an argument error (message set).
 int plan_sampling(int32_t num_seeds, const int32_t* fanouts, int32_t num_layers, int64_t num_nodes,
@@ -143,7 +140,7 @@ int plan_sampling(int32_t num_seeds, const int32_t* fanouts, int32_t num_layers,
     hp.items = gmb::scan_items_for(hp.cap_nnz);
     const bool last = h + 1 == num_layers;
     hp.table = hp.fanout <= 64 && (h == 0 || p.hop[h - 1].table) &&
-               (!last || (hp.cap_nnz <= kTableLastNnz && !owner_hook()));
+               (!last || hp.cap_nnz <= kTableLastNnz);
     if (hp.table) {
       hp.tile_stride = gmb::scan_tiles(hp.cap_nnz, hp.items);
     } else {

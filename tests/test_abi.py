@@ -97,6 +97,16 @@ def test_workspace_bytes_and_caps(L):
     assert b >= a
 
 
+@pytest.mark.parametrize("slots", ["64", "8192"])
+def test_owner_table_hook_leaves_the_plan_alone(L, slots, monkeypatch):
+    """The limit on the owners' LDS tables is no part of the plan: a workspace
+    sized without it serves a call with it, and the other way round."""
+    shapes = [(64, _fo(5, 5), 2, 10000), (1000, _fo(15, 10, 5), 3, 2449029), (300, _fo(70), 1, 3000)]
+    plain = [L.gmb_sample_workspace_bytes(*s) for s in shapes]
+    monkeypatch.setenv("GMB_OWNER_TABLE_SLOTS", slots)
+    assert [L.gmb_sample_workspace_bytes(*s) for s in shapes] == plain
+
+
 def test_sample_blocks_rejects_bad_arguments_on_host(L):
     import paper_2010_05337_amd as gmb
     fake = ctypes.c_void_p(1 << 20)   # never dereferenced: every case fails validation first

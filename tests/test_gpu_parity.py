@@ -364,11 +364,12 @@ def test_forward_fused_hubs(orc, dg):
     _fused_case(orc, dg, g, feats, w, seeds.astype(np.int32), [25, 10], 66, TOL_BF16)
 
 
-@pytest.mark.parametrize("fanouts, num_seeds", [([12, 8, 5], 3000), ([70], 300), ([6, 30], 800)])
+@pytest.mark.parametrize("fanouts, num_seeds", [([12, 8, 5], 3000), ([70], 300), ([6, 70], 800), ([10, 30], 1500)])
 def test_owner_overflow_path(orc, dg, fanouts, num_seeds, monkeypatch):
     """An owner whose vertices do not fit its LDS table redoes its pairs
     through the state's per-vertex table: forced here with a 64-slot limit
-    (the test hook GMB_OWNER_TABLE_SLOTS), every block must still equal the
+    (the test hook GMB_OWNER_TABLE_SLOTS) on hops that the owners take (an
+    edge capacity above 2^18, or a fan-out above 64 here or before), every block must still equal the
     oracle's, repeated seeds must still be reported, and the table must be
     clear afterwards."""
     monkeypatch.setenv("GMB_OWNER_TABLE_SLOTS", "64")
@@ -403,7 +404,7 @@ def test_validation_mode_passes_on_real_blocks(orc, dg, tiny, monkeypatch):
         gpu_blocks(csr, seeds, fo, 7)
         csr.check_status()
     monkeypatch.setenv("GMB_OWNER_TABLE_SLOTS", "64")
-    gpu_blocks(csr, seeds, [12, 8], 8)
+    gpu_blocks(csr, seeds, [12, 70], 8)
     csr.check_status()
 
 

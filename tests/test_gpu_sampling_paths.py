@@ -1,6 +1,6 @@
 """The sampler's kernels at the sizes where their dispatch changes: the last
-hop through the state's table or through owners (forced on small inputs with
-GMB_OWNER_TABLE_SLOTS), every group width of the fan-out, one seed, tile and
+hop through the state's table or through owners (on small inputs: after a
+first hop of a fan-out above 64), every group width of the fan-out, one seed, tile and
 router remainders, and the edge capacity at which the last hop changes its
 dedup.  Every block must equal the oracle's bit for bit, and the state must
 be clear afterwards."""
@@ -26,9 +26,9 @@ def graph(dg):
 @pytest.mark.parametrize("fanouts, num_seeds", [
     ([1], 1), ([8], 257), ([9, 3], 33), ([17, 16], 255), ([4, 32], 64), ([33, 2], 100), ([64], 513),
     ([15, 10, 5], 97), ([3, 1, 4, 2], 300)])
-def test_dedup_paths_bitexact(orc, dg, graph, fanouts, num_seeds, owners, monkeypatch):
-    if owners:
-        monkeypatch.setenv("GMB_OWNER_TABLE_SLOTS", "8192")
+def test_dedup_paths_bitexact(orc, dg, graph, fanouts, num_seeds, owners):
+    if owners:   # every hop after a fan-out that the table sampler does not take
+        fanouts = fanouts + [65]
     for wide in (False, True):
         print(f"fanouts {fanouts}, {num_seeds} seeds, owners {owners}, wide {wide}", flush=True)
         csr = csr_on_device(graph, wide)
