@@ -723,9 +723,12 @@ bool launch_parts_op(const int32_t* sizes, const Op& op, int nch, int64_t cap_ro
 }
 
 // bf16 with the weight slab resident in LDS, on v_mfma_f32_16x16x32_bf16.
-// A workgroup of eight waves owns BN = 16 J output columns and keeps those
-// columns of [W_self; W_neigh] in LDS; it walks over tiles of 128 rows (16 per
-// wave), persistent, the next tile's A reads issued as soon as each chunk's
+// A workgroup of eight waves (four above d_in 384: a lane's A operands alone
+// take 128 or 160 registers there, and with eight waves, 256 registers each,
+// the loop spilled 132 to 436 bytes a lane: 60k rows, 2 x 640 -> 256 543 -> 193
+// us, 2 x 512 -> 256 187 -> 125) owns BN = 16 J output columns and keeps those
+// columns of [W_self; W_neigh] in LDS; it walks over tiles of 16 rows per wave,
+// persistent, the next tile's A reads issued as soon as each chunk's
 // products are.  The reduction runs over groups of eight k: `gh` groups of
 // h_v, then gh of the mean, gh = ceil(d_in / 8); chunk c takes the groups 4c
 // + q, q = lane / 16.  Group g of a half starts at k = 8 g, the last one at
@@ -736,7 +739,8 @@ bool launch_parts_op(const int32_t* sizes, const Op& op, int nch, int64_t cap_ro
 // Operand order: the slab holds Bp[(g * BN + n) * 8 + s] = W[k(g) + s][n],
 // one 16-byte LDS read per lane, chunk and column subtile.  W goes in as the
 // first operand, so lane (q, i) ends with out[row i][16 j + 4 q .. + 3]: four
-// adjacent columns, one 8- or 16-byte store where N allows it.
+// adjacent columns, one 8- or 16-byte store (misaligned where N % 4 != 0, which
+// global stores may be), 2- or 4-byte stores in the last columns of such an N.
 //
 // The fill: an item is eight k of four adjacent columns, eight 8-byte loads
 // (N % 4 == 0) transposed by byte permutes into four 16-byte LDS words.
@@ -747,8 +751,7 @@ bool launch_parts_op(const int32_t* sizes, const Op& op, int nch, int64_t cap_ro
 // output at 41k rows (42 MB: 15.0 us, 2.8 TB/s; 33.0 us before, with four
 // waves and the 2-byte fill), latency at few rows: 4000 rows, 2 x 256 -> 47
 // 20.0 -> 11.9 us, 1000 rows, 2 x 256 -> 172 20.4 -> 8.9 us.
-constexpr int kBf16Waves = 8;
-constexpr int kBf16Rows = 16 * kBf16Waves;
+constexpr int bf16_waves(int nch) { return nch > 24 ? 4 : 8; }
 
 constexpr int bf16_slab_bytes(int nch, int j) { return nch * 4 * 16 * j * 8 * 2; }
 
@@ -759,17 +762,19 @@ __device__ __forceinline__ uint4 load16_any(const uint16_t* p) {
 }
 
 template <int NCH, int J>
-__global__ __launch_bounds__(64 * kBf16Waves) void k_linear_bf16_slab(
+__global__ __launch_bounds__(64 * bf16_waves(NCH)) void k_linear_bf16_slab(
     const int32_t* sizes, const uint16_t* __restrict__ Hs, const uint16_t* __restrict__ Ag,
     const uint16_t* __restrict__ Ws, const uint16_t* __restrict__ Wn, const float* __restrict__ bias, int d_in, int N,
-    int relu, int out_f32, int avec, int wquad, int ovec, void* __restrict__ out) {
+    int relu, int out_f32, int avec, int wquad, void* __restrict__ out) {
   constexpr int BN = 16 * J;
-  constexpr int THREADS = 64 * kBf16Waves;
+  constexpr int THREADS = 64 * bf16_waves(NCH);
+  constexpr int ROWS = 16 * bf16_waves(NCH);
   constexpr int GROUPS = NCH * 4;
   __shared__ __attribute__((aligned(16))) uint16_t Bp[GROUPS * BN * 8];
-  __shared__ __attribute__((aligned(16))) float s_bias[BN];
+  constexpr bool kBiasLds = bf16_slab_bytes(NCH, J) + 4 * BN <= 160 * 1024;   // (the widest slab fills the LDS)
+  __shared__ __attribute__((aligned(16))) float s_bias[kBiasLds ? BN : 4];
   const int32_t M = load_size(&sizes[kNDst]);
-  const int row_tiles = (M + kBf16Rows - 1) / kBf16Rows;
+  const int row_tiles = (M + ROWS - 1) / ROWS;
   if (static_cast<int>(blockIdx.x) >= row_tiles) return;
   const int n0 = blockIdx.y * BN;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -784,7 +789,7 @@ __global__ __launch_bounds__(64 * kBf16Waves) void k_linear_bf16_slab(
   };
   // A: issue the read of chunk c of this lane's row; finish after use is near
   auto tile_rows = [&](int rt, const uint16_t*& hrow, const uint16_t*& grow) {
-    const int row = rt * kBf16Rows + wave * 16 + r16;
+    const int row = rt * ROWS + wave * 16 + r16;
     const int64_t arow = row < M ? row : M - 1;   // a row past the end is not stored
     hrow = Hs + arow * d_in;
     grow = Ag + arow * d_in;
@@ -877,7 +882,8 @@ __global__ __launch_bounds__(64 * kBf16Waves) void k_linear_bf16_slab(
       dst[3] = pack([&](int i) { return v[u][i].y; }, 0x07060302u);
     }
   }
-  for (int i = threadIdx.x; i < BN; i += THREADS) s_bias[i] = bias[n0 + i < N ? n0 + i : N - 1];
+  if constexpr (kBiasLds)
+    for (int i = threadIdx.x; i < BN; i += THREADS) s_bias[i] = bias[n0 + i < N ? n0 + i : N - 1];
   if constexpr (!kEarlyA) first_a();
   __syncthreads();
   for (int rt = blockIdx.x; rt < row_tiles; rt += gridDim.x) {
@@ -913,27 +919,29 @@ __global__ __launch_bounds__(64 * kBf16Waves) void k_linear_bf16_slab(
       for (int j = 0; j < J; ++j) acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[j], x, acc[j], 0, 0, 0);
       if (more) a[c] = load_frag(hnext, gnext, c, ql);
     }
-    const int row = rt * kBf16Rows + wave * 16 + r16;
+    const int row = rt * ROWS + wave * 16 + r16;
     if (row < M) {
 #pragma unroll
       for (int j = 0; j < J; ++j) {
         const int col = n0 + j * 16 + 4 * q;
-        const float4 b4 = *reinterpret_cast<const float4*>(&s_bias[j * 16 + 4 * q]);
-        float z[4] = {acc[j][0] + b4.x, acc[j][1] + b4.y, acc[j][2] + b4.z, acc[j][3] + b4.w};
+        float z[4];
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
+        for (int r = 0; r < 4; ++r) {
+          z[r] = acc[j][r];
+          if constexpr (kBiasLds) z[r] += s_bias[j * 16 + 4 * q + r];
+          else z[r] += bias[col + r < N ? col + r : N - 1];
           if (relu) z[r] = z[r] > 0.f ? z[r] : 0.f;
+        }
         const int64_t o = static_cast<int64_t>(row) * N + col;
-        if (ovec) {   // uniform: N % 4 == 0 and the output aligned to four values
-          if (col < N) {
-            if (out_f32) {
-              *reinterpret_cast<float4*>(static_cast<float*>(out) + o) = make_float4(z[0], z[1], z[2], z[3]);
-            } else {
-              uint2 p;
-              p.x = f32_to_bf16(z[0]) | (static_cast<uint32_t>(f32_to_bf16(z[1])) << 16);
-              p.y = f32_to_bf16(z[2]) | (static_cast<uint32_t>(f32_to_bf16(z[3])) << 16);
-              *reinterpret_cast<uint2*>(static_cast<uint16_t*>(out) + o) = p;
-            }
+        if (col + 4 <= N) {
+          if (out_f32) {
+            const float4 p = make_float4(z[0], z[1], z[2], z[3]);
+            __builtin_memcpy(static_cast<float*>(out) + o, &p, 16);
+          } else {
+            uint2 p;
+            p.x = f32_to_bf16(z[0]) | (static_cast<uint32_t>(f32_to_bf16(z[1])) << 16);
+            p.y = f32_to_bf16(z[2]) | (static_cast<uint32_t>(f32_to_bf16(z[3])) << 16);
+            __builtin_memcpy(static_cast<uint16_t*>(out) + o, &p, 8);
           }
         } else {
 #pragma unroll
@@ -955,31 +963,43 @@ void launch_bf16_slab(const int32_t* sizes, const uint16_t* hs, const uint16_t* 
   constexpr int BN = 16 * J;
   constexpr int per_cu = bf16_slab_bytes(NCH, J) <= 72 * 1024 ? kSlabBlocksBf16 : 1;
   const int col_tiles = (N + BN - 1) / BN;
-  int64_t rows = (cap_rows + kBf16Rows - 1) / kBf16Rows;
+  constexpr int ROWS = 16 * bf16_waves(NCH);
+  int64_t rows = (cap_rows + ROWS - 1) / ROWS;
   const int64_t want = (kComputeUnits * per_cu + col_tiles - 1) / col_tiles;
   if (rows > want) rows = want;
   if (rows < 1) rows = 1;
   const int avec = K % 8 == 0 && (reinterpret_cast<uintptr_t>(hs) | reinterpret_cast<uintptr_t>(ag)) % 16 == 0;
   const int wquad = N % 4 == 0 && (reinterpret_cast<uintptr_t>(ws) | reinterpret_cast<uintptr_t>(wn)) % 8 == 0;
-  const int ovec = N % 4 == 0 && reinterpret_cast<uintptr_t>(out) % (out_f32 ? 16 : 8) == 0;
   hipLaunchKernelGGL((k_linear_bf16_slab<NCH, J>), dim3(static_cast<unsigned>(rows), col_tiles),
-                     dim3(64 * kBf16Waves), 0, s, sizes, hs, ag, ws, wn, bias, K, N, relu, out_f32, avec, wquad, ovec,
+                     dim3(64 * bf16_waves(NCH)), 0, s, sizes, hs, ag, ws, wn, bias, K, N, relu, out_f32, avec, wquad,
                      out);
 }
 
 // The column width: as wide as the LDS allows (an A row is read once per
-// column tile) while the tiles at capacity still give every CU a workgroup.
+// column tile) while the tiles at capacity still give every CU a workgroup,
+// and no wider than N needs (60k rows, 2 x 16 -> 47: 17.0 us with 128 columns
+// and 4-byte stores, 13.2 with 64).  Where the next narrower width has a few
+// more tiles than CUs, its last ones run as a round of their own, and somewhat
+// fewer wide tiles are faster: 4000 rows, 2 x 256 -> 172, 352 tiles of 16 columns
+// 18.6 us, 192 of 32 13.2 (the mean's kernel, about 4 us, in both); 376 narrow
+// ones are faster than 188 wide ones (12k rows, 2 x 128 -> 256): 15.0 against 16.1.
 template <int NCH>
 void launch_bf16_slab_for(const int32_t* sizes, const uint16_t* hs, const uint16_t* ag, const uint16_t* ws,
                           const uint16_t* wn, const float* bias, int K, int N, int relu, int out_f32, void* out,
                           int64_t cap_rows, hipStream_t s) {
-  const int64_t row_tiles = (cap_rows + kBf16Rows - 1) / kBf16Rows;
-  auto enough = [&](int j) { return row_tiles * ((N + 16 * j - 1) / (16 * j)) >= kComputeUnits; };
+  constexpr int ROWS = 16 * bf16_waves(NCH);
+  const int64_t row_tiles = (cap_rows + ROWS - 1) / ROWS;
+  auto tiles = [&](int j) { return row_tiles * ((N + 16 * j - 1) / (16 * j)); };
+  auto enough = [&](int j) {
+    if (N <= 8 * j) return false;   // half the width holds every column
+    if (tiles(j) >= kComputeUnits) return true;
+    return bf16_slab_bytes(NCH, j) <= 72 * 1024 && 16 * tiles(j) >= 9 * kComputeUnits &&
+           tiles(j / 2) > kComputeUnits && 5 * tiles(j / 2) <= 7 * kComputeUnits;
+  };
 #define GMB_SLAB16_J(JJ) launch_bf16_slab<NCH, JJ>(sizes, hs, ag, ws, wn, bias, K, N, relu, out_f32, out, cap_rows, s)
   if constexpr (NCH <= 16)
     if (enough(8)) return GMB_SLAB16_J(8);
-  if constexpr (NCH <= 32)
-    if (enough(4)) return GMB_SLAB16_J(4);
+  if (enough(4)) return GMB_SLAB16_J(4);
   if (enough(2)) return GMB_SLAB16_J(2);
   GMB_SLAB16_J(1);
 #undef GMB_SLAB16_J

@@ -22,7 +22,10 @@ def graph(dg):
 
 @pytest.mark.parametrize("d_in, d_out, rows", [
     (8, 5, 1), (9, 7, 127), (75, 41, 300), (33, 130, 4000), (250, 255, 17001), (128, 256, 17000), (31, 64, 9000),
-    (256, 172, 1000), (320, 47, 5000), (513, 10, 200)])
+    (256, 172, 1000), (320, 47, 5000), (513, 10, 200),
+    # four waves per workgroup; a slab that leaves no LDS for the bias; a wide
+    # tile of fewer tiles than CUs; no wider than the columns
+    (640, 256, 17000), (602, 47, 20000), (640, 13, 65), (512, 172, 4000), (16, 47, 30000), (24, 16, 30000)])
 def test_linear_bf16_widths(orc, dg, graph, d_in, d_out, rows):
     """One layer of d_in -> d_out over `rows` destinations (the 2e-2 of every
     bf16 forward: the mean is rounded to bf16)."""
@@ -30,6 +33,19 @@ def test_linear_bf16_widths(orc, dg, graph, d_in, d_out, rows):
     feats = dg.features(graph.num_nodes, d_in, 5, "bf16")
     w = dg.sage_weights([d_in, d_out], 6, "bf16")
     _forward_case(orc, dg, graph, feats, w, dg.permutation(graph.num_nodes, 7)[:rows], [5], 8, TOL_BF16)
+
+
+@pytest.mark.parametrize("dims", [[33, 47, 9], [640, 255, 41], [16, 26, 21]])
+def test_bf16_hidden_rows_of_any_width(orc, dg, graph, dims):
+    """bf16 rows whose width four does not divide: misaligned stores of four
+    columns, the last columns one by one, nothing past a row's end.  (Of 640 ->
+    255 -> 6, the rounding of the means and hidden rows alone, taken in 64 bits,
+    moves one row whose six logits are all near zero by 2.6e-2; of 41 columns by
+    less than 1e-2.  Narrow hidden rows do the same.)"""
+    print(f"bf16 hidden {dims}", flush=True)
+    feats = dg.features(graph.num_nodes, dims[0], 5, "bf16")
+    w = dg.sage_weights(dims, 6, "bf16")
+    _forward_case(orc, dg, graph, feats, w, dg.permutation(graph.num_nodes, 7)[:700], [5, 4], 8, TOL_BF16)
 
 
 @pytest.mark.parametrize("d_in, d_out, rows", [
