@@ -103,6 +103,7 @@ struct LinearOp {
   static constexpr bool kQuadCapable = true;
   static constexpr bool kEarlyA = true;   // the first tile's A loads overlap the slab's
   static constexpr bool kFixA = false;    // A's values need no masking
+  static constexpr bool kByChunk = false;
   __host__ __device__ int n() const { return N; }
   __host__ __device__ int64_t ldo() const { return N; }
   __device__ void a_rows(int64_t row, const float*& p0, const float*& p1) const {
@@ -169,6 +170,7 @@ struct LinearAnyOp {
   static constexpr bool kQuadCapable = true;
   static constexpr bool kEarlyA = true;
   static constexpr bool kFixA = true;
+  static constexpr bool kByChunk = false;
   __host__ __device__ int n() const { return N; }
   __host__ __device__ int64_t ldo() const { return N; }
   // first k of group g within its half; half: 0 h_v, 1 the mean, -1 past both
@@ -239,6 +241,14 @@ struct LinearAnyOp {
   __device__ float* out_at(int64_t row, int col) const { return out + row * N + col; }
 };
 
+// The same with every chunk's products summed from zero and the chunks' sums
+// then added in order, as the split form adds its waves': the split form's
+// results bit for bit on 128-row tiles.  (One sum through all chunks has 1.3 to
+// 1.8 times the error, and up to a fifth less time.)
+struct LinearAnyChunkOp : LinearAnyOp {
+  static constexpr bool kByChunk = true;
+};
+
 // The input gradient: A = dZ (d_out columns, row stride ldz), B = [W_self;
 // W_neigh]^T (B[k][nn] = W[nn][k], 2 d_in columns), the result's columns
 // nn < d_in to dH and the others to dM (row stride d_in each).
@@ -246,6 +256,7 @@ struct DgradOp {
   static constexpr bool kQuadCapable = false;   // its eight k are one contiguous run already
   static constexpr bool kEarlyA = false;        // (the largest tiling has no registers to spare for it)
   static constexpr bool kFixA = false;
+  static constexpr bool kByChunk = false;
   const float* dZ;
   const float* Ws;
   const float* Wn;
@@ -496,10 +507,15 @@ __device__ __forceinline__ void parts_gemm(const Op& op, int32_t M) {
 #pragma unroll
     for (int f = 0; f < R; ++f) frag_rows(rt + gridDim.x, f, hr[f], gr[f]);
     floatx4 acc[R][J];
+    auto clear_acc = [&]() {
 #pragma unroll
-    for (int f = 0; f < R; ++f)
+      for (int f = 0; f < R; ++f)
 #pragma unroll
-      for (int j = 0; j < J; ++j) acc[f][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+        for (int j = 0; j < J; ++j) acc[f][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+    };
+    clear_acc();
+    constexpr bool kByChunk = Op::kByChunk && SPLIT == 1;
+    floatx4 total[kByChunk ? R : 1][kByChunk ? J : 1];
     auto load_b = [&](int i, bf16x8 (&b)[3][J]) {
       const int c = chunk_of(i);
       const int cc = c < NCH ? c : NCH - 1;
@@ -546,6 +562,7 @@ __device__ __forceinline__ void parts_gemm(const Op& op, int32_t M) {
 #pragma unroll
         for (int f = 0; f < R; ++f) cut_a(a[f][i + 1][0], a[f][i + 1][1], i + 1, pn[f]);
       }
+      if (kByChunk && i > 0) clear_acc();
       if (chunk_of(i) < NCH) {   // uniform: depends on the wave index only
 #pragma unroll
         for (int f = 0; f < R; ++f) {
@@ -570,6 +587,12 @@ __device__ __forceinline__ void parts_gemm(const Op& op, int32_t M) {
       for (int m = 0; m < 6 * R * J; ++m) {
         __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
         __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);
+      }
+      if constexpr (kByChunk) {
+#pragma unroll
+        for (int f = 0; f < R; ++f)
+#pragma unroll
+          for (int j = 0; j < J; ++j) total[f][j] = i == 0 ? acc[f][j] : total[f][j] + acc[f][j];
       }
       // the A values of chunk i + 1 are cut: its registers take the next
       // tile's chunk i + 1 (chunk 0 was reloaded before the loop)
@@ -607,13 +630,15 @@ __device__ __forceinline__ void parts_gemm(const Op& op, int32_t M) {
 #pragma unroll
       for (int f = 0; f < R; ++f)
 #pragma unroll
-        for (int j = 0; j < J; ++j) held[f][j] = acc[f][j];
+        for (int j = 0; j < J; ++j) {
+          if constexpr (kByChunk) held[f][j] = total[f][j];
+          else held[f][j] = acc[f][j];
+        }
     }
     held_rt = rt;
   }
   store_held();
 }
-
 
 // Grid of a part-product launch: row tiles of the persistent grid, column tiles.
 template <int J, int R, int SPLIT, int WAVES>
@@ -622,8 +647,10 @@ inline dim3 parts_grid(int64_t cap_rows, int N) {
   constexpr int ROWS = SPLIT > 1 ? 16 * R : 16 * WAVES * R;
   const int col_tiles = (N + BN - 1) / BN;
   int64_t rows = (cap_rows + ROWS - 1) / ROWS;
-  // one workgroup per CU (the LDS holds one slab), the grid covering the chip once
-  const int64_t want = (256 + col_tiles - 1) / col_tiles;
+  // one workgroup per CU (the LDS holds one slab), the grid covering the chip
+  // at most once: with 43 row tiles by 6 column tiles the last two workgroups
+  // were a round of their own (16k rows, 2 x 75 -> 172: 50.7 us, 32.6 with 42)
+  const int64_t want = 256 / col_tiles;
   if (rows > want) rows = want;
   if (rows < 1) rows = 1;
   return dim3(static_cast<unsigned>(rows), col_tiles);

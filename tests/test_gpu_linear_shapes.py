@@ -62,6 +62,32 @@ def test_linear_f32_widths(orc, dg, graph, d_in, d_out, rows):
     assert max(errs) <= 5e-6, errs
 
 
+@pytest.mark.parametrize("d_in, d_out", [(9, 47), (16, 33), (17, 100), (31, 255), (33, 64), (63, 172), (64, 47)])
+def test_linear_f32_tilings_agree(dg, graph, d_in, d_out):
+    """The same rows in batches on either side of the line between the split
+    tiles and the 128-row tiles: the same bits (d_in 16 and 64 by rows that are
+    not 16-byte aligned)."""
+    print(f"f32 {d_in} -> {d_out}", flush=True)
+    cols = (d_out + 31) // 32
+    rows = 16 * (1500 // cols + 1) + 5
+    csr = csr_on_device(graph)
+    w = to_torch_weights(dg.sage_weights([d_in, d_out], 6))
+    seeds = torch.from_numpy(dg.permutation(graph.num_nodes, 7)[:rows]).cuda()
+
+    def forward(s):
+        blocks = gmb.sample_blocks(csr, s, [5], 8)
+        x = gmb.gather_features(blocks, feats)
+        odd = torch.empty(x.numel() + 1, device="cuda")[1:].view(x.shape)
+        odd.copy_(x)
+        return gmb.sage_forward(blocks, odd, w)
+    feats = to_torch_feats(dg.features(graph.num_nodes, d_in, 5, "f32"))
+    whole = forward(seeds)
+    part = rows // 7
+    for at in range(0, rows, part):
+        assert torch.equal(whole[at:at + part], forward(seeds[at:at + part].contiguous())), at
+    csr.check_status()
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("d_in", [9, 75, 101])
 def test_linear_infinities_stay_in_their_element(dg, graph, dtype, d_in):
