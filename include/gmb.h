@@ -269,8 +269,12 @@ int64_t gmb_forward_hidden_offset(const gmb_blocks* blocks, const gmb_sage_weigh
  *           256-byte aligned.
  * Per layer: the mean of the sampled in-neighbours' rows (0 for a vertex
  * with none) accumulated in fp32, then the two products and the bias in
- * one matrix-core GEMM with fp32 accumulation.  In bf16 mode the mean and
- * the hidden activations are rounded to bf16 before the next product.
+ * one matrix-core GEMM with fp32 accumulation.  In fp32 mode, where d_in and
+ * the rows allow it, every operand is cut exactly into three bf16 parts and a
+ * product is the sum of six of the nine part products (eight at some widths);
+ * what is left out is below 2^-21 of the product, and the results' error is of
+ * the order of an fp32 sum's.  In bf16 mode the mean and the hidden activations
+ * are rounded to bf16 before the next product.
  * An empty batch (num_seeds == 0) has no rows in any layer: nothing is
  * enqueued, and x and logits may be NULL. */
 int gmb_sage_forward(const gmb_blocks* blocks, const void* x, const gmb_sage_weights* weights,

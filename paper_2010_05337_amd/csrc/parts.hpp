@@ -103,7 +103,8 @@ struct LinearOp {
   static constexpr bool kQuadCapable = true;
   static constexpr bool kEarlyA = true;   // the first tile's A loads overlap the slab's
   static constexpr bool kFixA = false;    // A's values need no masking
-  static constexpr bool kByChunk = false;
+  static constexpr bool kByChunk = false; // one sum through all chunks
+  static constexpr bool kEight = false;   // six part products whatever the number of chunks
   __host__ __device__ int n() const { return N; }
   __host__ __device__ int64_t ldo() const { return N; }
   __device__ void a_rows(int64_t row, const float*& p0, const float*& p1) const {
@@ -158,6 +159,18 @@ struct LinearOp {
 // read of A is 16 bytes inside the row, misaligned where d_in % 4 != 0 (global
 // reads may be).  75 -> 100 on 2.6k rows: 27.6 us on the general kernel, 5.3
 // here.  Infinite operands give what that kernel gave (plain).
+//
+// Precision: these widths ran in fp32 before (k_linear_f32), and six of the nine
+// part products in one sum per entry, as LinearOp takes them, are further off
+// than that on rows with many zeros (ReLU outputs, widths 10 to 127: 1.02 to
+// 1.19 times its error against 64 bits).  So every chunk's products are summed
+// from zero and the chunks' sums then added in order (kByChunk; the split form
+// sums its waves' so anyway, with the same bits), and up to two chunks two more
+// products are taken (kEight; the ninth is below 2^-32 of the product).  The
+// error is then 0.3 to 0.83 times the fp32 kernel's on normal, positive and
+// ReLU rows of widths 9 to 127; 60k rows, 2 x 19 -> 255 30.4 -> 32.2 us, 2 x 127
+// -> 255 75 as before (the chunks' sums take the registers of the tile before,
+// stored first).
 struct LinearAnyOp {
   const float* Hs;
   const float* Ag;
@@ -170,7 +183,8 @@ struct LinearAnyOp {
   static constexpr bool kQuadCapable = true;
   static constexpr bool kEarlyA = true;
   static constexpr bool kFixA = true;
-  static constexpr bool kByChunk = false;
+  static constexpr bool kByChunk = true;
+  static constexpr bool kEight = true;
   __host__ __device__ int n() const { return N; }
   __host__ __device__ int64_t ldo() const { return N; }
   // first k of group g within its half; half: 0 h_v, 1 the mean, -1 past both
@@ -241,14 +255,6 @@ struct LinearAnyOp {
   __device__ float* out_at(int64_t row, int col) const { return out + row * N + col; }
 };
 
-// The same with every chunk's products summed from zero and the chunks' sums
-// then added in order, as the split form adds its waves': the split form's
-// results bit for bit on 128-row tiles.  (One sum through all chunks has 1.3 to
-// 1.8 times the error, and up to a fifth less time.)
-struct LinearAnyChunkOp : LinearAnyOp {
-  static constexpr bool kByChunk = true;
-};
-
 // The input gradient: A = dZ (d_out columns, row stride ldz), B = [W_self;
 // W_neigh]^T (B[k][nn] = W[nn][k], 2 d_in columns), the result's columns
 // nn < d_in to dH and the others to dM (row stride d_in each).
@@ -257,6 +263,7 @@ struct DgradOp {
   static constexpr bool kEarlyA = false;        // (the largest tiling has no registers to spare for it)
   static constexpr bool kFixA = false;
   static constexpr bool kByChunk = false;
+  static constexpr bool kEight = false;
   const float* dZ;
   const float* Ws;
   const float* Wn;
@@ -568,6 +575,12 @@ __device__ __forceinline__ void parts_gemm(const Op& op, int32_t M) {
         for (int f = 0; f < R; ++f) {
           const bf16x8 (&ap)[3] = pc[f];
           // the smallest part products first
+          if constexpr (Op::kEight && NCH <= 2) {
+#pragma unroll
+            for (int j = 0; j < J; ++j) acc[f][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ap[1], bc[2][j], acc[f][j], 0, 0, 0);
+#pragma unroll
+            for (int j = 0; j < J; ++j) acc[f][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ap[2], bc[1][j], acc[f][j], 0, 0, 0);
+          }
 #pragma unroll
           for (int j = 0; j < J; ++j) acc[f][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ap[0], bc[2][j], acc[f][j], 0, 0, 0);
 #pragma unroll
@@ -588,12 +601,6 @@ __device__ __forceinline__ void parts_gemm(const Op& op, int32_t M) {
         __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
         __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);
       }
-      if constexpr (kByChunk) {
-#pragma unroll
-        for (int f = 0; f < R; ++f)
-#pragma unroll
-          for (int j = 0; j < J; ++j) total[f][j] = i == 0 ? acc[f][j] : total[f][j] + acc[f][j];
-      }
       // the A values of chunk i + 1 are cut: its registers take the next
       // tile's chunk i + 1 (chunk 0 was reloaded before the loop)
       if (i + 1 < MYCH) {
@@ -604,7 +611,14 @@ __device__ __forceinline__ void parts_gemm(const Op& op, int32_t M) {
           a[f][i + 1][1] = load4(hr[f], gr[f], k + 4);
         }
       }
-      if (i == MYCH / 2) store_held();
+      // (kByChunk: at once, so that `total` takes its registers)
+      if (i == (kByChunk ? 0 : MYCH / 2)) store_held();
+      if constexpr (kByChunk) {
+#pragma unroll
+        for (int f = 0; f < R; ++f)
+#pragma unroll
+          for (int j = 0; j < J; ++j) total[f][j] = i == 0 ? acc[f][j] : total[f][j] + acc[f][j];
+      }
     }
     if constexpr (SPLIT > 1) {
       // partials of the waves -> LDS; thread t then holds the entries

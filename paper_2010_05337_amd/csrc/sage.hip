@@ -693,11 +693,11 @@ void launch_parts(const int32_t* sizes, const Op& op, int64_t cap_rows, hipStrea
 // 64-column slab; smaller layers split K over the eight waves, on 16-row
 // tiles of 32 columns when there are enough rows, else 16.  A split of few
 // chunks leaves waves without one, so LinearAnyOp up to d_in 64 takes the
-// 128-row tiles from 1500 split tiles on, with the split form's results
-// (LinearAnyChunkOp): 60k rows, 2 x 9 -> 47 30.9 -> 10.8 us
-// (14.1 on k_linear_f32), 32k rows, 2 x 22 -> 100 34.3 -> 14.2 (22.8), 16k rows,
-// 2 x 49 -> 255 33.4 -> 18.2 (35.0); 8k rows, 2 x 49 -> 47, 1000 split tiles, is
-// the other way round, 10.3 against 11.4.  Returns false for more than eight
+// 128-row tiles from 1500 split tiles on (its results are the same bits in both
+// forms): 60k rows, 2 x 9 -> 47 30.9 -> 10.8 us (14.1 on k_linear_f32), 32k
+// rows, 2 x 22 -> 100 34.3 -> 14.2 (22.8), 16k rows, 2 x 49 -> 255 33.4 -> 18.2
+// (35.0); 8k rows, 2 x 49 -> 47, 1000 split tiles, is the other way round, 10.3
+// against 11.4.  Returns false for more than eight
 // chunks on many rows (the 128-row tiles would not fit their registers): the
 // fp32 slab kernel takes d_in % 4 == 0 there, k_linear_f32 other widths.
 template <int NCH, class Op>
@@ -714,7 +714,7 @@ bool launch_parts_for(const int32_t* sizes, const Op& op, int64_t cap_rows, hipS
   if constexpr (std::is_same<Op, parts::LinearAnyOp>::value && NCH <= 4) {
     const int64_t split_tiles = ((cap_rows + 15) / 16) * ((N + 31) / 32);
     if (split_tiles >= 1500) {
-      launch_parts<NCH, 4, 1, 1, 8>(sizes, parts::LinearAnyChunkOp{op}, cap_rows, s);
+      launch_parts<NCH, 4, 1, 1, 8>(sizes, op, cap_rows, s);
       return true;
     }
   }

@@ -62,6 +62,34 @@ def test_linear_f32_widths(orc, dg, graph, d_in, d_out, rows):
     assert max(errs) <= 5e-6, errs
 
 
+@pytest.mark.parametrize("d_in, d_out, rows", [(13, 255, 17001), (18, 255, 20000), (18, 41, 900), (33, 172, 20000),
+                                               (75, 255, 17001), (125, 100, 20000), (127, 255, 20000), (125, 41, 2000),
+                                               (253, 47, 3000)])
+def test_linear_f32_error_is_no_larger_than_fp32_sums(dg, graph, d_in, d_out, rows):
+    """Widths that four does not divide, on rows with many zeros (ReLU outputs):
+    the error of the part products against 64 bits (2-norm) is no larger than
+    that of a plain fp32 sum, one fused multiply-add after another."""
+    print(f"f32 {d_in} -> {d_out}, {rows} rows", flush=True)
+    w = to_torch_weights(dg.sage_weights([d_in, d_out], 6))
+    seeds = torch.from_numpy(dg.permutation(graph.num_nodes, 7)[:rows]).cuda()
+    blocks = gmb.sample_blocks(csr_on_device(graph), seeds, [5], 8)
+    x = gmb.gather_features(blocks, to_torch_feats(dg.features(graph.num_nodes, d_in, 5, "f32"))).clamp_min(0)
+    ws = gmb._aligned_bytes(gmb.forward_workspace_bytes(blocks, w), x.device)[1]
+    got = gmb.sage_forward(blocks, x, w, workspace=ws).double()
+    mean = ws[:4 * rows * d_in].view(torch.float32).view(rows, d_in)   # the first array of the workspace
+    a = torch.cat((x[:rows], mean), 1).double()
+    b = torch.cat((w.w_self[0], w.w_neigh[0])).double()
+    bias = w.bias[0].double()
+    want = a @ b + bias
+    plain = torch.zeros((rows, d_out), device="cuda")
+    for k in range(2 * d_in):   # products and sums of fp32 values are exact enough in 64 bits, then rounded once
+        plain = (plain.double() + a[:, k:k + 1] * b[k]).float()
+    plain = (plain.double() + bias).float().double()
+    err, bound = (got - want).norm() / want.norm(), (plain - want).norm() / want.norm()
+    print(f"error {float(err):.3e}, of a plain fp32 sum {float(bound):.3e}", flush=True)
+    assert float(err) <= float(bound)
+
+
 @pytest.mark.parametrize("d_in, d_out", [(9, 47), (16, 33), (17, 100), (31, 255), (33, 64), (63, 172), (64, 47)])
 def test_linear_f32_tilings_agree(dg, graph, d_in, d_out):
     """The same rows in batches on either side of the line between the split
