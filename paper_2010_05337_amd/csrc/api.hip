@@ -467,7 +467,9 @@ int check_blocks(const gmb_blocks* b) {
   return GMB_OK;
 }
 
-int plan_forward(const gmb_blocks* b, const gmb_sage_weights* w, ForwardPlan* plan) {
+// keep_mean0 = false: without room for layer 0's mean (the fp32 copies that a
+// bf16 model's backward makes).
+int plan_forward(const gmb_blocks* b, const gmb_sage_weights* w, ForwardPlan* plan, bool keep_mean0 = true) {
   int st = check_blocks(b);
   if (st != GMB_OK) return st;
   if (!w) return fail(GMB_EINVAL, "weights is NULL");
@@ -488,7 +490,8 @@ int plan_forward(const gmb_blocks* b, const gmb_sage_weights* w, ForwardPlan* pl
   size_t off = 0;
   for (int l = 0; l < w->num_layers; ++l) {
     p.off_agg[l] = off;
-    off = align_up(off + static_cast<size_t>(std::max<int64_t>(b->blk[l].cap_dst, 1)) * w->dims[l] * es);
+    if (l > 0 || keep_mean0)
+      off = align_up(off + static_cast<size_t>(std::max<int64_t>(b->blk[l].cap_dst, 1)) * w->dims[l] * es);
   }
   for (int l = 0; l + 1 < w->num_layers; ++l) {
     p.off_hidden[l] = off;
@@ -749,8 +752,8 @@ struct BackwardPlan {
   int64_t clear_len;                           // ints cleared at the start (counters + scan states)
   size_t total;
   // bf16 models: fp32 copies of what the upper layers' products read (in a
-  // forward workspace laid out for fp32; their matrices), after the fp32
-  // backward's own workspace
+  // forward workspace laid out for fp32, without layer 0's mean; their
+  // matrices), after the fp32 backward's own workspace
   size_t off_shadow, off_w32[GMB_MAX_LAYERS][2];
   size_t fp32_total;
 };
@@ -789,7 +792,7 @@ int plan_backward(const gmb_blocks* b, const gmb_sage_weights* w, BackwardPlan* 
   int st = plan_backward_f32(b, &w32, &p, false);
   if (st != GMB_OK) return st;
   ForwardPlan fp32;
-  plan_forward(b, &w32, &fp32);
+  plan_forward(b, &w32, &fp32, false);
   size_t off = p.total;
   p.fp32_total = p.total;
   p.off_shadow = off;
@@ -816,7 +819,7 @@ int plan_backward_f32(const gmb_blocks* b, const gmb_sage_weights* w, BackwardPl
   for (int l = first; l < L; ++l)
     if (w->dims[l + 1] > 640) return fail(GMB_EINVAL, "dims[%d]=%d above 640 (input-gradient kernel)", l + 1, w->dims[l + 1]);
   BackwardPlan p{};
-  size_t buf = 0, dm = 0, part = 0, src = 1, nnz = 1;
+  size_t buf = 0, dm = 0, part = 0, src = 1, nnz = 1, cursors = 0;
   for (int l = 0; l < L; ++l) {
     const int d_in = w->dims[l], d_out = w->dims[l + 1];
     const gmb_block& k = b->blk[l];
@@ -828,6 +831,7 @@ int plan_backward_f32(const gmb_blocks* b, const gmb_sage_weights* w, BackwardPl
       dm = std::max(dm, static_cast<size_t>(std::max<int64_t>(k.cap_dst, 1)) * d_in);
       src = std::max(src, static_cast<size_t>(k.cap_src));
       nnz = std::max(nnz, static_cast<size_t>(k.cap_nnz));
+      if (k.cap_nnz <= kPlaceNnz) cursors = std::max(cursors, static_cast<size_t>(k.cap_src));
     }
     const size_t parts = gmb::wgrad_parts(std::max<int64_t>(k.cap_dst, 1), d_in, d_out);
     part = std::max(part, parts * (2 * static_cast<size_t>(d_in) + 1) * gmb::wgrad_ldp(d_out));
@@ -851,7 +855,7 @@ int plan_backward_f32(const gmb_blocks* b, const gmb_sage_weights* w, BackwardPl
   p.off_off = off;
   off = align_up(off + 4 * (src + 1));
   p.off_pos = off;
-  off = align_up(off + 4 * src);
+  off = align_up(off + 4 * cursors);
   p.off_place = off;
   if (nnz > kPlaceNnz) off = align_up(off + 4 * nnz);
   p.off_csc = off;
@@ -898,7 +902,7 @@ int run_backward(const gmb_blocks* blocks, const void* x, const gmb_sage_weights
   int st = plan_backward(blocks, weights, &p, embed);
   if (st != GMB_OK) return st;
   ForwardPlan fp;
-  plan_forward(blocks, weights, &fp);
+  plan_forward(blocks, weights, &fp, !lo);
   st = check_grads(grads, weights);
   if (st != GMB_OK) return st;
   if (!fwd_ws || fwd_ws_bytes < fp.total) return fail(GMB_ENOSPC, "forward workspace missing or too small");
@@ -918,7 +922,7 @@ int run_backward(const gmb_blocks* blocks, const void* x, const gmb_sage_weights
     char* base = static_cast<char*>(ws);
     const gmb_sage_weights w32 = widened_weights(weights, p, base);
     ForwardPlan f32;
-    plan_forward(blocks, &w32, &f32);
+    plan_forward(blocks, &w32, &f32, false);
     const char* fsrc = static_cast<const char*>(fwd_ws);
     gmb::WidenArgs wa{};
     auto add = [&](const void* src, void* dst, const int32_t* rows_dev, int64_t cap_rows, int64_t cols) {

@@ -97,6 +97,46 @@ def test_workspace_bytes_and_caps(L):
     assert b >= a
 
 
+def _layers(dims, caps, dtype):
+    """Blocks of the capacities caps[l] = (cap_dst, cap_src, cap_nnz) and
+    weights of the widths dims, on addresses that nothing reads."""
+    import paper_2010_05337_amd as gmb
+    b, w = gmb.BlocksStruct(), gmb.WeightsStruct()
+    b.num_layers = w.num_layers = len(caps)
+    b.num_seeds = caps[-1][0]
+    w.dtype = dtype
+    for i, d in enumerate(dims):
+        w.dims[i] = d
+    for l, (dst, src, nnz) in enumerate(caps):
+        k = b.blk[l]
+        k.indptr = k.indices = k.nbr = k.src_ids = k.sizes = 1 << 40
+        k.cap_dst, k.cap_src, k.cap_nnz, k.fanout, k.layer = dst, src, nnz, 16, l
+        w.w_self[l] = w.w_neigh[l] = w.bias[l] = 1 << 41
+    return ctypes.byref(b), ctypes.byref(w)
+
+
+def _up(n):
+    return (n + 255) // 256 * 256
+
+
+def test_backward_workspace_holds_what_is_used(L):
+    """A bf16 model's backward adds fp32 copies of the upper layers' means,
+    inputs and matrices, and nothing for layer 0; a block takes either cursors
+    (one word per source) or places (one per edge), not both."""
+    one = [(1000, 9000, 16000)]
+    assert L.gmb_backward_workspace_bytes(*_layers([128, 47], one, 1)) == \
+        L.gmb_backward_workspace_bytes(*_layers([128, 47], one, 0)) > 0
+    two = [(40_000, 300_000, 500_000), (4000, 40_000, 36_000)]
+    dims = [128, 256, 47]
+    copies = _up(4 * 4000 * 256) + _up(4 * 40_000 * 256) + 2 * _up(4 * 256 * 47)
+    assert L.gmb_backward_workspace_bytes(*_layers(dims, two, 1)) == \
+        L.gmb_backward_workspace_bytes(*_layers(dims, two, 0)) + copies
+    n, src = 1 << 18, 200_000
+    cursors, places = (L.gmb_backward_embedding_workspace_bytes(*_layers([16, 8], [(20_000, src, nnz)], 0))
+                       for nnz in (n, n + 1))
+    assert places - cursors == _up(8 * (n + 1)) - _up(8 * n) + _up(4 * (n + 1)) - _up(4 * src)
+
+
 @pytest.mark.parametrize("slots", ["64", "8192"])
 def test_owner_table_hook_leaves_the_plan_alone(L, slots, monkeypatch):
     """The limit on the owners' LDS tables is no part of the plan: a workspace
