@@ -96,10 +96,11 @@ int32_t owner_slots() {
 // Largest edge capacity at which the last hop, too, dedups through the
 // per-vertex table: two kernels instead of the owners' three, whose fixed
 // cost is the larger, while the table's random accesses grow with the edges.
-// sample_blocks on the 2.4M-vertex graph, table against owners: 31 k edges of
-// capacity 36.0 / 47.5 us, 127 k 44.7 / 53.7, 253 k 52.7 / 56.8, 384 k 57.2 /
-// 57.7, 507 k 65.7 / 62.6, 990 k 87.8 / 75.5 us; the line is drawn below the
-// crossing, since a larger graph's table spreads over more lines.
+// sample_blocks, table against owners, on graphs of 100k, 2.4M and 100M vertices
+// (degrees 16, 30, 16): 32 k edges of capacity 31.0 / 42.9, 29.1 / 45.9, 30.3 /
+// 47.4 us; 110 k 39.2 / 52.2, 38.2 / 54.4, 39.4 / 56.6; 253 k 50.8 / 56.1, 54.6 /
+// 64.4, 54.0 / 65.0; 256 k (one hop) 55.6 / 59.0, 71.5 / 79.0, 71.4 / 79.0; 528 k
+// 70.8 / 65.8, 79.7 / 74.4, 80.6 / 76.5.
 constexpr int64_t kTableLastNnz = 262144;
 
 // Fills the plan; returns GMB_OK or an argument error (message set).
@@ -159,10 +160,12 @@ int plan_sampling(int32_t num_seeds, const int32_t* fanouts, int32_t num_layers,
       hp.routers = static_cast<int32_t>(routers);
       const int64_t pairs = hp.cap_nnz + hp.cap_dst;
       int64_t owners = std::max<int64_t>(1, (pairs + gmb::kOwnerPairs - 1) / gmb::kOwnerPairs);
-      // one owner per CU at a time: a count just past a multiple of the CU
-      // count would run its last owners as a wave of their own, doubling
-      // the kernel; take the multiple below while each owner's share at full
-      // capacity still fits three quarters of its table
+      // a count just past a multiple of the CU count leaves a few CUs with an
+      // owner more than the others, and the kernel waits for them (two owners,
+      // 65.5 KB of LDS each, fit a CU); take the multiple below while each
+      // owner's share at full capacity still fits three quarters of its table:
+      // sample_blocks with 258 owners 97.0 us, 256 95.1; 280 115.6, 256 109.9;
+      // 515 160.0, 512 147.1
       if (owners > gmb::kComputeUnits) {
         const int64_t lower = (owners - 1) / gmb::kComputeUnits * gmb::kComputeUnits;
         if ((pairs + lower - 1) / lower <= gmb::kOwnerSlots * 3 / 4) owners = lower;
@@ -327,7 +330,8 @@ int run_sampling(const gmb_csr* csr, const int32_t* seeds, int32_t num_seeds, in
     gmb::DeferredArgs fix{hops[0].local, hops[0].sizes + 3 - gmb::kNnz, 1};
     if (h > 0) fix = gmb::DeferredArgs{hops[h - 1].local, hops[h - 1].sizes, std::max<int64_t>(hops[h - 1].cap_nnz, 1)};
     if (hp.table) {
-      if (h > 0 || !seed_sample) e = gmb::launch_sample_table(g, ids, hops[h], table, status, k0, k1, h == 0 ? 1 : 0, fix, s);
+      if (h > 0 || !seed_sample)
+        e = gmb::launch_sample_table(g, ids, hops[h], table, status, k0, k1, h == 0 ? 1 : 0, fix, s);
       if (e != hipSuccess) return hip_fail(e, "sample launch");
       gmb::AssignArgs aa{};
       aa.nbr = hops[h].nbr;
@@ -1002,10 +1006,10 @@ int run_backward(const gmb_blocks* blocks, const void* x, const gmb_sage_weights
     gmb::WgradArgs defer{};
     gmb::ReduceArgs fold{};
     const bool first_lo = lo && l == 0;
-    e = gmb::launch_wgrad(bk.sizes, first_lo ? lo->x : h_in, first_lo ? lo->mean : m, first_lo ? 1 : 0, d_in, cur, p.ldz[l], d_out, std::max<int64_t>(bk.cap_dst, 1), part,
-                          grads->d_self[l], grads->d_neigh[l], grads->d_bias[l], top ? loss_rows : nullptr,
-                          blocks->num_seeds, top ? loss : nullptr, beside_scan ? &defer : nullptr,
-                          below ? &fold : nullptr, s);
+    e = gmb::launch_wgrad(bk.sizes, first_lo ? lo->x : h_in, first_lo ? lo->mean : m, first_lo ? 1 : 0, d_in, cur,
+                          p.ldz[l], d_out, std::max<int64_t>(bk.cap_dst, 1), part, grads->d_self[l],
+                          grads->d_neigh[l], grads->d_bias[l], top ? loss_rows : nullptr, blocks->num_seeds,
+                          top ? loss : nullptr, beside_scan ? &defer : nullptr, below ? &fold : nullptr, s);
     if (e != hipSuccess) return hip_fail(e, "weight-gradient launch");
     if (!below) break;
     int32_t* place = bk.cap_nnz > kPlaceNnz ? reinterpret_cast<int32_t*>(base + p.off_place) : nullptr;
@@ -1020,8 +1024,8 @@ int run_backward(const gmb_blocks* blocks, const void* x, const gmb_sage_weights
     // 0 (learnable embeddings) the input gradient goes into the table rows
     uint32_t* scan_state = reinterpret_cast<uint32_t*>(cnt + p.cnt_len + (embed ? l : l - 1) * p.scan_len);
     const void* mask = l == 0 ? nullptr : (lo ? lo->hidden[l - 1] : static_cast<const void*>(h_in));
-    e = gmb::launch_mean_backward(bk.sizes, bk.indptr, bk.indices, bk.cap_nnz, bk.fanout, dM, mask, lo ? 1 : 0, d_in, other, bk.cap_dst, bk.cap_src, cnt, offs, pos, place,
-                                  scan_state, csc, long_rows, l == 0 ? table : nullptr, bk.src_ids, num_nodes,
+    e = gmb::launch_mean_backward(bk.sizes, bk.indptr, bk.indices, bk.cap_nnz, bk.fanout, dM, mask, lo ? 1 : 0, d_in,
+                                  other, bk.cap_dst, bk.cap_src, cnt, offs, pos, place, scan_state, csc, long_rows, l == 0 ? table : nullptr, bk.src_ids, num_nodes,
                                   emb_lr, beside_scan ? &defer : nullptr, &fold, loss ? loss : grads->d_bias[0], s);
     if (e != hipSuccess) return hip_fail(e, "mean-backward launch");
     std::swap(cur, other);

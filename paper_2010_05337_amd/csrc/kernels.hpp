@@ -88,8 +88,7 @@ constexpr int kMaxSpan = 1024;
 constexpr int kOwnerSlots = 8192;
 // pairs per owner the plan aims at, at full capacity (half the table)
 constexpr int64_t kOwnerPairs = 4096;
-// compute units of the MI355X (gfx950); an owner's LDS table takes most of
-// a CU's LDS, so one owner workgroup runs per CU at a time
+// compute units of the MI355X (gfx950)
 constexpr int kComputeUnits = 256;
 
 // Sampling arguments of one hop (fan-out f, model layer `layer`); the
@@ -310,8 +309,8 @@ int64_t csc_scan_tiles(int64_t cap_src);
 // writing the masked gradient into dH (out unused).
 // With `defer` (from launch_wgrad) the transpose scan's grid also runs the
 // weight gradient's products, with `fold` the fill's grid its reduction.
-// If a wait of the scan runs out (max_spins sleeps; 0: kLookbackSpins), every row of dH becomes NaN (a table stays as it is), and so does
-// *report.
+// If a wait of the scan runs out (max_spins sleeps; 0: kLookbackSpins), every
+// row of dH becomes NaN (a table stays as it is), and so does *report.
 hipError_t launch_mean_backward(const int32_t* sizes, const int32_t* indptr, const int32_t* local,
                                 int64_t cap_nnz, int32_t fanout, const float* dM, const void* out, int out_bf16, int d,
                                 float* dH, int64_t cap_dst, int64_t cap_src, int32_t* cnt, int32_t* off,

@@ -635,8 +635,9 @@ __device__ __forceinline__ void for_each_edge_slot(const EdgeView& ev, int32_t n
   const int64_t total = static_cast<int64_t>(n_dst) * fanout;
   for (int64_t t = t0; t < total; t += stride) {
     // (the slots number below 2^31 in every sampled block: a 32-bit division)
-    const int64_t v = total <= INT32_MAX ? static_cast<int64_t>(static_cast<uint32_t>(t) / static_cast<uint32_t>(fanout))
-                                         : t / fanout;
+    const int64_t v = total <= INT32_MAX
+                          ? static_cast<int64_t>(static_cast<uint32_t>(t) / static_cast<uint32_t>(fanout))
+                          : t / fanout;
     const int32_t j = static_cast<int32_t>(t - v * fanout);
     int32_t b, e;
     edge_range(ev, v, b, e);

@@ -400,7 +400,10 @@ __global__ __launch_bounds__(256) void k_sample_table(CsrArgs ga, const int32_t*
 // seeds over all waves, 4 keeps larger batches to few chunks.
 // One launch and two rounds of reads fewer than k_seed_scan followed by
 // k_sample_table: 5.4 + 4.9 -> 8.4 us at 1000 seeds and fan-out 5, 15.5 + 7.4 ->
-// 13.6 us at 4000 and 10.  Above 8192 seeds every workgroup would read too many.
+// 13.6 us at 4000 and 10.  The reads grow with the square of the seeds: one hop
+// of sample_blocks over 8192 seeds, in one launch and apart, 24.0 / 29.5 us at
+// fan-out 5, 39.9 / 51.7 at 25, 54.0 / 54.8 at 33, 44.9 / 45.0 at 64 (16 seeds a
+// workgroup); from 64 to 4096 seeds one launch is the faster at every fan-out.
 constexpr int kSeedSampleSeeds = 8192;
 template <int G, int NV, bool WIDE, int ITEMS>
 __global__ __launch_bounds__(1024) void k_seed_sample(SeedArgs a, CsrArgs ga, int32_t* nbr, uint32_t* table,

@@ -66,7 +66,9 @@ hipError_t launch_xent(const float*, const int32_t*, int, int, int, float*, floa
   return hipSuccess;
 }
 int wgrad_ldp(int d_out) { return (d_out + 3) / 4 * 4; }
-int wgrad_parts(int64_t cap_rows, int, int) { return static_cast<int>(std::min<int64_t>(8, std::max<int64_t>(1, cap_rows / 64))); }
+int wgrad_parts(int64_t cap_rows, int, int) {
+  return static_cast<int>(std::min<int64_t>(8, std::max<int64_t>(1, cap_rows / 64)));
+}
 hipError_t launch_wgrad(const int32_t*, const void*, const void*, int, int, const float*, int, int, int64_t, float*,
                         float*, float*, float*, const float*, int, float*, WgradArgs*, ReduceArgs*, hipStream_t) {
   return hipSuccess;
