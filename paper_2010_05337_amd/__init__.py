@@ -528,7 +528,8 @@ def sage_backward(blocks: Blocks, feats: torch.Tensor, weights: SageWeights, log
     int32, one per seed).  Returns (grads, loss) with loss a 1-element
     float32 device tensor.  With `embedding` (the fp32 [num_nodes, dims[0]]
     table the layer-0 inputs were taken from) the gradient in the input
-    rows is applied to the table as an SGD step of size emb_lr."""
+    rows is applied to the table as an SGD step of size emb_lr.  A NaN loss
+    may also mean that a bounded wait on the device ran out (gmb.h)."""
     _require_cuda(labels, "labels")
     if labels.dtype != torch.int32 or labels.numel() < blocks.num_seeds:
         raise TypeError("labels must be int32 with one entry per seed")

@@ -166,7 +166,7 @@ struct LinearOp {
 // 1.19 times its error against 64 bits).  So every chunk's products are summed
 // from zero and the chunks' sums then added in order (kByChunk; the split form
 // sums its waves' so anyway, with the same bits), and up to two chunks two more
-// products are taken (kEight; the ninth is below 2^-32 of the product).  The
+// products are taken (kEight; the ninth is below 2^-30 of the product).  The
 // error is then 0.3 to 0.83 times the fp32 kernel's on normal, positive and
 // ReLU rows of widths 9 to 127; 60k rows, 2 x 19 -> 255 30.4 -> 32.2 us, 2 x 127
 // -> 255 75 as before (the chunks' sums take the registers of the tile before,

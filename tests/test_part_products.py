@@ -74,6 +74,21 @@ def test_few_significant_bits_give_exact_products():
     assert np.array_equal(kept, c.astype(np.float64) * b.astype(np.float64))
 
 
+def test_eight_terms_drop_one_below_2_to_minus_30():
+    """Narrow layers of widths that four does not divide also keep a1 b2 and
+    a2 b1: what is left out is a2 b2, and on short dot products the error
+    against fp64 is smaller than the six terms'."""
+    eight = ((1, 2), (2, 1), (0, 2), (1, 1), (2, 0), (0, 1), (1, 0), (0, 0))
+    rng = np.random.default_rng(6)
+    a = rng.standard_normal((4000, 26)).astype(np.float32)
+    b = rng.standard_normal((4000, 26)).astype(np.float32)
+    a2, b2 = cut3(a)[2].astype(np.float64), cut3(b)[2].astype(np.float64)
+    assert np.all(np.abs(a2 * b2) < 2.0 ** -30 * np.abs(a.astype(np.float64) * b))
+    exact = (a.astype(np.float64) * b).sum(axis=1)
+    six, more = parts_dot(a, b), parts_dot(a, b, eight)
+    assert np.linalg.norm(more - exact) < np.linalg.norm(six - exact)
+
+
 def test_dropped_terms_are_below_2_to_minus_21():
     rng = np.random.default_rng(3)
     a = rng.standard_normal(50000).astype(np.float32)
